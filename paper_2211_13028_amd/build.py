@@ -21,10 +21,10 @@ SOURCES = ["api.cpp", "k_basic.hip", "k_ttm.hip", "k_sketch.hip", "k_qr.hip", "k
 ARCH = "gfx950"
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# The eigensolver file's matrix-core loops keep their accumulators in ordinary VGPRs: with the
+# These files' matrix-core loops keep their accumulators in ordinary VGPRs: with the
 # compiler's default choice of accumulation registers, the binary64 Gram loop copied every
 # accumulator out and back around each unrolled group of products.
-FILE_FLAGS = {"k_eig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"k_eig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "k_norm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _hipcc() -> str:

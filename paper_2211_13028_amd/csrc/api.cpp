@@ -913,11 +913,10 @@ int plan_rel_error(Ctx& c, const rt_tensor* X, const double* G, const int32_t* r
   const int64_t Brest = T.after(0);
   void* w = c.take(recon_residual_ws(X->dims[0], Brest));
   if (!c.dry) {
-    c.chk(launch_recon_residual(X->data, X->dtype, X->dims[0], Brest, U[0], static_cast<const double*>(T.p), r[0],
-                                out, w, c.st));
     int64_t ng = 1;
     for (int k = 0; k < d; ++k) ng *= r[k];
-    c.chk(launch_sumsq_f64(G, ng, out + 2, c.st));
+    c.chk(launch_recon_residual(X->data, X->dtype, X->dims[0], Brest, U[0], static_cast<const double*>(T.p), r[0], G,
+                                ng, out, w, c.st));
   }
   return RT_OK;
 }

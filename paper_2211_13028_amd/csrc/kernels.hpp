@@ -191,14 +191,12 @@ hipError_t launch_column_sign(double* V, int64_t n, int r, hipStream_t st);
 
 // ------------------------------------------------------------------ k_norm.hip
 // Residual of X viewed as (I1, Brest) against U1 (I1 x r1) times T (r1 x Brest),
-// both binary64: out[0] += ||X - U1 T||^2, out[1] = ||X||^2, out[3] = #nonfinite(X);
-// out[2] is left to the caller.  Deterministic.
+// both binary64: out[0] = ||X - U1 T||^2, out[1] = ||X||^2, out[3] = #nonfinite(X);
+// out[2] = ||G||^2 for the binary64 array G of ng values.  Deterministic.
 size_t recon_residual_ws(int64_t I1, int64_t Brest);
 hipError_t launch_recon_residual(const void* X, rt_dtype xdt, int64_t I1, int64_t Brest,
-                                 const double* U1, const double* T, int64_t r1, double* out,
-                                 void* ws, hipStream_t st);
-// out[2] = ||G||^2 for a binary64 array of n values.
-hipError_t launch_sumsq_f64(const double* g, int64_t n, double* out_slot, hipStream_t st);
+                                 const double* U1, const double* T, int64_t r1, const double* G, int64_t ng,
+                                 double* out, void* ws, hipStream_t st);
 
 // ------------------------------------------------------------------ grouped launches
 // For the batched decomposition: each launcher below runs many independent jobs

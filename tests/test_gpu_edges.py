@@ -1,0 +1,57 @@
+"""Kernels at the sizes where their tiling can go wrong (tile edges, remainders, row and column
+splits, unaligned bases), each against plain binary64 arithmetic."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2211_13028_amd as rt
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(a, dtype=torch.float64, skew=0):
+    """`a` on the GPU, `skew` elements past an aligned base."""
+    t = torch.from_numpy(np.ascontiguousarray(a)).to(dtype)
+    buf = torch.empty(t.numel() + skew, dtype=dtype, device="cuda")
+    out = buf[skew:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+# ------------------------------------------------------------------ explicit residual
+# 64-column waves, 256-column workgroups, 16-row blocks, 64-row chunks, ranges of >= 128 rows;
+# r1 in each of the five k lengths.  Values are exact in every dtype (multiples of 1/8), so the
+# binary64 sums differ by their order only: 4096 terms of one sign, 4096 * 2^-53 < 1e-12.
+@pytest.mark.parametrize("dims,r,dtype,skew", [
+    ((16, 8, 8), (1, 2, 2), torch.float64, 0),
+    ((17, 9, 7), (9, 3, 2), torch.float32, 0),
+    ((129, 16, 16), (16, 4, 4), torch.bfloat16, 0),
+    ((300, 13, 20), (17, 5, 3), torch.float32, 0),
+    ((300, 13, 20), (24, 5, 3), torch.float32, 1),
+    ((65, 5, 53), (25, 5, 7), torch.bfloat16, 3),
+    ((257, 12, 24), (33, 4, 9), torch.float32, 0),
+    ((128, 257), (64, 40), torch.float64, 1),
+])
+@pytest.mark.parametrize("bad", [False, True])
+def test_rel_error_tiles(dims, r, dtype, skew, bad):
+    rng = np.random.default_rng(sum(dims))
+    X = rng.integers(-16, 17, size=dims) / 8.0
+    G = rng.integers(-4, 5, size=r) / 4.0
+    Us = [rng.integers(-4, 5, size=(n, k)) / 8.0 for n, k in zip(dims, r)]
+    xh = G
+    for k, U in enumerate(Us):
+        xh = np.moveaxis(np.tensordot(xh, U, axes=([k], [1])), -1, k)
+    nbad = 0
+    if bad:
+        flat = X.reshape(-1)
+        where = np.array([0, flat.size // 2, flat.size - 1])
+        flat[where] = [np.nan, np.inf, -np.inf]
+        nbad = 3
+    fin = np.isfinite(X)
+    res2, x2 = float(((X - xh)[fin] ** 2).sum()), float((X[fin] ** 2).sum())
+    e, n = rt.rtucker_rel_error(_dev(X, dtype, skew), _dev(G), [_dev(U) for U in Us], allow_nonfinite=True)
+    assert n["nonfinite"] == nbad
+    assert abs(n["res2"] - res2) <= 1e-12 * res2
+    assert abs(n["x2"] - x2) <= 1e-12 * x2
+    assert abs(n["g2"] - float((G ** 2).sum())) <= 1e-12 * float((G ** 2).sum())
+    assert abs(e - (res2 / x2) ** 0.5) <= 1e-12 * e
