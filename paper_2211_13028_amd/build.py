@@ -24,7 +24,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall", "-Wno-
 # These files' matrix-core loops keep their accumulators in ordinary VGPRs: with the
 # compiler's default choice of accumulation registers, the binary64 Gram loop copied every
 # accumulator out and back around each unrolled group of products.
-FILE_FLAGS = {"k_eig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "k_norm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"k_eig.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "k_norm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "k_qr.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _hipcc() -> str:

@@ -142,17 +142,67 @@ inline size_t dtype_size(rt_dtype t) {
 // the waves exchange data through LDS alone.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// 1/sqrt(x) for normal x > 0: hardware estimate refined by two Newton steps
-// (each roughly doubles the correct bits), accurate to a few units in the last place.
-__device__ __forceinline__ double rsq_refined(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = fma(x * y, y, -1.0);  // x y^2 - 1
-    y = fma(-0.5 * y, e, y);
-  }
-  return y;
+// DPP moves on the two halves of a binary64 value (every source lane used here
+// lies inside the row, so bound_ctrl never takes effect and no old value is needed)
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int64_t u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(u & 0xffffffff), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const int64_t u = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(static_cast<int>(u & 0xffffffff), lane);
+  const int hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
 }
 
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_rows_f64(double v, double old) {
+  const int64_t u = __double_as_longlong(v), o = __double_as_longlong(old);
+  const int lo = __builtin_amdgcn_update_dpp(static_cast<int>(o & 0xffffffff), static_cast<int>(u & 0xffffffff),
+                                             CTRL, ROW_MASK, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(static_cast<int>(o >> 32), static_cast<int>(u >> 32), CTRL,
+                                             ROW_MASK, 0xF, false);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+// sum / max over the whole wave; every lane of every wave gets bitwise the same value
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0x141>(v);
+  v += dpp_f64<0x140>(v);
+  v += dpp_rows_f64<0x142, 0xA>(v, 0.0);  // row_bcast:15 -> rows 1, 3
+  v += dpp_rows_f64<0x143, 0xC>(v, 0.0);  // row_bcast:31 -> rows 2, 3
+  return readlane_f64(v, kWave - 1);
+}
+__device__ __forceinline__ double wave_max_f64(double v) {
+  v = fmax(v, dpp_f64<0xB1>(v));
+  v = fmax(v, dpp_f64<0x4E>(v));
+  v = fmax(v, dpp_f64<0x141>(v));
+  v = fmax(v, dpp_f64<0x140>(v));
+  v = fmax(v, dpp_rows_f64<0x142, 0xA>(v, v));
+  v = fmax(v, dpp_rows_f64<0x143, 0xC>(v, v));
+  return readlane_f64(v, kWave - 1);
+}
+
+// 1/sqrt(x) for normal x > 0: the hardware estimate (24 bits or more) and one third-order step,
+// with e = 1 - x y^2: 1/sqrt(x) = y (1 + e/2 + 3 e^2/8 + O(e^3)); accurate to a few units in
+// the last place.  Four dependent operations instead of the six of two Newton steps: it sits
+// on the serial chain of every factorisation and reduction step.
+__device__ __forceinline__ double rsq_refined(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// 1/x for normal x, in the same way
+__device__ __forceinline__ double rcp_refined(double x) {
+  // one third-order step from the hardware estimate: 1/x = y (1 + e + e^2 + O(e^3)), e = 1 - x y
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
+}
 
 }  // namespace rt

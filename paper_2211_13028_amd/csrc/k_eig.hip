@@ -534,15 +534,6 @@ constexpr int kMaxSweeps = 30;
 constexpr int kLStride = 72;  // doubles per column of L in LDS (padding spreads banks)
 constexpr int kAStride = 65;  // doubles per row of the working matrix
 
-// DPP moves on the two halves of a binary64 value (every source lane used here
-// lies inside the row, so bound_ctrl never takes effect and no old value is needed)
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int64_t u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(u & 0xffffffff), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(u >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
 // sum over aligned groups of 16 lanes (a DPP row); every lane of a group gets bitwise the
 // same value (each step adds a value to its partner's with the operands swapped, and
 // addition commutes)
@@ -571,13 +562,6 @@ __device__ __forceinline__ void group16_sum3(double& a, double& b, double& c) {
 #undef RT_STAGE
 }
 
-
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const int64_t u = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(u & 0xffffffff), lane);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), lane);
-  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
 
 // DPP broadcast of the last lane of a row into the rows of ROW_MASK (other rows keep v)
 template <int CTRL, int ROW_MASK>
@@ -850,40 +834,6 @@ constexpr int kInvIters = 2;
 // r); aliased by the per-wave vectors and partial sums of phase 1, by E and F of phase 4,
 // and by the Jacobi L
 
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_rows_f64(double v, double old) {
-  const int64_t u = __double_as_longlong(v), o = __double_as_longlong(old);
-  const int lo = __builtin_amdgcn_update_dpp(static_cast<int>(o & 0xffffffff), static_cast<int>(u & 0xffffffff),
-                                             CTRL, ROW_MASK, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(static_cast<int>(o >> 32), static_cast<int>(u >> 32), CTRL,
-                                             ROW_MASK, 0xF, false);
-  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
-// sum / max over the whole wave; every lane of every wave gets bitwise the same value
-__device__ __forceinline__ double wave_sum_f64(double v) {
-  v += dpp_f64<0xB1>(v);
-  v += dpp_f64<0x4E>(v);
-  v += dpp_f64<0x141>(v);
-  v += dpp_f64<0x140>(v);
-  v += dpp_rows_f64<0x142, 0xA>(v, 0.0);  // row_bcast:15 -> rows 1, 3
-  v += dpp_rows_f64<0x143, 0xC>(v, 0.0);  // row_bcast:31 -> rows 2, 3
-  return readlane_f64(v, kWave - 1);
-}
-__device__ __forceinline__ double wave_max_f64(double v) {
-  v = fmax(v, dpp_f64<0xB1>(v));
-  v = fmax(v, dpp_f64<0x4E>(v));
-  v = fmax(v, dpp_f64<0x141>(v));
-  v = fmax(v, dpp_f64<0x140>(v));
-  v = fmax(v, dpp_rows_f64<0x142, 0xA>(v, v));
-  v = fmax(v, dpp_rows_f64<0x143, 0xC>(v, v));
-  return readlane_f64(v, kWave - 1);
-}
-__device__ __forceinline__ double rcp_refined(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) y = fma(y, fma(-x, y, 1.0), y);
-  return y;
-}
 // fixed pseudo-random start value in [-1/2, 1/2) for row i of eigenvector m
 // (32-bit integer finaliser of MurmurHash3)
 __device__ __forceinline__ double start_value(int i, int m) {

@@ -260,13 +260,52 @@ struct CTabPtr {
 };
 
 
-// partial Gram of one 64-row chunk of Y (first pass); C (32 or 64) bounds the columns and
-// thread (ty, tx) owns a (C / 16) x (C / 16) block of the C x C partial
+// The Gram matrix and the product Q = Y R^-1 of a 64-row chunk run on 16x16x4 binary64
+// products: lane (r16, q) supplies entry (r16, 4 s + q) of A and (4 s + q, r16) of B in step s,
+// and holds rows q + 4 v (v = 0..3) of column r16 of the result.  On the vector ALU with 4 x 4
+// outputs a thread, the LDS reads of the operands took three times as long as the products
+// (Gram kernel at n = 64: 9.0 -> 5.3 us, apply kernel 10.9 -> 8.2 us).
+typedef double cq_f64x4 __attribute__((ext_vector_type(4)));
+// doubles per staged row: with C + 2 the 16 rows of an A read fall in different banks (B reads,
+// along a row, then meet two-fold conflicts); with C + 16 the B reads are free of conflicts
+constexpr int cq_row_stride(int c) { return c + 2; }
+constexpr int cq_col_stride(int c) { return c + 16; }
+
+// G = Y^T Y of a staged 64-row chunk, stored C x C row-major.  C = 64: wave w forms the 16 rows
+// 16 w .. of all column tiles below n; C = 32: one of the four tiles.
+template <int C>
+__device__ __forceinline__ void cq_chunk_gram(const double* sy, int n, double* __restrict__ out) {
+  constexpr int kS = cq_row_stride(C);
+  constexpr int kT = C / 16;             // tiles a side
+  constexpr int kPerWave = kT * kT / 4;  // tiles a wave
+  const int lane = static_cast<int>(threadIdx.x) % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int r16 = lane % 16, q = lane / 16;
+  const int ti = wv * kPerWave / kT, tj0 = wv * kPerWave % kT;
+  cq_f64x4 acc[kPerWave];
+#pragma unroll
+  for (int j = 0; j < kPerWave; ++j) acc[j] = cq_f64x4{0.0, 0.0, 0.0, 0.0};
+  if (16 * ti < n) {
+#pragma unroll 4
+    for (int s = 0; s < kGramRows / 4; ++s) {
+      const double* row = sy + (4 * s + q) * kS + r16;
+      const double a = row[16 * ti];
+#pragma unroll
+      for (int j = 0; j < kPerWave; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, row[16 * (tj0 + j)], acc[j], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kPerWave; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) out[(16 * ti + q + 4 * v) * C + 16 * (tj0 + j) + r16] = acc[j][v];
+}
+
+// partial Gram of one 64-row chunk of Y (first pass); C (32 or 64) bounds the columns
 template <typename TY, typename TAB, int C = kCols>
 __global__ __launch_bounds__(256) void cq_gram_kernel(TAB tab) {
-  constexpr int kO = C / 16;
+  constexpr int kS = cq_row_stride(C);
   constexpr int kStep = 256 / C;  // rows between a thread's loads
-  __shared__ double sy[kGramRows][C + 1];
+  __shared__ __align__(16) double sy[kGramRows * kS];
   const CJob& J = tab[blockIdx.y];
   if (static_cast<int>(blockIdx.x) >= J.chunks) return;
   // the breakdown flag of the job starts cleared (every later kernel reads it)
@@ -283,180 +322,207 @@ __global__ __launch_bounds__(256) void cq_gram_kernel(TAB tab) {
     yv[q] = (r < J.m && j < J.n) ? static_cast<double>(ys[r * J.B]) : 0.0;
   }
 #pragma unroll
-  for (int q = 0; q < kPer; ++q) sy[rr0 + kStep * q][j] = yv[q];
+  for (int q = 0; q < kPer; ++q) sy[(rr0 + kStep * q) * kS + j] = yv[q];
   __syncthreads();
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  double acc[kO][kO] = {};
-  for (int rr = 0; rr < kGramRows; ++rr) {
-    double a[kO], b[kO];
-#pragma unroll
-    for (int u = 0; u < kO; ++u) { a[u] = sy[rr][ty * kO + u]; b[u] = sy[rr][tx * kO + u]; }
-#pragma unroll
-    for (int u = 0; u < kO; ++u)
-#pragma unroll
-      for (int v = 0; v < kO; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-  }
-  double* out = J.part + static_cast<int64_t>(blockIdx.x) * C * C;
-#pragma unroll
-  for (int u = 0; u < kO; ++u)
-#pragma unroll
-    for (int v = 0; v < kO; ++v) out[(ty * kO + u) * C + tx * kO + v] = acc[u][v];
+  cq_chunk_gram<C>(sy, J.n, J.part + static_cast<int64_t>(blockIdx.x) * C * C);
 }
 
 
 // Sum the partial Grams (fixed order), factor G = R^T R (upper R) and form R^-1: the
 // symmetric elimination on [G | I] turns the left block into R and the right block into
-// R^-T.  W = NT / 64 waves (eight for one matrix per launch, measured 4 % faster than four; four
-// in the batched launches, where many workgroups share the CUs); thread (wave w, lane j) keeps
-// column j of rows C/W w .. C/W (w + 1) - 1 of both blocks in registers for the whole factorisation (C = 32: lanes 32 .. 63 hold no
-// column and store nothing).  After each step the wave that
-// owns the next pivot row stores all its C/W rows to LDS (static register indices; rows
-// that are not being eliminated keep their values, so concurrent readers of the current
-// row see the same bits), and a step touches LDS only for reads of that row.  Every wave keeps the diagonal in registers (lane j:
-// G[j][j], updated with the same rounding as the matrix).  R goes to the first C^2
-// doubles of the job's R1 / R2 buffer, R^-1 to the second.
+// R^-T.  The C x 2C array lives in LDS and is taken 16 pivot rows (a panel) at a time:
+//  * the panel's 16 steps run in registers, without a barrier, on two waves: a lane holds the
+//    16 rows of one column, lanes 0 .. 15 of both waves the panel's own columns, the others
+//    the C columns that the panel has entries in (the later ones of G, the first ones of the
+//    right block); a multiplier is a lane read;
+//  * the rows below are then updated tile by tile with 16x16x4 binary64 products, spread over
+//    the waves: tiles on or above the diagonal of the left block, tiles up to the panel of
+//    the right one.
+// Three barriers a panel.  Bound: latency, the chain of 16 reciprocal square roots a panel (one
+// workgroup a matrix).  Before, every one of the n pivots was a step of the whole workgroup
+// with its own barrier and LDS round trip: 27 us a launch at n = 64 (five 64-row chunks), 11.5 at
+// n = 16; now 16.5 and 6.  A panel's steps take 4000 cycles (250 a pivot, the latency of the
+// reciprocal square root and the operations around it), reading the partials 7000 to 9000.
+// Rows and columns past n hold zeros and a unit diagonal entry, which factor to themselves.
+// R1 goes to the first C^2 doubles of the job's R1 buffer (when the caller wants R), R^-1 to the
+// second half of its R1 / R2 buffer.
+constexpr int kPanel = 16;
+
+// The 16 elimination steps of one panel on a wave.  x: the panel's rows of the column that the
+// lane carries; lanes 0 .. 15 carry the panel's own columns, whose entries are the pivots and
+// multipliers (each wave repeats them: the same operations on the same values, so the same
+// bits; with the lane of a pivot in a register instead of the code a step takes half as long
+// again).  On return row t of x is divided by the pivot's square root.  Returns false when a
+// pivot before row `live` is not above dmin: they are tested together at the end, on the
+// square roots that the block's diagonal then holds (NaN for a pivot that is not positive),
+// since a test in each step lengthens its chain by a third.
+__device__ __forceinline__ bool cq_panel(double (&x)[kPanel], int live, double dmin) {
+#pragma unroll
+  for (int k = 0; k < kPanel; ++k) {
+    x[k] *= rsq_refined(readlane_f64(x[k], k));
+#pragma unroll
+    for (int i = k + 1; i < kPanel; ++i) x[i] = fma(-readlane_f64(x[k], i), x[k], x[i]);
+  }
+  const int lane = static_cast<int>(threadIdx.x) % kWave;
+  double root = x[0];
+#pragma unroll
+  for (int k = 1; k < kPanel; ++k) root = (lane == k) ? x[k] : root;
+  return __all(lane >= kPanel || lane >= live || root * root > dmin);
+}
+
 template <typename TAB, int C = kCols, int NT = 256>
 __global__ __launch_bounds__(NT) void cq_chol_kernel(TAB tab, int second) {
   constexpr int kW = NT / kWave;
   constexpr int kRows = C / kW;
-  __shared__ __align__(16) double fullL[C][kWave];  // the rows of the owner of the next row
-  __shared__ __align__(16) double fullR[C][kWave];
-  __shared__ double Rs[C][C + 1];
-  __shared__ double Xs[C][C + 1];
+  constexpr int kS = 2 * C + 2;
+  __shared__ __align__(16) double S[C * kS];  // [G | I], then [R | R^-T]
+  __shared__ int brk;
   const CJob& J = tab[blockIdx.x];
-  if (*J.flag) return;  // cleared by cq_gram_kernel before the first pass
   const int n = J.n;
-  const int lane = static_cast<int>(threadIdx.x) % kWave, wv = static_cast<int>(threadIdx.x) / kWave;
+  const int tid = static_cast<int>(threadIdx.x), lane = tid % kWave;
+  const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
   const double* part = J.part + (second ? static_cast<int64_t>(J.chunks) * C * C : 0);
-  double gl[kRows], gr[kRows];
+  {
+    double gl[kRows];
 #pragma unroll
-  for (int t = 0; t < kRows; ++t) gl[t] = 0.0;
-  // chunk partials in chunk order; the loads of two chunks are in flight together
-#pragma unroll 2
-  for (int c = 0; c < J.chunks; ++c) {
-    const double* pc = part + static_cast<int64_t>(c) * C * C + kRows * wv * C + (lane < C ? lane : 0);
-    double v[kRows];
+    for (int t = 0; t < kRows; ++t) gl[t] = 0.0;
+    // chunk partials in chunk order, four chunks in flight (a whole group of four is added
+    // even where the last chunks do not exist: their values are zeros); rows and columns past
+    // n are not read
+    const double* pc = part + kRows * wv * C + (lane < C ? lane : 0);
+    for (int c0 = 0; c0 < J.chunks; c0 += 4) {
+      double v[4][kRows];
 #pragma unroll
-    for (int t = 0; t < kRows; ++t) v[t] = lane < C ? pc[t * C] : 0.0;
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-    for (int t = 0; t < kRows; ++t) gl[t] += v[t];
+        for (int t = 0; t < kRows; ++t)
+          v[u][t] = (lane < n && kRows * wv + t < n && c0 + u < J.chunks)
+                        ? pc[static_cast<int64_t>(c0 + u) * C * C + t * C]
+                        : 0.0;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < kRows; ++t) gl[t] += v[u][t];
+    }
+    if (lane < C) {
+#pragma unroll
+      for (int t = 0; t < kRows; ++t) {
+        const int row = kRows * wv + t;
+        S[row * kS + lane] = (row == lane && row >= n) ? 1.0 : gl[t];
+        S[row * kS + C + lane] = (row == lane) ? 1.0 : 0.0;
+      }
+    }
   }
-#pragma unroll
-  for (int t = 0; t < kRows; ++t) gr[t] = (kRows * wv + t == lane) ? 1.0 : 0.0;
-  for (int idx = threadIdx.x; idx < C * (C + 1); idx += NT) {
-    (&Rs[0][0])[idx] = 0.0;
-    (&Xs[0][0])[idx] = 0.0;
-  }
-#pragma unroll
-  for (int t = 0; t < kRows; ++t) {
-    fullL[kRows * wv + t][lane] = gl[t];
-    fullR[kRows * wv + t][lane] = gr[t];
-  }
+  // (the flag, cleared by cq_gram_kernel before the first pass, is read beside the partials)
+  if (tid == 0) brk = *J.flag;
   __syncthreads();
+  if (brk) return;  // uniform
   const double shift = second ? J.shift2 : J.shift1;
+  double dj = (lane < n) ? S[lane * kS + lane] : 0.0;
   if (shift > 0.0) {
     // shifted Cholesky QR: factor G + s I, s = shift * trace(G).  Its pivots are at least
     // s, so it cannot break down, and Y R^-1 spans the columns of Y with a condition
     // number of order 1 / sqrt(shift) at worst (Fukaya et al., SIAM J. Sci. Comput. 2020)
-    double tr = (lane < n) ? fullL[lane][lane] : 0.0;
+    double tr = dj;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) tr += __shfl_xor(tr, off);  // same bits in every lane
-    const double sh = shift * tr;
+    dj += (lane < n) ? shift * tr : 0.0;
     __syncthreads();  // every wave has read the diagonal
+    if (wv == 0 && lane < n) S[lane * kS + lane] = dj;
+    __syncthreads();
+  }
+  const double dmax = wave_max_f64(dj);
+  // a pivot has to exceed 1e-13 of the largest diagonal entry, and that entry has to be positive
+  const double dmin = dmax > 0.0 ? 1e-13 * dmax : __builtin_huge_val();
+  const int panels = (n + kPanel - 1) / kPanel;
+  const int r16 = lane % 16, q = lane / 16;
+  for (int p = 0; p < panels; ++p) {
+    const int k0 = kPanel * p;
+    double* row = S + k0 * kS;
+    // columns k0 + 16 .. k0 + 15 + C of [G | I]; wave 0 takes the first 48 of them
+    const int idx = kPanel + (wv == 0 ? lane - kPanel : kWave - 2 * kPanel + lane);
+    const int col = lane < kPanel ? k0 + lane : k0 + idx;
+    const bool mine = lane < kPanel ? wv == 0 : idx < kPanel + C;
+    double x[kPanel];
+    if (wv <= 1) {
 #pragma unroll
-    for (int t = 0; t < kRows; ++t)
-      if (kRows * wv + t == lane && lane < n) {
-        gl[t] += sh;
-        fullL[lane][lane] = gl[t];
+      for (int t = 0; t < kPanel; ++t) x[t] = row[t * kS + ((lane < kPanel || mine) ? col : k0)];
+    }
+    __syncthreads();  // wave 0 stores over what wave 1 has read
+    if (wv <= 1) {
+      const bool fine = cq_panel(x, n - k0, dmin);
+      if (mine) {
+#pragma unroll
+        for (int t = 0; t < kPanel; ++t) row[t * kS + col] = lane >= kPanel || lane >= t ? x[t] : 0.0;
+      }
+      if (!fine && tid == 0) brk = 1;
+    }
+    __syncthreads();
+    if (brk) break;  // uniform
+    // tiles of the row panels below: (w, j >= w) of the left block, (w, j <= p) of the right
+    int tile = 0;
+    for (int w = p + 1; w < panels; ++w)
+      for (int jj = 0; jj < (panels - w) + (p + 1); ++jj, ++tile) {
+        if (tile % kW != wv) continue;
+        const int col = jj < panels - w ? kPanel * (w + jj) : C + kPanel * (jj - (panels - w));
+        double* out = S + (kPanel * w) * kS + col + r16;
+        cq_f64x4 acc;
+        double ma[4], mb[4];  // every operand is read before the first product
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          ma[s] = row[(4 * s + q) * kS + kPanel * w + r16];
+          mb[s] = row[(4 * s + q) * kS + col + r16];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[v] = out[(q + 4 * v) * kS];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-ma[s], mb[s], acc, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[(q + 4 * v) * kS] = acc[v];
       }
     __syncthreads();
   }
-  double dj = (lane < n) ? fullL[lane][lane] : 0.0;
-  double dmax = dj;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) dmax = fmax(dmax, __shfl_xor(dmax, off));
-  bool broke = false;
-  // the loop is unrolled over k, so the owner of the next pivot row stores that row alone
-  // (its register slot is static), and the other steps' stores are skipped
-#pragma clang loop unroll(full)
-  for (int k = 0; k < C; ++k) {
-    if (k >= n || broke) continue;  // uniform
-    const double lk = fullL[k][lane], rk = fullR[k][lane];
-    double li[kRows];
-#pragma unroll
-    for (int t = 0; t < kRows; t += 2) {
-      const double2 q = *reinterpret_cast<const double2*>(&fullL[k][kRows * wv + t]);
-      li[t] = q.x;
-      li[t + 1] = q.y;
-    }
-    const double d = __longlong_as_double(
-        (static_cast<long long>(__builtin_amdgcn_readlane(static_cast<int>(__double_as_longlong(dj) >> 32), k)) << 32) |
-        static_cast<unsigned>(__builtin_amdgcn_readlane(static_cast<int>(__double_as_longlong(dj) & 0xffffffff), k)));
-    if (!(d > 1e-13 * dmax) || !(dmax > 0.0)) {  // uniform: every lane holds the same d
-      broke = true;
-      continue;
-    }
-    const double inv_s = rsq_refined(d);
-    const double lj = lk * inv_s, xj = rk * inv_s;
-    if (wv == 0 && lane < n) {
-      if (lane >= k) Rs[k][lane] = lj;  // lane == k: d / sqrt(d)
-      Xs[lane][k] = xj;
-    }
-    // every row is updated: rows up to k are final (R and R^-1 took them at their own
-    // step) and are never read again, so no per-row test is needed
-#pragma unroll
-    for (int t = 0; t < kRows; ++t) {
-      const double mult = li[t] * inv_s;
-      gl[t] = fma(-mult, lj, gl[t]);
-      gr[t] = fma(-mult, xj, gr[t]);
-    }
-    if (lane > k) dj = fma(-lj, lj, dj);
-    if (k + 1 < n && wv == (k + 1) / kRows) {
-      fullL[k + 1][lane] = gl[(k + 1) % kRows];
-      fullR[k + 1][lane] = gr[(k + 1) % kRows];
-    }
-    __syncthreads();
-  }
-  if (broke) {
-    if (threadIdx.x == 0) *J.flag = 1;
+  if (brk) {
+    if (tid == 0) *J.flag = 1;
     return;
   }
   double* R = second ? J.R2 : J.R1;
-  for (int idx = threadIdx.x; idx < C * C; idx += NT) {
+  const bool keep = !second && J.Rout;  // R1 itself is read again for R = R2 R1 only
+  for (int idx = tid; idx < C * C; idx += NT) {
     const int i = idx / C, j = idx % C;
     const bool in = i < n && j < n && j >= i;
-    R[idx] = in ? Rs[i][j] : 0.0;
-    R[C * C + idx] = in ? Xs[i][j] : 0.0;
+    if (keep) R[idx] = in ? S[i * kS + j] : 0.0;
+    R[C * C + idx] = in ? S[j * kS + C + i] : 0.0;
   }
   if (second && J.Rout) {
-    // R = R2 R1 with R1 staged in LDS (the inverse array is free now)
+    // R = R2 R1 with R1 staged in LDS (the inverse's half is free now)
     __syncthreads();
-    for (int idx = threadIdx.x; idx < n * C; idx += NT) Xs[idx / C][idx % C] = J.R1[idx];
+    for (int idx = tid; idx < n * C; idx += NT) S[(idx / C) * kS + C + idx % C] = J.R1[idx];
     __syncthreads();
-    for (int idx = threadIdx.x; idx < n * n; idx += NT) {
+    for (int idx = tid; idx < n * n; idx += NT) {
       const int i = idx / n, j = idx % n;
       double s0 = 0.0, s1 = 0.0;
       int t = i;
       for (; t + 1 <= j; t += 2) {
-        s0 = fma(Rs[i][t], Xs[t][j], s0);
-        s1 = fma(Rs[i][t + 1], Xs[t + 1][j], s1);
+        s0 = fma(S[i * kS + t], S[t * kS + C + j], s0);
+        s1 = fma(S[i * kS + t + 1], S[(t + 1) * kS + C + j], s1);
       }
-      if (t <= j) s0 = fma(Rs[i][t], Xs[t][j], s0);
+      if (t <= j) s0 = fma(S[i * kS + t], S[t * kS + C + j], s0);
       J.Rout[idx] = (j >= i) ? s0 + s1 : 0.0;
     }
   }
 }
 
 // 64 rows of Q = Y R^-1 per workgroup as a product with the explicit inverse from
-// cq_chol_kernel (4 x C/16 outputs per thread); the first pass also stores Q1 and the
-// partial Gram of its rows
+// cq_chol_kernel; the first pass also stores Q1 and the partial Gram of its rows
 template <typename TY, typename TAB, int C = kCols>
 __global__ __launch_bounds__(256) void cq_apply_kernel(TAB tab, int second) {
-  constexpr int kS = C + 2;  // even row stride keeps the double2 reads aligned
-  constexpr int kO = C / 16;
+  constexpr int kS = cq_row_stride(C), kSX = cq_col_stride(C);
+  constexpr int kT = C / 16;
   constexpr int kStep = 256 / C;
-  __shared__ __align__(16) double sy[kGramRows][kS];
-  __shared__ __align__(16) double sx[C][kS];
+  __shared__ __align__(16) double sy[kGramRows * kS];
+  __shared__ __align__(16) double sx[C * kSX];
   const CJob& J = tab[blockIdx.y];
   if (static_cast<int>(blockIdx.x) >= J.chunks) return;
   if (*J.flag) return;
@@ -481,69 +547,43 @@ __global__ __launch_bounds__(256) void cq_apply_kernel(TAB tab, int second) {
 #pragma unroll
     for (int q = 0; q < kPerX; ++q) xv[q] = Xg[(rr0 + kStep * q) * C + j];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) sy[rr0 + kStep * q][j] = yv[q];
+    for (int q = 0; q < kPer; ++q) sy[(rr0 + kStep * q) * kS + j] = yv[q];
 #pragma unroll
-    for (int q = 0; q < kPerX; ++q) sx[rr0 + kStep * q][j] = xv[q];
+    for (int q = 0; q < kPerX; ++q) sx[(rr0 + kStep * q) * kSX + j] = xv[q];
   }
   __syncthreads();
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  {
-    double acc[4][kO] = {};
+  // wave w: rows 16 w .. 16 w + 15 of the chunk, every column tile below n
+  const int lane = static_cast<int>(threadIdx.x) % kWave, wv = static_cast<int>(threadIdx.x) / kWave;
+  const int r16 = lane % 16, q = lane / 16;
+  cq_f64x4 acc[kT];
+#pragma unroll
+  for (int t = 0; t < kT; ++t) acc[t] = cq_f64x4{0.0, 0.0, 0.0, 0.0};
+  const double* yr = sy + (16 * wv + r16) * kS + q;
+  const double* xr = sx + q * kSX + r16;
 #pragma unroll 4
-    for (int t = 0; t < n; ++t) {
-      double a[4], b[kO];
+  for (int k = 0; k < n; k += 4) {  // columns and rows past n are zero
+    const double a = yr[k];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = sy[ty * 4 + u][t];
-#pragma unroll
-      for (int v = 0; v < kO; v += 2) {
-        const double2 bv = *reinterpret_cast<const double2*>(&sx[t][tx * kO + v]);
-        b[v] = bv.x;
-        b[v + 1] = bv.y;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < kO; ++v) acc[u][v] = fma(a[u], b[v], acc[u][v]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < kO; ++v) sy[ty * 4 + u][tx * kO + v] = acc[u][v];
+    for (int t = 0; t < kT; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xr[k * kSX + 16 * t], acc[t], 0, 0, 0);
   }
-  __syncthreads();
   double* out = second ? J.Q : J.Q1;
-  for (int idx = threadIdx.x; idx < kGramRows * C; idx += 256) {
-    const int rr = idx / C, j = idx % C;
-    const int64_t r = r0 + rr;
-    if (r < J.m && j < n) out[r * n + j] = sy[rr][j];
-  }
+#pragma unroll
+  for (int t = 0; t < kT; ++t)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t r = r0 + 16 * wv + q + 4 * v;
+      const int j = 16 * t + r16;
+      if (r < J.m && j < n) out[r * n + j] = acc[t][v];
+    }
   if (second) return;
   // partial Gram of these Q1 rows for the second pass (rows past m and columns past n
-  // are zero: the inputs there were zero)
-  double g[kO][kO] = {};
-#pragma unroll 4
-  for (int rr = 0; rr < kGramRows; ++rr) {
-    double a[kO], b[kO];
+  // are zero: the inputs there were zero); a wave stores over the rows that it alone has read
 #pragma unroll
-    for (int v = 0; v < kO; v += 2) {
-      const double2 av = *reinterpret_cast<const double2*>(&sy[rr][ty * kO + v]);
-      const double2 bv = *reinterpret_cast<const double2*>(&sy[rr][tx * kO + v]);
-      a[v] = av.x;
-      a[v + 1] = av.y;
-      b[v] = bv.x;
-      b[v + 1] = bv.y;
-    }
+  for (int t = 0; t < kT; ++t)
 #pragma unroll
-    for (int u = 0; u < kO; ++u)
-#pragma unroll
-      for (int v = 0; v < kO; ++v) g[u][v] = fma(a[u], b[v], g[u][v]);
-  }
-  double* gp = J.part + (static_cast<int64_t>(J.chunks) + blockIdx.x) * C * C;
-#pragma unroll
-  for (int u = 0; u < kO; ++u)
-#pragma unroll
-    for (int v = 0; v < kO; ++v) gp[(ty * kO + u) * C + tx * kO + v] = g[u][v];
+    for (int v = 0; v < 4; ++v) sy[(16 * wv + q + 4 * v) * kS + 16 * t + r16] = acc[t][v];
+  __syncthreads();
+  cq_chunk_gram<C>(sy, n, J.part + (static_cast<int64_t>(J.chunks) + blockIdx.x) * C * C);
 }
 
 

@@ -55,3 +55,35 @@ def test_rel_error_tiles(dims, r, dtype, skew, bad):
     assert abs(n["x2"] - x2) <= 1e-12 * x2
     assert abs(n["g2"] - float((G ** 2).sum())) <= 1e-12 * float((G ** 2).sum())
     assert abs(e - (res2 / x2) ** 0.5) <= 1e-12 * e
+
+
+# ------------------------------------------------------------------ QR factorisation
+# 16-column panels: one column, panel edges +-1, the widest; one row more than a 64-row chunk.
+# Singular values are within a factor of ten, so Q and R move by at most a few hundred roundings.
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64])
+@pytest.mark.parametrize("extra", [0, 1, 65])
+def test_qr_panels(n, extra):
+    m = max(n, 64 * (n // 64)) + extra
+    rng = np.random.default_rng(100 * n + extra)
+    u, _ = np.linalg.qr(rng.standard_normal((m, n)))
+    v, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    Y = (u * np.linspace(1.0, 0.1, n)) @ v.T
+    Q, R = rt.rtucker_qr(_dev(Y), want_r=True)
+    Q, R = Q.cpu().numpy(), R.cpu().numpy()
+    q, r = np.linalg.qr(Y)
+    s = np.where(np.diagonal(r) < 0, -1.0, 1.0)
+    assert np.all(np.tril(R, -1) == 0.0) and np.all(np.diagonal(R) > 0.0)
+    assert np.abs(Q.T @ Q - np.eye(n)).max() <= 1e-13
+    assert np.abs(Q - q * s).max() <= 1e-12
+    assert np.abs(R - r * s[:, None]).max() <= 1e-12
+
+
+# a column that repeats another one has to reach the Householder path from any panel
+@pytest.mark.parametrize("n,dup", [(5, 4), (17, 16), (33, 20), (49, 48), (64, 40)])
+def test_qr_breakdown_in_any_panel(n, dup):
+    rng = np.random.default_rng(n)
+    Y = rng.standard_normal((130, n))
+    Y[:, dup] = Y[:, 0]
+    Q = rt.rtucker_qr(_dev(Y)).cpu().numpy()
+    assert np.abs(Q.T @ Q - np.eye(n)).max() <= 1e-13
+    assert np.abs(Q @ (Q.T @ Y) - Y).max() <= 1e-12 * np.abs(Y).max()
