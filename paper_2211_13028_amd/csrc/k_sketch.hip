@@ -306,46 +306,60 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
 }
 
 // ------------------------------------------------------------------ binary32 on matrix cores
-// The same pass for binary32 X with v_mfma_f32_16x16x4f32.  Wave w owns 128
-// columns; all waves step through 16 rows at a time.  Lane (li, kg) loads row
-// 4t + kg of each row quad t as two 16-byte groups (columns 4 li.. and 64 + 4 li..):
+// The same pass for binary32 X with v_mfma_f32_16x16x4f32.  A wave owns 128 columns of a
+// slab X[a]; CW waves side by side cover the column block (up to 512 columns) and the
+// workgroup takes 4 / CW slabs, so a tensor whose last mode is short keeps its four waves busy
+// (with all four side by side, 128^4 binary32, W alone: 432 us; 216 now).  All waves step
+// through the same rows, 16 at a time.  Lane (li, kg) loads row 4t + kg of each row quad t as
+// two 16-byte groups (columns 4 li.. and 64 + 4 li..):
 //  * W^T: A = PhiP[c][p] (one value per lane), B = the loaded groups, component c
 //    giving columns 4 n + c, so four MFMAs cover 64 columns per row quad;
 //  * Z: the 16 x 128 tile is staged row-major in the wave's LDS area, 64 columns at a
-//    time, and read back with lane (row li, 4 consecutive columns at 4 kg) as A; PhiQ is B, staged in LDS
-//    once per workgroup when s <= 8 (read from the caches, the 16 rows of a lane group
-//    touched 16 cache lines per load every step), else read from the caches.  Partial Z
-//    rows are added across the waves in LDS (fixed order).
-// Requires Q % 4 == 0; P, A arbitrary; s <= 16.
+//    time, and read back with lane (row li, 4 consecutive columns at 4 kg) as A; PhiQ is B, staged in
+//    LDS once per workgroup (read from the caches, the 16 rows of a lane group touched 16
+//    cache lines per load every step).  Partial Z rows are added across the CW waves in LDS
+//    (fixed order).
+// PhiP is staged in LDS 64 rows at a time, the next 64 in flight during the current ones.
+// VEC: Q % 4 == 0 and X 16-byte aligned, so a 16-byte group lies in one row and on its
+// boundary.  Otherwise the groups are loaded at whatever 4-byte boundary they start at, run into
+// the next row where the last one is cut by the row's end (masked when it is taken over), and
+// are loaded entry by entry in the last rows of the tensor.  (701 x 523 x 389 binary32 on the
+// vector-ALU pass instead: 297 us; 183 now,
+// 3.1 TB/s)
+// P, A arbitrary, Q >= 4; s <= 8.
 constexpr int kF32Stride = 68;  // floats per staged row: 64 + 4 padding (rows four banks apart)
-constexpr int kPhiQRows = 8;                     // PhiQ rows kept in LDS (s <= 8)
+constexpr int kPhiQRows = 8;
 constexpr int kPhiQStride = kZWColsMfma + 8;     // floats per row: 16-byte rows, rows 8 banks apart
+constexpr int kPhiPWin = 64;                     // rows of PhiP per staged window
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-template <bool QLDS>
+template <bool NZ, bool NW, bool VEC, int CW>
 __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3))) void sketch_zw_f32_mfma_kernel(
     const float* __restrict__ X, int64_t A, int64_t P, int64_t Q, const float* __restrict__ phiP, int sP,
-    const float* __restrict__ phiQ, int sQ, int64_t rows_per_block, int qblocks, int pblocks,
+    const float* __restrict__ phiQ, int sQ, int64_t rows_per_block, int64_t qcols, int qblocks, int pblocks,
     float* __restrict__ Zo, float* __restrict__ Wo) {
-  __shared__ float tile[kZWWaves][16 * kF32Stride];
-  __shared__ float zpart[2][kZWWaves][16 * 16];
-  __shared__ __align__(16) float sPhiQ[QLDS ? kPhiQRows * kPhiQStride : 4];  // PhiQ rows < 8 of the block's columns
-  __shared__ float sPhiP[QLDS ? 2 * 256 : 1];  // PhiP of a step, [parity][p - pb][c]
+  constexpr int kSlabs = kZWWaves / CW;
+  __shared__ __align__(16) float tile[NZ ? kZWWaves : 1][NZ ? 16 * kF32Stride : 4];
+  __shared__ float zpart[2][NZ && CW > 1 ? kZWWaves : 1][NZ && CW > 1 ? 16 * 16 : 1];
+  __shared__ __align__(16) float sPhiQ[NZ ? kPhiQRows * kPhiQStride : 4];  // PhiQ rows < 8 of the block's columns
+  __shared__ float sPhiP[2][NW ? kPhiPWin * 16 : 1];  // window of PhiP, [p][c]
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int64_t blk = blockIdx.x;
   const int qblk = static_cast<int>(blk % qblocks);
   const int64_t rest = blk / qblocks;
   const int pblk = static_cast<int>(rest % pblocks);
-  const int64_t a = rest / pblocks;
-  const int64_t q0 = static_cast<int64_t>(qblk) * kZWColsMfma;
-  const int64_t qend = (q0 + kZWColsMfma < Q) ? q0 + kZWColsMfma : Q;
-  const int64_t qw = q0 + 128 * wave;
-  const bool needZ = Zo != nullptr, needW = Wo != nullptr;
+  const int64_t a_raw = (rest / pblocks) * kSlabs + wave / CW;
+  const int64_t a = a_raw < A ? a_raw : A - 1;
+  const int64_t q0 = static_cast<int64_t>(qblk) * qcols;
+  const int64_t qend = (q0 + qcols < Q) ? q0 + qcols : Q;
+  const int64_t qw = q0 + 128 * (wave % CW);
+  const bool on = a_raw < A && qw < qend;  // waves past the last slab or column only keep the barriers
   const int li = lane % 16, kg = lane / 16;
   const int64_t pbeg = static_cast<int64_t>(pblk) * rows_per_block;
   const int64_t pend = (pbeg + rows_per_block < P) ? pbeg + rows_per_block : P;
   const float* xa = X + a * P * Q;
-  float* my = tile[wave];
+  float* my = tile[NZ ? wave : 0];
   const int64_t qc[2] = {qw + 4 * li, qw + 64 + 4 * li};
   const bool ok[2] = {qc[0] < qend, qc[1] < qend};
 
@@ -355,123 +369,162 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
 #pragma unroll
     for (int c = 0; c < 4; ++c) wacc[j][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // The next step's rows and PhiP values are loaded while the current step is multiplied.
-  // Loads carry no per-lane conditions: a row past pend reads row pend - 1 and a column
-  // group past qend the last group of the block (Q % 4 == 0); such values are zeroed when
-  // the step is taken over.  Without W the PhiP load reads an entry of PhiQ (in bounds:
-  // Z is then computed) and is unused.
-  const int64_t qcc[2] = {ok[0] ? qc[0] : qend - 4, ok[1] ? qc[1] : qend - 4};
+  // The next step's rows are loaded while the current step is multiplied.  Loads carry no
+  // per-lane conditions: a row past pend reads row pend - 1 and a column group past qend the
+  // last group of the row; such values are zeroed when the step is taken over.
+  const int64_t qlast = Q - 4;
+  const int64_t qcc[2] = {ok[0] ? qc[0] : qlast, ok[1] ? qc[1] : qlast};
   f32x4 rn[4][2];
-  float ppn[4];
-  auto load_step = [&](int64_t pb) {
+  const auto load_step = [&](int64_t pb) {
+    // groups cut by the end of the tensor's last row are loaded entry by entry
+    const bool tail = !VEC && a == A - 1 && pb + 16 >= P;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int64_t p = pb + 4 * t + kg;
       const int64_t pc = (p < pend) ? p : pend - 1;
-      if constexpr (!QLDS)
-        ppn[t] = *(needW ? phiP + static_cast<int64_t>(li) * P + pc : phiQ + static_cast<int64_t>(li) * Q + (qend - 4));
 #pragma unroll
-      for (int j = 0; j < 2; ++j) rn[t][j] = *reinterpret_cast<const f32x4*>(xa + pc * Q + qcc[j]);
+      for (int j = 0; j < 2; ++j) {
+        const float* src = xa + pc * Q + qcc[j];
+        if constexpr (VEC) {
+          rn[t][j] = *reinterpret_cast<const f32x4*>(src);
+        } else if (!tail) {
+          rn[t][j] = *reinterpret_cast<const f32x4u*>(src);
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) rn[t][j][c] = src[qcc[j] + c < Q ? c : 0];
+        }
+      }
     }
   };
-  load_step(pbeg);  // in flight while PhiQ is staged
-  // QLDS: the PhiP rows of a step are staged in LDS during the step before (thread: c = tid / 16,
-  // p = pb + tid % 16, zero past pend), loaded one step earlier still; the Z path's barrier
-  // of each step orders the stores before the next step's reads
-  const int pc_c = threadIdx.x / 16, pc_p = threadIdx.x % 16;
-  const auto phip_at = [&](int64_t pb) {
-    const int64_t p = pb + pc_p;
-    return (needW && p < pend) ? phiP[static_cast<int64_t>(pc_c) * P + p] : 0.f;
+  if (on) load_step(pbeg);  // in flight while the factors are staged
+  // thread: rows pl + 16 u of the window, column c of PhiP; zero past pend
+  const int pl = threadIdx.x % 16, pcol = threadIdx.x / 16;
+  float pv[kPhiPWin / 16];
+  const auto phip_load = [&](int64_t pw) {
+#pragma unroll
+    for (int u = 0; u < kPhiPWin / 16; ++u) {
+      const int64_t p = pw + pl + 16 * u;
+      pv[u] = p < pend ? phiP[static_cast<int64_t>(pcol) * P + p] : 0.f;
+    }
   };
-  float pvn = 0.f;
-  if constexpr (QLDS) {
-    sPhiP[pc_p * 16 + pc_c] = phip_at(pbeg);
-    pvn = phip_at(pbeg + 16);
+  const auto phip_store = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < kPhiPWin / 16; ++u) sPhiP[b][(pl + 16 * u) * 16 + pcol] = pv[u];
+  };
+  if constexpr (NW) {
+    phip_load(pbeg);
+    phip_store(0);
   }
-  // PhiQ (sQ <= 8) for the block's 512 columns in LDS, zero past sQ and past qend
-  if (QLDS && needZ) {
-    for (int g = threadIdx.x; g < kPhiQRows * (kZWColsMfma / 4); g += kZWThreads) {
-      const int c = g / (kZWColsMfma / 4), q4 = 4 * (g % (kZWColsMfma / 4));
-      f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (c < sQ && q0 + q4 < qend) v = *reinterpret_cast<const f32x4*>(phiQ + static_cast<int64_t>(c) * Q + q0 + q4);
-      *reinterpret_cast<f32x4*>(&sPhiQ[c * kPhiQStride + q4]) = v;
+  if constexpr (NZ && CW > 1) {
+    if (!on)  // a wave without columns adds zeros
+      for (int g = lane; g < 2 * 256; g += kWave) zpart[g / 256][wave][g % 256] = 0.f;
+  }
+  if constexpr (NZ) {
+    // PhiQ (sQ <= 8) for the block's columns, zero past sQ and past qend
+    constexpr int kV = VEC ? 4 : 1, kRow = 128 * CW / kV;
+    for (int g = threadIdx.x; g < kPhiQRows * kRow; g += kZWThreads) {
+      const int c = g / kRow, q = kV * (g % kRow);
+      const float* src = phiQ + static_cast<int64_t>(c) * Q + q0 + q;
+      const bool in = c < sQ && q0 + q < qend;
+      if constexpr (VEC)
+        *reinterpret_cast<f32x4*>(&sPhiQ[c * kPhiQStride + q]) =
+            in ? *reinterpret_cast<const f32x4*>(src) : f32x4{0.f, 0.f, 0.f, 0.f};
+      else
+        sPhiQ[c * kPhiQStride + q] = in ? *src : 0.f;
     }
   }
   __syncthreads();
-  int buf = 0;
+  int buf = 0, win = 0;
   for (int64_t pb = pbeg; pb < pend; pb += 16) {
-    f32x4 r[4][2];
-    float ppv[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const bool pin = pb + 4 * t + kg < pend;
-#pragma unroll
-      for (int j = 0; j < 2; ++j) r[t][j] = (ok[j] && pin) ? rn[t][j] : f32x4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (QLDS)
-        ppv[t] = pin ? sPhiP[buf * 256 + (4 * t + kg) * 16 + li] : 0.f;
-      else
-        ppv[t] = pin ? ppn[t] : 0.f;
-    }
-    if constexpr (QLDS) {
-      sPhiP[(buf ^ 1) * 256 + pc_p * 16 + pc_c] = pvn;  // the next step's rows
-      pvn = phip_at(pb + 32);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    load_step(pb + 16);  // past pend: clamped, never used
-    __builtin_amdgcn_sched_barrier(0);
-    if (needW) {
+    const int step = static_cast<int>((pb - pbeg) / 16) % (kPhiPWin / 16);  // of the window
+    const bool more = pb - 16 * step + kPhiPWin < pend;
+    if (NW && step == 0 && more) phip_load(pb + kPhiPWin);
+    if (on) {
+      f32x4 r[4][2];
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
-        const float pp = ppv[t];
+        const bool pin = pb + 4 * t + kg < pend;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 2; ++j) {
+          if constexpr (VEC) {
+            r[t][j] = (ok[j] && pin) ? rn[t][j] : f32x4{0.f, 0.f, 0.f, 0.f};
+          } else {
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            wacc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp, r[t][j][c], wacc[j][c], 0, 0, 0);
+            for (int c = 0; c < 4; ++c) r[t][j][c] = (pin && qc[j] + c < qend) ? rn[t][j][c] : 0.f;
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      load_step(pb + 16);  // past pend: clamped, never used
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (NW) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const float pp = sPhiP[win][(16 * step + 4 * t + kg) * 16 + li];  // zero past pend
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              wacc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp, r[t][j][c], wacc[j][c], 0, 0, 0);
+        }
+      }
+      if constexpr (NZ) {
+        f32x4 zacc = f32x4{0.f, 0.f, 0.f, 0.f};
+        // the 16 x 128 tile in two halves of 64 columns (a 16 x 64 stage per wave)
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb) {
+          if (kb % 4 == 0) {
+            __builtin_amdgcn_wave_barrier();  // the previous half's reads of the stage stay above
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              *reinterpret_cast<f32x4*>(my + (4 * t + kg) * kF32Stride + 4 * li) = r[t][kb / 4];
+            __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
+          }
+          const int qk = 128 * (wave % CW) + 16 * kb + 4 * kg;
+          f32x4 bq = *reinterpret_cast<const f32x4*>(&sPhiQ[(li & (kPhiQRows - 1)) * kPhiQStride + qk]);
+          if (li >= kPhiQRows) bq = f32x4{0.f, 0.f, 0.f, 0.f};
+          const f32x4 xr = *reinterpret_cast<const f32x4*>(my + li * kF32Stride + 16 * (kb % 4) + 4 * kg);
+#pragma unroll
+          for (int c = 0; c < 4; ++c) zacc = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], zacc, 0, 0, 0);
+        }
+        // D layout: row 4 kg + v, column c = li
+        if constexpr (CW > 1) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) zpart[buf][wave][(4 * kg + v) * 16 + li] = zacc[v];
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int64_t p = pb + 4 * kg + v;
+            if (li < sQ && p < pend) Zo[((static_cast<int64_t>(qblk) * A + a) * P + p) * sQ + li] = zacc[v];
+          }
+        }
       }
     }
-    if (needZ) {
-      f32x4 zacc = f32x4{0.f, 0.f, 0.f, 0.f};
-      // the 16 x 128 tile in two halves of 64 columns (a 16 x 64 stage per wave)
-#pragma unroll
-      for (int kb = 0; kb < 8; ++kb) {
-        if (kb % 4 == 0) {
-          __builtin_amdgcn_wave_barrier();  // the previous half's reads of the stage stay above
-#pragma unroll
-          for (int t = 0; t < 4; ++t)
-            *reinterpret_cast<f32x4*>(my + (4 * t + kg) * kF32Stride + 4 * li) = r[t][kb / 4];
-          __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
-        }
-        // PhiQ[li][qw + 16 kb + 4 kg .. + 3]: a small operand re-read from the caches each step
-        // (holding it in registers would cost the occupancy)
-        const int64_t qk = qw + 16 * kb + 4 * kg;
-        f32x4 bq;
-        if constexpr (QLDS) {
-          bq = *reinterpret_cast<const f32x4*>(&sPhiQ[(li & (kPhiQRows - 1)) * kPhiQStride + (qk - q0)]);
-          if (li >= kPhiQRows) bq = f32x4{0.f, 0.f, 0.f, 0.f};
-        } else {
-          bq = *reinterpret_cast<const f32x4*>(phiQ + static_cast<int64_t>(li) * Q + ((qk < qend) ? qk : qend - 4));
-          if (!(qk < qend)) bq = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        const f32x4 xr = *reinterpret_cast<const f32x4*>(my + li * kF32Stride + 16 * (kb % 4) + 4 * kg);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) zacc = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], zacc, 0, 0, 0);
-      }
-      float* zp = zpart[buf][wave];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) zp[(4 * kg + v) * 16 + li] = zacc[v];
+    // the next window is stored before the last step's barrier: its area was last read in the
+    // window before this one
+    const bool turn = NW && step == kPhiPWin / 16 - 1 && more;
+    if (turn) phip_store(win ^ 1);
+    if constexpr (NZ && CW > 1) {
       lds_barrier();  // the next rows' loads stay in flight
-      // wave w finishes rows 4 w .. 4 w + 3 of the step: lane -> (row, c)
-      const int row = 4 * wave + lane / 16, c = lane % 16;
+      // the waves of a slab finish 16 / CW rows of the step each: lane -> (row, c)
+      constexpr int kZRows = 16 / CW;
+      const int row = kZRows * (wave % CW) + lane / 8, c = lane % 8;
       const int64_t p = pb + row;
-      float z = zpart[buf][0][row * 16 + c];
+      if (lane / 8 < kZRows && c < sQ && p < pend && a_raw < A) {
+        const int first = wave - wave % CW;
+        float z = zpart[buf][first][row * 16 + c];
 #pragma unroll
-      for (int w = 1; w < kZWWaves; ++w) z += zpart[buf][w][row * 16 + c];
-      if (c < sQ && p < pend) Zo[((static_cast<int64_t>(qblk) * A + a) * P + p) * sQ + c] = z;
+        for (int w = 1; w < CW; ++w) z += zpart[buf][first + w][row * 16 + c];
+        Zo[((static_cast<int64_t>(qblk) * A + a) * P + p) * sQ + c] = z;
+      }
       buf ^= 1;
     }
+    if (turn) {
+      if constexpr (!(NZ && CW > 1)) lds_barrier();
+      win ^= 1;
+    }
   }
-  if (!needW) return;
+  if (!NW || !on) return;
   float* wout = Wo + (static_cast<int64_t>(pblk) * A + a) * sP * Q;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
@@ -479,9 +532,15 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int cp = 4 * kg + v;
-      if (cp < sP)
-        *reinterpret_cast<f32x4*>(wout + static_cast<int64_t>(cp) * Q + qc[j]) =
-            f32x4{wacc[j][0][v], wacc[j][1][v], wacc[j][2][v], wacc[j][3][v]};
+      if (cp >= sP) continue;
+      float* dst = wout + static_cast<int64_t>(cp) * Q + qc[j];
+      if constexpr (VEC) {
+        *reinterpret_cast<f32x4*>(dst) = f32x4{wacc[j][0][v], wacc[j][1][v], wacc[j][2][v], wacc[j][3][v]};
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (qc[j] + c < qend) dst[c] = wacc[j][c][v];
+      }
     }
   }
 }
@@ -533,30 +592,41 @@ ZWPlan sketch_zw_plan(rt_dtype xdt, int64_t A, int64_t P, int64_t Q, int64_t sP,
                       bool needW) {
   ZWPlan p;
   const bool mf16 = (xdt == RT_BF16 || xdt == RT_F8E4M3) && (P % 8 == 0) && (Q % 8 == 0) && P >= 32;
-  const bool mf32 = (xdt == RT_F32) && (Q % 4 == 0) && P >= 16;
+  // (below 16 entries a row or 16 rows, most of a step's matrix-core tile would be padding)
+  const bool mf32 = (xdt == RT_F32) && Q >= 16 && P >= 16;
   p.mfma = mf16 || mf32;
   const int nq = pick_nq(xdt, Q);
   p.qblocks = p.mfma ? ceil_div(Q, kZWColsMfma) : ceil_div(Q, 64 * nq);
+  p.qcols = p.mfma ? kZWColsMfma : 64 * nq;
+  p.waves_per_slab = kZWWaves;
+  if (mf32) {
+    // binary32: the column blocks share the 128-column units evenly, and a block of one or two
+    // units leaves waves for further slabs
+    const int64_t units = ceil_div(ceil_div(Q, 128), p.qblocks);
+    p.qcols = 128 * units;
+    p.waves_per_slab = units > 2 ? 4 : static_cast<int>(units);
+  }
   if (p.mfma) {
     // Row split for the matrix-core pass: 768 workgroups are resident at once
     // (3 per CU).  Cost in units of "one row per resident workgroup":
     //   rows_per_block * max(1, workgroups / 768)  +  partial-W traffic of pb row ranges,
-    // with the W partials (written and re-read, binary32) converted at the
-    // 1 KiB of X that one row of 512 bfloat16 columns is.  A grid of at least one full
-    // round streams at about the same rate whether its last round is full or not (the
+    // with the W partials (written and re-read, binary32) converted at the bytes of X that one
+    // row of the resident workgroups is (512 columns each, over their slabs).  A grid of at
+    // least one full round streams at about the same rate whether its last round is full or not (the
     // pass is bound by HBM), so rounds count fractionally; a grid below one round is
     // bound by its longest workgroup.  (Counting the last round as full chose three row
     // ranges for 1024 x 1024 x 512 binary32, 20 us per decomposition slower than one.)
     const int64_t resident = 768;
     const int64_t step = mf32 ? 16 : 32;  // rows per step of the kernel
     const double row_bytes = static_cast<double>(resident) * kZWColsMfma * (mf32 ? 4 : 2);
+    const int64_t slab_groups = ceil_div(A, kZWWaves / p.waves_per_slab);
     double best = 0.0;
     int64_t best_rows = 0;
     for (int64_t pb = 1; pb <= 64; ++pb) {
       const int64_t rows = ceil_div(ceil_div(P, pb), step) * step;
       const int64_t pbs = ceil_div(P, rows);
       if (pbs != pb || (pb > 1 && rows < 128)) continue;
-      const int64_t wgs = A * p.qblocks * pb;
+      const int64_t wgs = slab_groups * p.qblocks * pb;
       const double rounds = wgs > resident ? static_cast<double>(wgs) / resident : 1.0;
       const double t = rounds * rows +
                        (pb > 1 && needW ? 2.0 * pb * A * sP * Q * 4.0 / row_bytes : 0.0);
@@ -605,16 +675,31 @@ hipError_t launch_sketch_zw(const void* X, rt_dtype xdt, int64_t A, int64_t P, i
   if (plan.mfma) {
     const int64_t blocks = A * plan.pblocks * plan.qblocks;
     if (xdt == RT_F32) {
-      if (sQ <= kPhiQRows && zdst != nullptr)
-        sketch_zw_f32_mfma_kernel<true><<<static_cast<unsigned>(blocks), kZWThreads, 0, st>>>(
-            static_cast<const float*>(X), A, P, Q, static_cast<const float*>(phiP16), isP,
-            static_cast<const float*>(phiQ16), isQ, plan.rows_per_block, static_cast<int>(plan.qblocks),
-            static_cast<int>(plan.pblocks), static_cast<float*>(zdst), static_cast<float*>(wdst));
-      else
-        sketch_zw_f32_mfma_kernel<false><<<static_cast<unsigned>(blocks), kZWThreads, 0, st>>>(
-            static_cast<const float*>(X), A, P, Q, static_cast<const float*>(phiP16), isP,
-            static_cast<const float*>(phiQ16), isQ, plan.rows_per_block, static_cast<int>(plan.qblocks),
-            static_cast<int>(plan.pblocks), static_cast<float*>(zdst), static_cast<float*>(wdst));
+      const bool vec = Q % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+      const int64_t groups = ceil_div(A, kZWWaves / plan.waves_per_slab) * plan.pblocks * plan.qblocks;
+      const unsigned g = static_cast<unsigned>(groups);
+#define RT_ZWF(NZV, NWV, VV, CWV)                                                                                    \
+  sketch_zw_f32_mfma_kernel<NZV, NWV, VV, CWV><<<g, kZWThreads, 0, st>>>(                                            \
+      static_cast<const float*>(X), A, P, Q, static_cast<const float*>(phiP16), isP, static_cast<const float*>(phiQ16), \
+      isQ, plan.rows_per_block, plan.qcols, static_cast<int>(plan.qblocks), static_cast<int>(plan.pblocks),           \
+      static_cast<float*>(zdst), static_cast<float*>(wdst))
+#define RT_ZWF_W(NZV, NWV, VV)                            \
+  do {                                                    \
+    if (plan.waves_per_slab == 1) RT_ZWF(NZV, NWV, VV, 1); \
+    else if (plan.waves_per_slab == 2) RT_ZWF(NZV, NWV, VV, 2); \
+    else RT_ZWF(NZV, NWV, VV, 4);                         \
+  } while (0)
+#define RT_ZWF_V(NZV, NWV)                 \
+  do {                                     \
+    if (vec) RT_ZWF_W(NZV, NWV, true);     \
+    else RT_ZWF_W(NZV, NWV, false);        \
+  } while (0)
+      if (zdst && wdst) RT_ZWF_V(true, true);
+      else if (zdst) RT_ZWF_V(true, false);
+      else RT_ZWF_V(false, true);
+#undef RT_ZWF_V
+#undef RT_ZWF_W
+#undef RT_ZWF
     }
     else if (xdt == RT_F8E4M3)
       sketch_zw_bf16_mfma_kernel<f8_t><<<static_cast<unsigned>(blocks), kZWThreads, 0, st>>>(

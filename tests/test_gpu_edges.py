@@ -87,3 +87,41 @@ def test_qr_breakdown_in_any_panel(n, dup):
     Q = rt.rtucker_qr(_dev(Y)).cpu().numpy()
     assert np.abs(Q.T @ Q - np.eye(n)).max() <= 1e-13
     assert np.abs(Q @ (Q.T @ Y) - Y).max() <= 1e-12 * np.abs(Y).max()
+
+
+# ------------------------------------------------------------------ binary32 sketch pass
+# 128-column waves (1, 2 or 4 a slab, several column blocks), 16-row steps, 64-row windows, row
+# splits, last slab of a workgroup; rows that start at any 4-byte boundary and are cut by the end
+# of the tensor.  Each entry is a binary32 sum of at most 1100 products: 1100 * 2^-24 < 7e-5 of the
+# sum of their magnitudes.
+@pytest.mark.parametrize("dims,sp,sl", [
+    ((5, 16, 16), 3, 2), ((5, 17, 19), 4, 8), ((4, 63, 127), 8, 5), ((7, 65, 128), 3, 3), ((3, 64, 129), 2, 7),
+    ((2, 3, 130, 131), 5, 4), ((6, 80, 255), 4, 4), ((3, 81, 257), 7, 6), ((2, 100, 389), 7, 7),
+    ((1, 700, 513), 3, 8), ((2, 40, 640), 8, 1), ((1, 1100, 66), 5, 5), ((1, 33, 1027), 6, 2),
+])
+@pytest.mark.parametrize("want", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_sketch_pass_f32_tiles(dims, sp, sl, want, skew):
+    rng = np.random.default_rng(sum(dims) + sp)
+    X = rng.standard_normal(dims).astype(np.float32).astype(np.float64)
+    fp = rng.standard_normal((sp, dims[-2])).astype(np.float32).astype(np.float64)
+    fl = rng.standard_normal((sl, dims[-1])).astype(np.float32).astype(np.float64)
+    Z, W = rt.rtucker_sketch_pass(_dev(X, torch.float32, skew), _dev(fp), _dev(fl), want=want)
+    for got, on, ref, mag in ((Z, want[0], X @ fl.T, np.abs(X) @ np.abs(fl).T),
+                              (W, want[1], fp @ X, np.abs(fp) @ np.abs(X))):
+        assert (got is not None) == on
+        if on:
+            assert np.all(np.abs(got.double().cpu().numpy() - ref) <= 7e-5 * mag)
+
+
+def test_sketch_pass_f32_nonfinite_stays_in_its_row_and_column():
+    dims = (3, 40, 77)
+    X = np.ones(dims)
+    X[1, 17, 76] = np.inf
+    Z, W = rt.rtucker_sketch_pass(_dev(X, torch.float32), _dev(np.ones((2, 40))), _dev(np.ones((2, 77))))
+    Z, W = Z.cpu().numpy(), W.cpu().numpy()
+    want_z = np.full((3, 40, 2), 77.0)
+    want_z[1, 17] = np.inf
+    want_w = np.full((3, 2, 77), 40.0)
+    want_w[1, :, 76] = np.inf
+    assert np.array_equal(Z, want_z) and np.array_equal(W, want_w)
