@@ -6,11 +6,15 @@
 //
 //  * ttm_generic: VALU kernel for every dtype and shape (one output column per
 //    thread, m split into register tiles, M chunks broadcast from LDS).
-//  * ttm_mfma:   matrix-core kernel for binary32 / bfloat16 X and B % 4 == 0
-//    (binary32) or B % 8 == 0 (bfloat16), m <= 64.  Each wave owns a 64 x 128
+//  * ttm_split:  matrix-core kernel for binary32 X (B >= 64, m <= 64): three
+//    bfloat16 terms a value, X streamed once, M split and staged in LDS.
+//  * ttm_mfma:   matrix-core kernels for bfloat16 X (B % 8 == 0, m <= 64) and for the
+//    small binary32 contractions of one launch.  Each wave owns a 64 x 128
 //    output tile (m padded to a multiple of 16) and streams X rows once; the
 //    prepared M operand is read from L2.  bfloat16 operands are re-packed in
 //    registers so that each lane holds 8 consecutive k of one column.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace rt {
@@ -197,14 +201,11 @@ constexpr int kUnitCols = 128;
 // Work unit = (a, 128-column chunk, k-split part).  Y (or a split-K partial) is
 // written for rows i < m only.
 // One work unit (a wave) of the binary32 contraction; unit < A * chunks * ksplit.
-// TAIL > 0 (with VM): rows 16 MT .. 16 MT + TAIL - 1 of M are not a whole 16-row matrix-core
-// tile, and are multiplied on the vector ALU from the X values the lane already holds
-// (m = 49 = 3 x 16 + 1 would otherwise pad a fourth tile: 31 % more matrix-core work).
-template <int MT, bool VM, int TAIL = 0, int DEPTH = 3>
+// (binary32 products: the small grouped contractions of the sketch's dimension tree)
+template <int MT, bool VM>
 __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_t A, int64_t K, int64_t B,
                                              const float* __restrict__ Mop, int64_t m, int64_t chunks, int ksplit,
                                              int64_t kper, float* __restrict__ Y, int64_t unit) {
-  static_assert(TAIL == 0 || VM, "vector-ALU tail rows need K % 4 == 0");
   const int lane = threadIdx.x % kWave;
   const int ks = static_cast<int>(unit % ksplit);
   const int64_t ac = unit / ksplit;
@@ -235,13 +236,9 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
   const int64_t c0off = colok0 ? b0 + 4 * j : b0, c1off = colok1 ? b0 + 64 + 4 * j : b0;
   const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
   // DEPTH blocks in flight: set P holds the block DEPTH steps ahead of the one multiplied
-  static_assert(DEPTH >= 1 && DEPTH <= 4, "one to four blocks ahead (four measured slower than three: registers)");
+  constexpr int DEPTH = 3;  // (four measured slower: registers)
   f32x4 n0[DEPTH][4], n1[DEPTH][4];
   float nw[DEPTH][MT][4];
-  f32x4 ntw[DEPTH][TAIL > 0 ? TAIL : 1];
-  f32x4 tacc[TAIL > 0 ? TAIL : 1][2];
-#pragma unroll
-  for (int r = 0; r < TAIL; ++r) tacc[r][0] = tacc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   const auto load_block = [&](int64_t k0, auto Pc) {
     constexpr int P = decltype(Pc)::value;
     const int64_t kl = k0 + 4 * q;
@@ -261,8 +258,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 #pragma unroll
         for (int s = 0; s < 4; ++s) nw[P][mt][s] = v[s];
       }
-#pragma unroll
-      for (int r = 0; r < TAIL; ++r) ntw[P][r] = *reinterpret_cast<const f32x4*>(Mop + (MT * 16 + r) * K + km);
     } else {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
@@ -274,7 +269,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
     constexpr int P = decltype(Pc)::value;
     f32x4 y0[4], y1[4];
     float w[4][MT];
-    f32x4 tw[TAIL > 0 ? TAIL : 1];
     const int64_t kl = k0 + 4 * q;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -284,8 +278,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) w[s][mt] = kin ? nw[P][mt][s] : 0.f;
     }
-#pragma unroll
-    for (int r = 0; r < TAIL; ++r) tw[r] = ntw[P][r];
     // the block DEPTH steps ahead goes out before this block's products (the scheduler may
     // move neither the operand take-over below it nor it into the products)
     __builtin_amdgcn_sched_barrier(0);
@@ -302,17 +294,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
         }
       }
     }
-    // tail rows: the lane's four k of the block against its eight columns (y past kend
-    // are zero, and the clamped loads of the tail rows are finite)
-#pragma unroll
-    for (int r = 0; r < TAIL; ++r)
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          tacc[r][0][c] = fmaf(tw[r][s], y0[s][c], tacc[r][0][c]);
-          tacc[r][1][c] = fmaf(tw[r][s], y1[s][c], tacc[r][1][c]);
-        }
   };
   constexpr auto sets = std::make_integer_sequence<int, DEPTH>{};
   if (kbeg < kend) for_each_index([&](auto Pc) { load_block(kbeg + 16 * decltype(Pc)::value, Pc); }, sets);
@@ -324,23 +305,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
         },
         sets);
   float* ya = Y + (static_cast<int64_t>(ks) * A + a) * m * B;
-  // tail rows: the four lane groups q hold the partial sums of k = 4 q + s of every block;
-  // add them in a fixed order (lane j collects groups 0..3) and store from group 0
-#pragma unroll
-  for (int r = 0; r < TAIL; ++r) {
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      f32x4 v = tacc[r][g];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float p1 = __shfl(v[c], j + 16), p2 = __shfl(v[c], j + 32), p3 = __shfl(v[c], j + 48);
-        v[c] = ((v[c] + p1) + p2) + p3;
-      }
-      const int64_t i = MT * 16 + r;
-      const int64_t c0 = b0 + 64 * g + 4 * j;
-      if (q == 0 && i < m && c0 < B) *reinterpret_cast<f32x4*>(ya + i * B + c0) = v;
-    }
-  }
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -359,218 +323,223 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
   }
 }
 
-template <int MT, bool VM, int TAIL = 0>
-__global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_kernel(const float* __restrict__ X, int64_t A, int64_t K,
-                                                                    int64_t B, const float* __restrict__ Mop,
-                                                                    int64_t m, int64_t chunks, int ksplit,
-                                                                    int64_t kper, float* __restrict__ Y) {
-  const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
-  if (unit >= A * chunks * ksplit) return;
-  ttm_f32_unit<MT, VM, TAIL>(X, A, K, B, Mop, m, chunks, ksplit, kper, Y, unit);
+// ------------------------------------------------------------------ binary32 as three bfloat16 terms
+// The binary32 contraction on the bfloat16 matrix cores, at binary32 accuracy.  Every value is
+// the exact sum of three bfloat16 terms, x = h + m + l (each the rounding to nearest of what is
+// left, 8 bits at a time), and of the nine products of x and M the six of relative size 2^-16 or
+// more are kept (hh, hm, mh, mm, hl, lh, smallest first); the dropped ones are below 2^-24 of
+// |x M|, half a unit in the last place of binary32, with random signs.  A 16x16x32 bfloat16
+// product takes a quarter of the time a k of 16x16x4 binary32 ones do, so six of them take
+// 0.375 of it, and the sum of 32 k is rounded six times instead of eight (normal X of 1024 k: error
+// 1.23e-7 of the result's norm against 1.63e-7; over K = 100 .. 4096 between 0.5 and 0.97 of it).
+//
+// A wave owns 64 columns of one slab (lane j: four consecutive columns, at any 4-byte
+// boundary) and takes k in blocks of 32: lane group q loads the rows k0 + 8 q .. + 7, converts
+// them pairwise (the packed pair is what the B operand holds: two k of one column), and has the
+// next block in flight during the block's products.  The four waves of a workgroup share the k
+// range; M is split while it is staged in LDS, 64 k at a time, double-buffered.
+//
+// Bound: HBM (1024 x 1024 x 512 with m = 49: 0.165 ms of matrix-core time at peak against 0.36 ms
+// of reading at 6.3 TB/s); the binary32 products before were bound by the matrix cores.
+// First contraction of the 1024 x 1024 x 512 decomposition: 518 -> 430 us (5.2 TB/s); of 512 x 768
+// x 640 with m = 36: 340 -> 222; of 128^4 with m = 27: 271 -> 245.
+//
+// X is scaled by 2^32 before it is split, so that all terms of the smallest subnormal are normal
+// bfloat16 values, and the results are scaled back.  What the terms cannot hold goes to binary32
+// products, per wave and after the loop: results that are not finite (an infinity splits into
+// NaN; so does what overflows in the scaling or the sums), and an M with nonzero entries outside
+// [2^-100, 2^20].
+constexpr float kSplitUp = 0x1p32f, kSplitDown = 0x1p-32f;
+constexpr int kSplitCols = 64;
+constexpr int kSplitWin = 64;                // k of M per staged window
+constexpr int kSplitStride = kSplitWin + 8;  // bfloat16 per staged row: 16-byte groups, rows 36 banks apart
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// the three terms of two values, packed in pairs
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  const auto round2 = [](float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+  };
+  const auto low = [](uint32_t v) { return __uint_as_float(v << 16); };
+  const auto high = [](uint32_t v) { return __uint_as_float(v & 0xffff0000u); };
+  h = round2(x0, x1);
+  const float r0 = x0 - low(h), r1 = x1 - high(h);  // exact
+  m = round2(r0, r1);
+  l = round2(r0 - low(m), r1 - high(m));
 }
 
-// The same for at most three 16-row tiles, held to 256 registers so that two waves share
-// each SIMD: a wave has one block of X in flight besides the one it multiplies, so with one
-// wave per SIMD (the compiler's choice otherwise: about 300 vector and matrix registers) the
-// loads in flight per CU cover too little of the memory latency.  (With four tiles the
-// limit would spill.)
-template <int MT, bool VM, int TAIL = 0>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_f32_occ2_kernel(
+template <int MT, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ttm_split_f32_kernel(
     const float* __restrict__ X, int64_t A, int64_t K, int64_t B, const float* __restrict__ Mop, int64_t m,
-    int64_t chunks, int ksplit, int64_t kper, float* __restrict__ Y) {
-  static_assert(MT <= 3, "four tiles do not fit two waves per SIMD");
-  const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
-  if (unit >= A * chunks * ksplit) return;
-  ttm_f32_unit<MT, VM, TAIL, 1>(X, A, K, B, Mop, m, chunks, ksplit, kper, Y, unit);
-}
-
-// The binary32 contraction with M staged in LDS, for plans without a split over k and
-// K % 4 == 0 (rows 16 MT .. 16 MT + TAIL - 1 on the vector ALU as above).  The four waves
-// of a workgroup take four consecutive units, which share the k loop, so M is staged once
-// per workgroup in windows of kMWin k, double-buffered: every thread stages a share of the
-// next window during each round of DEPTH 16-k blocks of the current one, and a barrier
-// closes each window.  A lane's A operand (16 rows, four consecutive k) is then one 16-byte
-// LDS read per tile; read from the caches instead, the 16 rows of a lane group touch 16
-// cache lines per load, as many line accesses as the X loads themselves (the kernel ran
-// 23 % faster in a timing build without the M loads).  Waves past the last unit run the
-// loop on unit 0's data and store nothing.
-constexpr int kMWin = 192;              // k per window: whole rounds of DEPTH 16-k blocks
-// two waves per SIMD with two blocks of X in flight each (measured 10 % faster than one wave
-// with three; three tiles plus two tail rows take one block, to stay within 256 registers)
-constexpr int mlds_depth(int mt, int tail) { return (mt == 3 && tail == 2) ? 1 : 2; }
-constexpr int kMWinStride = kMWin + 4;  // floats per staged row: 16-byte rows, rows four banks apart
-
-template <int MT, int TAIL, int DEPTH, bool OCC2>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(OCC2 ? 2 : 1))) void
-ttm_mfma_f32_mlds_kernel(const float* __restrict__ X, int64_t A, int64_t K, int64_t B, const float* __restrict__ Mop,
-                         int64_t m, int64_t chunks, float* __restrict__ Y) {
-  constexpr int kRounds = kMWin / (16 * DEPTH);  // rounds of DEPTH blocks per window
-  static_assert(kRounds * 16 * DEPTH == kMWin, "a window is whole rounds of DEPTH blocks");
-  constexpr int kRows = 16 * MT + TAIL;
-  constexpr int kF4 = kMWin / 4;        // 16-byte groups per staged row
-  constexpr int kGroups = kRows * kF4;  // per window
-  constexpr int kPer = (kGroups + kRounds * kMfmaThreads - 1) / (kRounds * kMfmaThreads);  // per thread and round
-  __shared__ __align__(16) float sMw[2][kRows * kMWinStride];
-  const int tid = threadIdx.x;
-  const int lane = tid % kWave;
-  const int64_t unit_raw = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + tid / kWave;
+    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y) {
+  __shared__ __align__(16) uint16_t sM[2][3][16 * MT * kSplitStride];
+  __shared__ int odd;  // M has entries that its terms cannot hold
+  const int tid = threadIdx.x, lane = tid % kWave;
+  const int j = lane % 16, q = lane / 16;
+  const int64_t ks = blockIdx.x / groups;
+  const int64_t unit_raw = (blockIdx.x - ks * groups) * (NT / kWave) + tid / kWave;
   const bool active = unit_raw < A * chunks;
   const int64_t unit = active ? unit_raw : 0;
   const int64_t a = unit / chunks;
-  const int64_t b0 = (unit - a * chunks) * kUnitCols;
-  const int j = lane % 16, q = lane / 16;
+  const int64_t col_raw = (unit - a * chunks) * kSplitCols + 4 * j;
+  // a lane whose columns run past B takes the last four: its results repeat its neighbour's
+  const int64_t col = col_raw + 4 <= B ? col_raw : B - 4;
+  const int64_t kbeg = ks * kper;
+  const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
+  const float* xa = X + a * K * B + col;
 
-  f32x4 acc[MT][2][4];
+  f32x4 acc[MT][4];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int g = 0; g < 2; ++g)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) acc[mt][g][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 tacc[TAIL > 0 ? TAIL : 1][2];
-#pragma unroll
-  for (int r = 0; r < TAIL; ++r) tacc[r][0] = tacc[r][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < 4; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const float* xa = X + a * K * B;
-  const bool colok0 = (b0 + 4 * j) < B;
-  const bool colok1 = (b0 + 64 + 4 * j) < B;
-  const int64_t c0off = colok0 ? b0 + 4 * j : b0, c1off = colok1 ? b0 + 64 + 4 * j : b0;
-  const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 n0[DEPTH][4], n1[DEPTH][4];
-  const auto load_block = [&](int64_t k0, auto Pc) {
-    constexpr int P = decltype(Pc)::value;
-    const int64_t kl = k0 + 4 * q;
+  // The lane's rows of a block, at xp (advanced by 32 rows a block: forming each row's address
+  // from its number cost more issue slots than the conversion).  In the range's last block rows
+  // past kend read row kend - 1 again; M is zero there.
+  f32x4 rn[8];
+  const float* xp = xa + (kbeg + 8 * q) * B;
+  const auto load = [&](int64_t k0) {
+    if (k0 + 32 <= kend) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int64_t kc = (kl + s < K) ? kl + s : K - 1;
-      n0[P][s] = *reinterpret_cast<const f32x4*>(xa + kc * B + c0off);
-      n1[P][s] = *reinterpret_cast<const f32x4*>(xa + kc * B + c1off);
+      for (int t = 0; t < 8; ++t) rn[t] = *reinterpret_cast<const f32x4u*>(xp + t * B);
+    } else if (k0 < kend) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int64_t k = k0 + 8 * q + t;
+        rn[t] = *reinterpret_cast<const f32x4u*>(xa + (k < kend ? k : kend - 1) * B);
+      }
     }
+    xp += 32 * B;
   };
-  // staging: group g of a window is row g / kF4, k = kw + 4 (g % kF4); zero past K
+  // staging: group g = NT i + tid of a window is row g / 16, k = kw + 4 (g % 16) ..
+  constexpr int kGroups = 16 * MT * (kSplitWin / 4), kPer = (kGroups + NT - 1) / NT;
   f32x4 sv[kPer];
-  const auto stage_load = [&](int64_t kw, int round) {
+  const auto group_of = [&](int g, int64_t kw) {
+    const int64_t k = kw + 4 * (g % 16);
+    const float* src = Mop + static_cast<int64_t>(g / 16) * K + k;
+    f32x4 v;
+    if (k + 4 <= kend) {
+      v = *reinterpret_cast<const f32x4u*>(src);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[c] = k + c < kend ? src[c] : 0.f;
+    }
+    return v;
+  };
+  const auto stage_load = [&](int64_t kw) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int g = (round * kPer + i) * kMfmaThreads + tid;
-      const int row = g / kF4, c4 = g - (g / kF4) * kF4;
-      const int64_t k = kw + 4 * c4;
-      sv[i] = (g < kGroups && k < K) ? *reinterpret_cast<const f32x4*>(Mop + row * K + k) : zero4;
+      const int g = i * NT + tid;
+      if (g < kGroups) sv[i] = group_of(g, kw);
     }
   };
-  const auto stage_store = [&](int b, int round) {
+  bool outside = false;
+  const auto stage_store = [&](int b) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int g = (round * kPer + i) * kMfmaThreads + tid;
-      const int row = g / kF4, c4 = g - (g / kF4) * kF4;
-      if (g < kGroups) *reinterpret_cast<f32x4*>(&sMw[b][row * kMWinStride + 4 * c4]) = sv[i];
+      const int g = i * NT + tid;
+      if (g >= kGroups) break;
+      uint32_t t[3][2];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t u = __float_as_uint(sv[i][c]) & 0x7fffffffu;
+        outside = outside || (u != 0 && (u < 0x0d800000u || u > 0x49800000u));
+      }
+      split3(sv[i][0], sv[i][1], t[0][0], t[1][0], t[2][0]);
+      split3(sv[i][2], sv[i][3], t[0][1], t[1][1], t[2][1]);
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        *reinterpret_cast<uint2*>(&sM[b][p][(g / 16) * kSplitStride + 4 * (g % 16)]) = make_uint2(t[p][0], t[p][1]);
     }
   };
-  int buf = 0;
-  int64_t kw = 0;
-  const auto block = [&](int64_t k0, auto Pc) {
-    constexpr int P = decltype(Pc)::value;
-    f32x4 y0[4], y1[4];
-    float w[4][MT];
-    f32x4 tw[TAIL > 0 ? TAIL : 1];
-    const int64_t kl = k0 + 4 * q;
-    const float* mw = &sMw[buf][kl - kw];
+  load(kbeg);
+  if (tid == 0) odd = 0;
+  stage_load(kbeg);
+  stage_store(0);
+  __syncthreads();
+  int buf = 0, half = 0;
+  for (int64_t k0 = kbeg; k0 < kend; k0 += 32) {
+    // window: the blocks k0 - 32 half and the one after it
+    const bool more = k0 + (kSplitWin - 32 * half) < kend;
+    if (half == 0 && more) stage_load(k0 + kSplitWin);
+    u32x4 xt[3][4];  // terms of the lane's four columns, 8 k each
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t h, md, l;
+        split3(rn[2 * w][c] * kSplitUp, rn[2 * w + 1][c] * kSplitUp, h, md, l);
+        xt[0][c][w] = h;
+        xt[1][c][w] = md;
+        xt[2][c][w] = l;
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    load(k0 + 32);
+    __builtin_amdgcn_sched_barrier(0);
+    const uint16_t* mw = &sM[buf][0][j * kSplitStride + 32 * half + 8 * q];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(mw + (mt * 16 + j) * kMWinStride);
+      bf16x8 mv[3];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) w[s][mt] = v[s];  // zero past K (staged so)
+      for (int p = 0; p < 3; ++p)
+        mv[p] = *reinterpret_cast<const bf16x8*>(mw + (p * 16 * MT + 16 * mt) * kSplitStride);
+      constexpr int kTm[6] = {2, 0, 1, 1, 0, 0}, kTx[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int e = 0; e < 6; ++e)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              mv[kTm[e]], __builtin_bit_cast(bf16x8, xt[kTx[e]][c]), acc[mt][c], 0, 0, 0);
     }
-#pragma unroll
-    for (int r = 0; r < TAIL; ++r) tw[r] = *reinterpret_cast<const f32x4*>(mw + (MT * 16 + r) * kMWinStride);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const bool kin = kl + s < K;
-      y0[s] = kin ? n0[P][s] : zero4;
-      y1[s] = kin ? n1[P][s] : zero4;
-    }
-    // the block DEPTH steps ahead goes out before this block's products
-    __builtin_amdgcn_sched_barrier(0);
-    load_block(k0 + 16 * DEPTH, Pc);  // past K: rows K - 1 again, never used
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          acc[mt][0][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][mt], y0[s][t], acc[mt][0][t], 0, 0, 0);
-          acc[mt][1][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][mt], y1[s][t], acc[mt][1][t], 0, 0, 0);
-        }
-#pragma unroll
-    for (int r = 0; r < TAIL; ++r)
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          tacc[r][0][c] = fmaf(tw[r][s], y0[s][c], tacc[r][0][c]);
-          tacc[r][1][c] = fmaf(tw[r][s], y1[s][c], tacc[r][1][c]);
-        }
-  };
-  constexpr auto sets = std::make_integer_sequence<int, DEPTH>{};
-  for_each_index([&](auto Pc) { load_block(16 * decltype(Pc)::value, Pc); }, sets);
-  // window 0 before the loop
-#pragma unroll
-  for (int round = 0; round < kRounds; ++round) {
-    stage_load(0, round);
-    stage_store(0, round);
-  }
-  __syncthreads();
-  for (int64_t k0 = 0; k0 < K; k0 += 16 * DEPTH) {
-    const int round = static_cast<int>((k0 / (16 * DEPTH)) % kRounds);
-    const bool more = kw + kMWin < K;
-    if (more) stage_load(kw + kMWin, round);
-    for_each_index(
-        [&](auto Pc) {
-          const int64_t kb = k0 + 16 * decltype(Pc)::value;
-          if (kb < K) block(kb, Pc);
-        },
-        sets);
-    if (more) stage_store(buf ^ 1, round);
-    if (round == kRounds - 1 || k0 + 16 * DEPTH >= K) {
-      __syncthreads();  // the window is read by every wave and the next one staged
+    half ^= 1;
+    if (half == 0 || k0 + 32 >= kend) {
+      if (more) stage_store(buf ^ 1);
+      if (outside) odd = 1;
+      lds_barrier();  // the window is read by every wave and the next one staged; loads of X stay in flight
       buf ^= 1;
-      kw += kMWin;
     }
   }
   if (!active) return;
-  float* ya = Y + a * m * B;
+  // results outside the range of the terms (see above): once more with binary32 products
+  bool again = odd != 0;
 #pragma unroll
-  for (int r = 0; r < TAIL; ++r) {
+  for (int c = 0; c < 4; ++c) {
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      f32x4 v = tacc[r][g];
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float p1 = __shfl(v[c], j + 16), p2 = __shfl(v[c], j + 32), p3 = __shfl(v[c], j + 48);
-        v[c] = ((v[c] + p1) + p2) + p3;
+      for (int v = 0; v < 4; ++v) {
+        again = again || !isfinite(acc[mt][c][v]);
+        acc[mt][c][v] *= kSplitDown;
       }
-      const int64_t i = MT * 16 + r;
-      const int64_t c0 = b0 + 64 * g + 4 * j;
-      if (q == 0 && i < m && c0 < B) *reinterpret_cast<f32x4*>(ya + i * B + c0) = v;
+  }
+  if (__any(again)) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t k0 = kbeg; k0 < kend; k0 += 4) {
+      const int64_t k = k0 + q;
+      const f32x4 xv = k < kend ? static_cast<f32x4>(*reinterpret_cast<const f32x4u*>(xa + k * B)) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        const float w = k < kend ? Mop[(16 * mt + j) * K + k] : 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xv[c], acc[mt][c], 0, 0, 0);
+      }
     }
   }
+  if (col_raw >= B) return;
+  float* ya = Y + (ks * A + a) * m * B + col;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int64_t i = mt * 16 + 4 * q + v;
-      if (i >= m) continue;
-#pragma unroll
-      for (int g = 0; g < 2; ++g) {
-        const int64_t c = b0 + 64 * g + 4 * j;
-        if (c < B) {
-          f32x4 o = f32x4{acc[mt][g][0][v], acc[mt][g][1][v], acc[mt][g][2][v], acc[mt][g][3][v]};
-          *reinterpret_cast<f32x4*>(ya + i * B + c) = o;
-        }
-      }
+      const int64_t i = 16 * mt + 4 * q + v;
+      if (i < m) *reinterpret_cast<f32x4u*>(ya + i * B) = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
     }
-  }
 }
 
 // Independent binary32 contractions of one shape class in one launch: job q owns the
@@ -806,11 +775,11 @@ struct MfmaPlan {
   int64_t kper;
 };
 
-MfmaPlan mfma_plan(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
+MfmaPlan mfma_plan(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m, int64_t unit_cols) {
   MfmaPlan p;
-  p.chunks = ceil_div(B, kUnitCols);
+  p.chunks = ceil_div(B, unit_cols);
   const int64_t units = A * p.chunks;
-  const int64_t kgran = (xdt == RT_BF16) ? 32 : 4;
+  const int64_t kgran = (xdt == RT_BF16 || unit_cols == kSplitCols) ? 32 : 4;
   int ks = 1;
   // aim for >= 2048 waves (8 per CU) when K is long enough to split; short K
   // (>= 64 per part) is split too while the partial sums stay under a quarter
@@ -865,78 +834,69 @@ int64_t ttm_mfma_mpad(int64_t m) { return ceil_div(m, 16) * 16; }
 
 bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
   if (m < 1 || m > 64 || A < 1 || K < 1) return false;
-  if (xdt == RT_F32) return B >= 64 && (B % 4) == 0;
+  // rows off the 16-byte grid: the split kernel takes them too, but a contraction with few columns
+  // is faster on the vector ALU, whose waves share the rows of M (80 x 49 x 49 over its first
+  // mode: 7 us against 9; 250 x 310 x 190 over its second: 42 against 25)
+  if (xdt == RT_F32) return B >= 64 && (B % 4 == 0 || A * ceil_div(B, 64) >= 256);
   if (xdt == RT_BF16) return B >= 64 && (B % 8) == 0 && (K % 8) == 0;
   return false;
 }
 
 size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
-  const MfmaPlan p = mfma_plan(xdt, A, K, B, m);
-  if (p.ksplit == 1) return 0;
-  return align256(static_cast<size_t>(p.ksplit) * A * m * B * sizeof(float));
+  // (a binary32 contraction may run alone or in a group, whose plans differ)
+  int ks = mfma_plan(xdt, A, K, B, m, kUnitCols).ksplit;
+  if (xdt == RT_F32) ks = std::max(ks, mfma_plan(xdt, A, K, B, m, kSplitCols).ksplit);
+  if (ks == 1) return 0;
+  return align256(static_cast<size_t>(ks) * A * m * B * sizeof(float));
 }
 
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop,
                               int64_t m, float* Y, void* ws, hipStream_t st) {
-  const MfmaPlan p = mfma_plan(xdt, A, K, B, m);
+  const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
   float* out = (p.ksplit == 1) ? Y : static_cast<float*>(ws);
-  const int64_t units = A * p.chunks * p.ksplit;
-  const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
-#define RT_LAUNCH_F32_K(KERNEL, MTV)                                                                        \
-  if (K % 4 == 0)                                                                                           \
-    KERNEL<MTV, true><<<grid, kMfmaThreads, 0, st>>>(static_cast<const float*>(X), A, K, B,                 \
-                                                     static_cast<const float*>(Mop), m, p.chunks, p.ksplit,  \
-                                                     p.kper, out);                                          \
-  else                                                                                                      \
-    KERNEL<MTV, false><<<grid, kMfmaThreads, 0, st>>>(static_cast<const float*>(X), A, K, B,                \
-                                                      static_cast<const float*>(Mop), m, p.chunks, p.ksplit, \
-                                                      p.kper, out)
-#define RT_LAUNCH_F32(MTV) RT_LAUNCH_F32_K(ttm_mfma_f32_occ2_kernel, MTV)
+  constexpr int64_t kUnits = kMfmaThreads / kWave;  // units per workgroup
+  if (xdt == RT_F32) {
+    // Eight waves a workgroup when each has a long range of k: they read 2 KB of a row together
+    // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
+    // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
+    // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
+    // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
+    // 49) was no faster here, unlike with binary32 products.
+    const bool wide = p.kper > 768;
+    const int64_t groups = ceil_div(A * p.chunks, wide ? 8 : 4);
+    const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
+#define RT_SPLIT(MTV, NTV)                                                                          \
+  ttm_split_f32_kernel<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const float*>(X), A, K, B,        \
+                                                       static_cast<const float*>(Mop), m, p.chunks, \
+                                                       groups, p.kper, out)
+#define RT_SPLIT_W(MTV)              \
+  do {                               \
+    if (wide) RT_SPLIT(MTV, 512);    \
+    else RT_SPLIT(MTV, 256);         \
+  } while (0)
+    switch (MT) {
+      case 1: RT_SPLIT_W(1); break;
+      case 2: RT_SPLIT_W(2); break;
+      case 3: RT_SPLIT_W(3); break;
+      default: RT_SPLIT_W(4); break;
+    }
+#undef RT_SPLIT_W
+#undef RT_SPLIT
+  } else {
+    const unsigned grid = static_cast<unsigned>(ceil_div(A * p.chunks * p.ksplit, kUnits));
 #define RT_LAUNCH_BF16(MTV)                                                                                 \
   ttm_mfma_bf16_kernel<MTV><<<grid, kMfmaThreads, 0, st>>>(static_cast<const bf16_t*>(X), A, K, B,          \
                                                            static_cast<const bf16_t*>(Mop), m, p.chunks,    \
                                                            p.ksplit, p.kper, out)
-  // rows past the last whole 16-row tile on the vector ALU when there are at most two
-  const int tail = (K % 4 == 0 && m % 16 != 0 && m % 16 <= 2 && m > 16) ? static_cast<int>(m % 16) : 0;
-  const int MTfull = static_cast<int>(m / 16);
-#define RT_LAUNCH_F32_TAIL(MTV, TV)                                                                         \
-  if (p.ksplit == 1)                                                                                         \
-    ttm_mfma_f32_mlds_kernel<MTV, TV, mlds_depth(MTV, TV), true><<<grid, kMfmaThreads, 0, st>>>(             \
-        static_cast<const float*>(X), A, K, B,                                                               \
-                                                                     static_cast<const float*>(Mop), m,      \
-                                                                     p.chunks, out);                         \
-  else                                                                                                       \
-    ttm_mfma_f32_kernel<MTV, true, TV><<<grid, kMfmaThreads, 0, st>>>(static_cast<const float*>(X), A, K, B, \
-                                                                      static_cast<const float*>(Mop), m,     \
-                                                                      p.chunks, p.ksplit, p.kper, out)
-  if (xdt == RT_F32 && tail > 0) {
-    if (MTfull == 1) {
-      if (tail == 1) RT_LAUNCH_F32_TAIL(1, 1); else RT_LAUNCH_F32_TAIL(1, 2);
-    } else if (MTfull == 2) {
-      if (tail == 1) RT_LAUNCH_F32_TAIL(2, 1); else RT_LAUNCH_F32_TAIL(2, 2);
-    } else {
-      if (tail == 1) RT_LAUNCH_F32_TAIL(3, 1); else RT_LAUNCH_F32_TAIL(3, 2);
-    }
-  } else if (xdt == RT_F32) {
-    switch (MT) {
-      case 1: RT_LAUNCH_F32(1); break;
-      case 2: RT_LAUNCH_F32(2); break;
-      case 3: RT_LAUNCH_F32(3); break;
-      default: RT_LAUNCH_F32_K(ttm_mfma_f32_kernel, 4); break;
-    }
-  } else {
     switch (MT) {
       case 1: RT_LAUNCH_BF16(1); break;
       case 2: RT_LAUNCH_BF16(2); break;
       case 3: RT_LAUNCH_BF16(3); break;
       default: RT_LAUNCH_BF16(4); break;
     }
-  }
-#undef RT_LAUNCH_F32
-#undef RT_LAUNCH_F32_K
-#undef RT_LAUNCH_F32_TAIL
 #undef RT_LAUNCH_BF16
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.ksplit == 1) return e;
   const int64_t n = A * m * B;
@@ -947,12 +907,14 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
 
 hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStream_t st) {
   if (count <= 0) return hipSuccess;
-  // one launch needs one kernel instance: every job with the same tile count and M load
+  // one launch needs one kernel instance: every job with the same tile count and M load, and
+  // rows that start on 16-byte boundaries
   int mt0 = -1;
   bool vm0 = true, same = count <= kMaxF32Group;
   for (int i = 0; i < count && same; ++i) {
     const int mt = static_cast<int>(ttm_mfma_mpad(c[i].m) / 16);
     const bool vm = c[i].K % 4 == 0;
+    if (c[i].B % 4 != 0 || reinterpret_cast<uintptr_t>(c[i].X) % 16 != 0) same = false;
     if (i == 0) {
       mt0 = mt;
       vm0 = vm;
@@ -973,7 +935,7 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStre
   tab.count = count;
   int64_t units = 0, sum_total = 0;
   for (int i = 0; i < count; ++i) {
-    const MfmaPlan p = mfma_plan(RT_F32, c[i].A, c[i].K, c[i].B, c[i].m);
+    const MfmaPlan p = mfma_plan(RT_F32, c[i].A, c[i].K, c[i].B, c[i].m, kUnitCols);
     F32Job& J = tab.j[i];
     J.X = c[i].X;
     J.Mop = c[i].Mop;

@@ -125,3 +125,73 @@ def test_sketch_pass_f32_nonfinite_stays_in_its_row_and_column():
     want_w = np.full((3, 2, 77), 40.0)
     want_w[1, :, 76] = np.inf
     assert np.array_equal(Z, want_z) and np.array_equal(W, want_w)
+
+
+# ------------------------------------------------------------------ binary32 contraction in three bfloat16 terms
+# 64-column waves of four or eight a workgroup (eight from k ranges past 512), 16-row tiles of M with
+# one row more, 32-k blocks, 64-k windows, splits of k, rows at any 4-byte boundary.  A binary32
+# sum of K products is within (K + 8) 2^-24 of the sum of their magnitudes in any order; the
+# matrix cores may truncate where an addition rounds, hence twice that.
+def _contract(X, U, skew=0):
+    G = rt.rtucker_core(_dev(X, torch.float32, skew), [None, _dev(U), None], modes=[1])
+    return G.double().cpu().numpy()
+
+
+@pytest.mark.parametrize("shape,m", [
+    ((1, 1, 64), 1), ((1, 5, 65), 16), ((3, 31, 67), 17), ((2, 33, 127), 33), ((5, 64, 130), 32), ((2, 65, 191), 49),
+    ((1, 100, 640), 64), ((7, 512, 66), 18), ((3, 513, 70), 17), ((2, 1030, 131), 49), ((9, 1100, 64), 33),
+    ((1, 2050, 257), 48), ((33, 96, 64), 50), ((1, 4000, 64), 3),
+])
+@pytest.mark.parametrize("skew", [0, 3])
+def test_contraction_f32_tiles(shape, m, skew):
+    rng = np.random.default_rng(sum(shape) + m)
+    X = rng.standard_normal(shape).astype(np.float32).astype(np.float64)
+    U = rng.standard_normal((shape[1], m)).astype(np.float32).astype(np.float64)
+    got = _contract(X, U, skew)
+    ref = np.einsum("akb,km->amb", X, U)
+    mag = np.einsum("akb,km->amb", np.abs(X), np.abs(U))
+    assert np.all(np.abs(got - ref) <= 2 * (shape[1] + 8) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("K,m", [(70, 20), (600, 49)])
+def test_contraction_f32_nonfinite(K, m):
+    rng = np.random.default_rng(K)
+    X = rng.standard_normal((2, K, 96)).astype(np.float32).astype(np.float64)
+    U = rng.standard_normal((K, m)).astype(np.float32).astype(np.float64)
+    X[0, 3, 5], X[1, K - 1, 95], X[1, 40, 64] = np.inf, -np.inf, np.nan
+    got = _contract(X, U)
+    assert np.array_equal(got[0, :, 5], np.sign(U[3]) * np.inf)
+    assert np.array_equal(got[1, :, 95], -np.sign(U[K - 1]) * np.inf)
+    assert np.all(np.isnan(got[1, :, 64]))
+    bad = np.zeros((2, 96), dtype=bool)
+    bad[0, 5] = bad[1, 95] = bad[1, 64] = True
+    fin = np.moveaxis(got, 1, 2)[~bad]
+    Xf = np.where(np.isfinite(X), X, 0.0)
+    ref = np.moveaxis(np.einsum("akb,km->amb", Xf, U), 1, 2)[~bad]
+    mag = np.moveaxis(np.einsum("akb,km->amb", np.abs(Xf), np.abs(U)), 1, 2)[~bad]
+    assert np.all(np.abs(fin - ref) <= 2 * (K + 8) * 2.0 ** -24 * mag)
+
+
+# scales where a term of x or M leaves bfloat16's range; every product and sum stays in binary32's
+# (the last row: its subnormals, hence the absolute part)
+@pytest.mark.parametrize("sx,su", [(2.0 ** -60, 1.0), (2.0 ** -110, 1.0), (2.0 ** -125, 1.0), (2.0 ** 100, 2.0 ** -110),
+                                   (2.0 ** -110, 2.0 ** 100), (2.0 ** 118, 1.0), (2.0 ** -140, 1.0)])
+@pytest.mark.parametrize("K,m", [(90, 33), (700, 17)])
+def test_contraction_f32_scales(sx, su, K, m):
+    rng = np.random.default_rng(K + m)
+    X = (rng.standard_normal((1, K, 72)) * sx).astype(np.float32).astype(np.float64)
+    U = (rng.standard_normal((K, m)) * su).astype(np.float32).astype(np.float64)
+    got = _contract(X, U)
+    ref = np.einsum("akb,km->amb", X, U)
+    mag = np.einsum("akb,km->amb", np.abs(X), np.abs(U))
+    assert np.all(np.abs(got - ref) <= 2 * (K + 8) * 2.0 ** -24 * mag + K * 2.0 ** -149)
+
+
+def test_contraction_f32_largest_entry():
+    X = np.zeros((1, 64, 64))
+    X[0, 7, 9] = float(np.finfo(np.float32).max)
+    U = np.zeros((64, 20))
+    U[7, 19] = 0.5
+    ref = np.zeros((1, 20, 64))
+    ref[0, 19, 9] = 0.5 * X[0, 7, 9]
+    assert np.array_equal(_contract(X, U), ref)
