@@ -194,7 +194,7 @@ void sketch_impl(Ctx& c, const Ten& X, const double* const* phi, const int64_t* 
     for (int i = 0; i < k; ++i) Ab *= dims[i];
     for (int i = k + 1; i < d; ++i) Bb *= dims[i];
     mf = ct == RT_F32 && ttm_mfma_ok(RT_F32, Ab, dims[k], Bb, s[k]);
-    last = ct == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_ok(Ab, dims[k], s[k]);
+    last = ct == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_ok(RT_F32, Ab, dims[k], s[k]);
   };
   // Memoised dimension tree below the two first-level nodes (Sec. 4.4): a node serves a
   // set M of requested modes; every mode that is neither contracted yet nor in M is
@@ -312,8 +312,7 @@ void sketch_impl(Ctx& c, const Ten& X, const double* const* phi, const int64_t* 
         const NodeKey& key = last_keys[i];
         const int k = key.second.back();
         const Ten& t = node.at(NodeKey{key.first, std::vector<int>(key.second.begin(), key.second.end() - 1)});
-        c.chk(launch_ttm_mfma_last(static_cast<const float*>(t.p), t.before(k), t.dims[k],
-                                   static_cast<const float*>(opm[k]), s[k],
+        c.chk(launch_ttm_mfma_last(t.p, RT_F32, t.before(k), t.dims[k], opm[k], s[k],
                                    static_cast<float*>(const_cast<void*>(node.at(key).p)), last_ws[i], c.st));
       }
       c.chk(launch_ttm_mfma_f32_group(group.data(), static_cast<int>(group.size()), c.st));
@@ -366,9 +365,8 @@ Ten core_impl(Ctx& c, const Ten& X, const double* const* U, const int64_t* l, ui
     st.in_dt = cur_dt;
     const rt_dtype ct = ctype(cur_dt);
     st.mfma = (cur_dt == RT_F32 || cur_dt == RT_BF16) && ttm_mfma_ok(cur_dt, st.A, st.K, st.B, st.m);
-    // a binary32 contraction over the last mode (B = 1) runs on the matrix-core kernel
-    // for contiguous rows
-    st.last = !st.mfma && cur_dt == RT_F32 && st.B == 1 && ttm_mfma_last_ok(st.A, st.K, st.m);
+    // a contraction over the last mode (B = 1) runs on the matrix-core kernel for contiguous rows
+    st.last = !st.mfma && st.B == 1 && ttm_mfma_last_ok(cur_dt, st.A, st.K, st.m);
     st.wide = last && f64_out && st.last && !dst;
     st.y = (last && dst) ? dst
                          : c.take(static_cast<size_t>(st.A) * st.m * st.B * (st.wide ? sizeof(double) : dtype_size(ct)));
@@ -376,7 +374,7 @@ Ten core_impl(Ctx& c, const Ten& X, const double* const* U, const int64_t* l, ui
       st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m));
       st.w = c.take(ttm_mfma_ws(cur_dt, st.A, st.K, st.B, st.m));
     } else if (st.last) {
-      st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, RT_F32, RT_F32, ttm_mfma_mpad(st.m));
+      st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m));
       st.w = c.take(ttm_mfma_last_ws(st.A, st.K, st.m, st.wide));
     } else {
       st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt == RT_F64 ? RT_F64 : cur_dt, ct);
@@ -393,7 +391,7 @@ Ten core_impl(Ctx& c, const Ten& X, const double* const* U, const int64_t* l, ui
       if (st.mfma)
         c.chk(launch_ttm_mfma_ws(cur.p, cur.dt, st.A, st.K, st.B, st.op, st.m, static_cast<float*>(st.y), st.w, c.st));
       else if (st.last)
-        c.chk(launch_ttm_mfma_last(static_cast<const float*>(cur.p), st.A, st.K, static_cast<const float*>(st.op), st.m,
+        c.chk(launch_ttm_mfma_last(cur.p, cur.dt, st.A, st.K, st.op, st.m,
                                    st.wide ? nullptr : static_cast<float*>(st.y), st.w, c.st,
                                    st.wide ? static_cast<double*>(st.y) : nullptr));
       else
@@ -955,7 +953,7 @@ int plan_multi_ttm(Ctx& c, const rt_tensor* X, const void* const* A, const int64
     void* dst = (i + 1 == order.size()) ? Y : nullptr;
     const int64_t Ab = cur.before(k), K = cur.dims[k], Bb = cur.after(k);
     const bool mf = X->dtype == RT_F32 && ttm_mfma_ok(RT_F32, Ab, K, Bb, m[k]);
-    const bool last = X->dtype == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_ok(Ab, K, m[k]);
+    const bool last = X->dtype == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_ok(RT_F32, Ab, K, m[k]);
     if (mf || last) {
       // matrix cores: operand packed to a multiple of 16 rows, binary32 accumulation
       const int64_t mp = ttm_mfma_mpad(m[k]);
@@ -970,7 +968,7 @@ int plan_multi_ttm(Ctx& c, const rt_tensor* X, const void* const* A, const int64
         float* y = static_cast<float*>(const_cast<void*>(out.p));
         c.chk(launch_pack_f32(static_cast<const float*>(M), m[k], K, trans != 0, mp, op, c.st));
         if (last)
-          c.chk(launch_ttm_mfma_last(static_cast<const float*>(cur.p), Ab, K, op, m[k], y, w, c.st));
+          c.chk(launch_ttm_mfma_last(cur.p, RT_F32, Ab, K, op, m[k], y, w, c.st));
         else
           c.chk(launch_ttm_mfma_ws(cur.p, RT_F32, Ab, K, Bb, op, m[k], y, w, c.st));
       }

@@ -194,6 +194,7 @@ __global__ __launch_bounds__(kWave) void ttm_grouped_kernel(const GTtmJob* __res
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));  // at any bfloat16 boundary
 
 constexpr int kMfmaThreads = 256;  // 4 waves, one 128-column unit each
 constexpr int kUnitCols = 128;
@@ -594,13 +595,58 @@ __global__ __launch_bounds__(256) void sum_splits_grouped_kernel(SumJobTable tab
 
 // Last-mode contraction (B == 1): Y[a, i] = sum_k X[a, k] M[i, k], a GEMM with
 // the long contiguous rows of X as the reduction axis.  A wave owns 64 rows of X
-// (four 16-row MFMA tiles) and reads them with 16-byte loads along k; the packed
-// operand supplies the 16-row tiles of M.  Requires K % 4 == 0.
-template <int MT>
-__global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_last_kernel(const float* __restrict__ X, int64_t A,
-                                                                         int64_t K, const float* __restrict__ Mop,
-                                                                         int64_t m, int ksplit, int64_t kper,
-                                                                         float* __restrict__ Y) {
+// (four 16-row MFMA tiles) and reads them with 16-byte loads along k, at whatever boundary the
+// rows start; the packed operand supplies the 16-row tiles of M.  A lane's 16 bytes are its
+// share of one or four products: 8 k of one 16x16x32 bfloat16 product, or one k of four 16x16x4
+// binary32 ones (k = k0 + 4 q + s in product s).  (bfloat16 X, and binary32 rows that are not a
+// multiple of four long, ran on the vector ALU before, a thread a row: LAST_FIGURES)
+template <typename TX>
+struct LastIO;
+template <>
+struct LastIO<float> {
+  typedef f32x4 vec_t;
+  typedef f32x4u load_t;
+  static constexpr int kPer = 4;  // k a lane
+  static __device__ __forceinline__ vec_t zero() { return vec_t{0.f, 0.f, 0.f, 0.f}; }
+  static __device__ __forceinline__ vec_t part(const float* p, int n) {  // the first n values
+    vec_t v = zero();
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (c < n) v[c] = p[c];
+    return v;
+  }
+  static __device__ __forceinline__ f32x4 mac(vec_t m, vec_t x, f32x4 acc, int c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(m[c], x[c], acc, 0, 0, 0);
+  }
+  static constexpr int kMacs = 4;
+};
+template <>
+struct LastIO<bf16_t> {
+  typedef u32x4 vec_t;
+  typedef u32x4u load_t;
+  static constexpr int kPer = 8;
+  static __device__ __forceinline__ vec_t zero() { return vec_t{0u, 0u, 0u, 0u}; }
+  static __device__ __forceinline__ vec_t part(const bf16_t* p, int n) {
+    vec_t v = zero();
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      v[w] = (2 * w < n ? p[2 * w] : 0u) | (2 * w + 1 < n ? static_cast<uint32_t>(p[2 * w + 1]) << 16 : 0u);
+    return v;
+  }
+  static __device__ __forceinline__ f32x4 mac(vec_t m, vec_t x, f32x4 acc, int) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, x), acc, 0,
+                                                   0, 0);
+  }
+  static constexpr int kMacs = 1;
+};
+
+template <typename TX, int MT>
+__global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K,
+                                                                     const TX* __restrict__ Mop, int64_t m, int ksplit,
+                                                                     int64_t kper, float* __restrict__ Y) {
+  typedef LastIO<TX> IO;
+  typedef typename IO::vec_t vec_t;
+  constexpr int kBlock = 4 * IO::kPer;  // k a step
   const int lane = threadIdx.x % kWave;
   const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
   const int64_t groups = (A + 63) / 64;
@@ -615,41 +661,48 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_last_kernel(const f
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int at = 0; at < 4; ++at) acc[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // The next 16 k are loaded while the current ones are multiplied.  Loads carry no
-  // conditions: k past kend reads the last four k of the range (zeroed before use; kbeg and
-  // kend are multiples of 4), and a row past A reads row A - 1 (its products land only in
-  // output rows that are not stored).
-  f32x4 nx[4], nw[MT];
+  // The next step's k are loaded while the current ones are multiplied.  A row past A reads row
+  // A - 1 (its products land only in output rows that are not stored); in the range's last step
+  // k past kend is zero in both operands.
+  const TX* xr[4];
+#pragma unroll
+  for (int at = 0; at < 4; ++at) {
+    const int64_t a = a0 + 16 * at + r16;
+    xr[at] = X + ((a < A) ? a : A - 1) * K + IO::kPer * q;
+  }
+  const TX* mr = Mop + r16 * K + IO::kPer * q;
+  vec_t nx[4], nw[MT];
   const auto load = [&](int64_t k0) {
-    const int64_t k = k0 + 4 * q;
-    const int64_t kc = (k < kend) ? k : kend - 4;
+    if (k0 + kBlock <= kend) {
 #pragma unroll
-    for (int at = 0; at < 4; ++at) {
-      const int64_t a = a0 + 16 * at + r16;
-      nx[at] = *reinterpret_cast<const f32x4*>(X + ((a < A) ? a : A - 1) * K + kc);
+      for (int at = 0; at < 4; ++at) nx[at] = *reinterpret_cast<const typename IO::load_t*>(xr[at] + k0);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) nw[mt] = *reinterpret_cast<const typename IO::load_t*>(mr + 16 * mt * K + k0);
+    } else if (k0 < kend) {
+      const int64_t left = kend - (k0 + IO::kPer * q);
+      const int n = left < 0 ? 0 : (left < IO::kPer ? static_cast<int>(left) : IO::kPer);
+#pragma unroll
+      for (int at = 0; at < 4; ++at) nx[at] = IO::part(xr[at] + k0, n);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) nw[mt] = IO::part(mr + 16 * mt * K + k0, n);
     }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) nw[mt] = *reinterpret_cast<const f32x4*>(Mop + (16 * mt + r16) * K + kc);
   };
-  if (kbeg < kend) load(kbeg);
-  const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int64_t k0 = kbeg; k0 < kend; k0 += 16) {
-    const bool kin = k0 + 4 * q < kend;
-    f32x4 xv[4], mv[MT];
+  load(kbeg);
+  for (int64_t k0 = kbeg; k0 < kend; k0 += kBlock) {
+    vec_t xv[4], mv[MT];
 #pragma unroll
-    for (int at = 0; at < 4; ++at) xv[at] = kin ? nx[at] : zero4;
+    for (int at = 0; at < 4; ++at) xv[at] = nx[at];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) mv[mt] = kin ? nw[mt] : zero4;
+    for (int mt = 0; mt < MT; ++mt) mv[mt] = nw[mt];
     __builtin_amdgcn_sched_barrier(0);
-    load(k0 + 16);  // past kend: clamped, never used
+    load(k0 + kBlock);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
+    for (int c = 0; c < IO::kMacs; ++c)
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int at = 0; at < 4; ++at)
-          acc[mt][at] = __builtin_amdgcn_mfma_f32_16x16x4f32(mv[mt][c], xv[at][c], acc[mt][at], 0, 0, 0);
+        for (int at = 0; at < 4; ++at) acc[mt][at] = IO::mac(mv[mt], xv[at], acc[mt][at], c);
   }
   float* y = Y + static_cast<int64_t>(ks) * A * m;
 #pragma unroll
@@ -669,24 +722,31 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_last_kernel(const f
 __device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return (a & 0xffffu) | (b << 16); }
 __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 
-template <int MT>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_bf16_kernel(
-    const bf16_t* __restrict__ X, int64_t A,
-                                                                     int64_t K, int64_t B,
-                                                                     const bf16_t* __restrict__ Mop, int64_t m,
-                                                                     int64_t chunks, int ksplit, int64_t kper,
-                                                                     float* __restrict__ Y) {
-  const int lane = threadIdx.x % kWave;
-  const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
-  const int64_t total = A * chunks * ksplit;
-  if (unit >= total) return;
-  const int ks = static_cast<int>(unit % ksplit);
-  const int64_t ac = unit / ksplit;
-  const int64_t a = ac / chunks;
-  const int64_t b0 = (ac - a * chunks) * kUnitCols;
+// bfloat16 contraction on 16x16x32 products.  A wave owns 128 columns of one slab (lane j: eight
+// consecutive columns, at any 2-byte boundary) and takes k in blocks of 32: lane group q loads
+// the rows k0 + 8 q .. + 7, with the next block in flight during the block's products, and packs
+// the eight k of a column just before its products (which keeps two waves on a SIMD).  The waves
+// of a workgroup share the k range, and M is staged in LDS 64 k at a time, double-buffered, zero
+// past the range.  Bound: HBM.  Rows off the 16-byte grid ran on the vector ALU before, at a
+// twentieth of the rate: BF16_FIGURES
+template <int MT, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_bf16_kernel(
+    const bf16_t* __restrict__ X, int64_t A, int64_t K, int64_t B, const bf16_t* __restrict__ Mop, int64_t m,
+    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y) {
+  __shared__ __align__(16) uint16_t sM[2][16 * MT * kSplitStride];
+  const int tid = threadIdx.x, lane = tid % kWave;
   const int j = lane % 16, q = lane / 16;
+  const int64_t ks = blockIdx.x / groups;
+  const int64_t unit_raw = (blockIdx.x - ks * groups) * (NT / kWave) + tid / kWave;
+  const bool active = unit_raw < A * chunks;
+  const int64_t unit = active ? unit_raw : 0;
+  const int64_t a = unit / chunks;
+  const int64_t col_raw = (unit - a * chunks) * kUnitCols + 8 * j;
+  // a lane whose columns run past B takes the last eight: its results repeat its neighbour's
+  const int64_t col = col_raw + 8 <= B ? col_raw : B - 8;
   const int64_t kbeg = ks * kper;
   const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
+  const bf16_t* xa = X + a * K * B + col;
 
   f32x4 acc[MT][8];
 #pragma unroll
@@ -694,38 +754,74 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const bf16_t* xa = X + a * K * B;
-  const int64_t col = b0 + 8 * j;
-  const bool colok = col < B;
-  // Lane loads rows k0 + 8q + t (t < 8) of columns col..col+7 and the matching 8 k of M.
-  // The next 32 k are loaded while the current ones are multiplied.  Loads carry no
-  // conditions: a block past kend reads the last 8 k of the range (zeroed before use; kbeg
-  // and kend are multiples of 8), and a column block past B reads the last 8 columns (its
-  // products land only in output columns that are not stored).
-  const int64_t colc = colok ? col : B - 8;
-  u32x4 rn[8], nw[MT];
+  // as in the binary32 kernel: the lane's rows of a block at xp; in the range's last block rows
+  // past kend read row kend - 1 again (zeroed when the block is taken over)
+  u32x4 rn[8];
+  const bf16_t* xp = xa + (kbeg + 8 * q) * B;
   const auto load = [&](int64_t k0) {
-    const int64_t k = k0 + 8 * q;
-    const int64_t kc = (k < kend) ? k : kend - 8;
+    if (k0 + 32 <= kend) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) nw[mt] = *reinterpret_cast<const u32x4*>(Mop + (mt * 16 + j) * K + kc);
+      for (int t = 0; t < 8; ++t) rn[t] = *reinterpret_cast<const u32x4u*>(xp + t * B);
+    } else if (k0 < kend) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) rn[t] = *reinterpret_cast<const u32x4*>(xa + (kc + t) * B + colc);
+      for (int t = 0; t < 8; ++t) {
+        const int64_t k = k0 + 8 * q + t;
+        rn[t] = *reinterpret_cast<const u32x4u*>(xa + (k < kend ? k : kend - 1) * B);
+      }
+    }
+    xp += 32 * B;
   };
-  if (kbeg < kend) load(kbeg);
-  const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+  // staging: group g = NT i + tid of a window is row g / 8, k = kw + 8 (g % 8) ..
+  constexpr int kGroups = 16 * MT * (kSplitWin / 8), kPer = (kGroups + NT - 1) / NT;
+  u32x4 sv[kPer];
+  const auto stage_load = [&](int64_t kw) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int g = i * NT + tid;
+      if (g >= kGroups) break;
+      const int64_t k = kw + 8 * (g % 8);
+      const bf16_t* src = Mop + static_cast<int64_t>(g / 8) * K + k;
+      if (k + 8 <= kend) {
+        sv[i] = *reinterpret_cast<const u32x4u*>(src);
+      } else {
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+          sv[i][w] = (k + 2 * w < kend ? src[2 * w] : 0u) |
+                     (k + 2 * w + 1 < kend ? static_cast<uint32_t>(src[2 * w + 1]) << 16 : 0u);
+      }
+    }
+  };
+  const auto stage_store = [&](int b) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int g = i * NT + tid;
+      if (g >= kGroups) break;
+      *reinterpret_cast<u32x4*>(&sM[b][(g / 8) * kSplitStride + 8 * (g % 8)]) = sv[i];
+    }
+  };
+  load(kbeg);
+  stage_load(kbeg);
+  stage_store(0);
+  __syncthreads();
+  int buf = 0, half = 0;
   for (int64_t k0 = kbeg; k0 < kend; k0 += 32) {
-    const bool kin = k0 + 8 * q < kend;
-    u32x4 r[8], mv[MT];
+    const bool more = k0 + (kSplitWin - 32 * half) < kend;
+    if (half == 0 && more) stage_load(k0 + kSplitWin);
+    u32x4 r[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) r[t] = kin ? rn[t] : zero4;
+    for (int t = 0; t < 8; ++t) r[t] = rn[t];
+    if (k0 + 32 > kend) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) mv[mt] = kin ? nw[mt] : zero4;
+      for (int t = 0; t < 8; ++t)
+        if (k0 + 8 * q + t >= kend) r[t] = u32x4{0u, 0u, 0u, 0u};
+    }
     __builtin_amdgcn_sched_barrier(0);
-    load(k0 + 32);  // past kend: clamped, never used
+    load(k0 + 32);
     __builtin_amdgcn_sched_barrier(0);
-    // operand for column c (8 consecutive k of column col + c) is packed just before its
-    // products, which keeps the register count low enough for two waves per SIMD
+    bf16x8 mv[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+      mv[mt] = *reinterpret_cast<const bf16x8*>(&sM[buf][(16 * mt + j) * kSplitStride + 32 * half + 8 * q]);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       u32x4 op;
@@ -737,24 +833,27 @@ __global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2)
       const bf16x8 bv = __builtin_bit_cast(bf16x8, op);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
-        acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, mv[mt]), bv, acc[mt][c], 0,
-                                                             0, 0);
+        acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[mt], bv, acc[mt][c], 0, 0, 0);
+    }
+    half ^= 1;
+    if (half == 0 || k0 + 32 >= kend) {
+      if (more) stage_store(buf ^ 1);
+      lds_barrier();  // the window is read by every wave and the next one staged; loads of X stay in flight
+      buf ^= 1;
     }
   }
-  float* ya = Y + (static_cast<int64_t>(ks) * A + a) * m * B;
-  if (!colok) return;
+  if (!active || col_raw >= B) return;
+  float* ya = Y + (ks * A + a) * m * B + col;
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int64_t i = mt * 16 + 4 * q + v;
+      const int64_t i = 16 * mt + 4 * q + v;
       if (i >= m) continue;
-      f32x4 o0 = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
-      f32x4 o1 = f32x4{acc[mt][4][v], acc[mt][5][v], acc[mt][6][v], acc[mt][7][v]};
-      *reinterpret_cast<f32x4*>(ya + i * B + col) = o0;
-      *reinterpret_cast<f32x4*>(ya + i * B + col + 4) = o1;
+      f32x4u* dst = reinterpret_cast<f32x4u*>(ya + i * B);
+      dst[0] = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
+      dst[1] = f32x4{acc[mt][4][v], acc[mt][5][v], acc[mt][6][v], acc[mt][7][v]};
     }
-  }
 }
 
 // Y = sum of the split parts in part order (binary32), stored as TO
@@ -838,7 +937,7 @@ bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
   // is faster on the vector ALU, whose waves share the rows of M (80 x 49 x 49 over its first
   // mode: 7 us against 9; 250 x 310 x 190 over its second: 42 against 25)
   if (xdt == RT_F32) return B >= 64 && (B % 4 == 0 || A * ceil_div(B, 64) >= 256);
-  if (xdt == RT_BF16) return B >= 64 && (B % 8) == 0 && (K % 8) == 0;
+  if (xdt == RT_BF16) return B >= 64 && ((B % 8 == 0 && K % 8 == 0) || A * ceil_div(B, 64) >= 256);
   return false;
 }
 
@@ -855,48 +954,34 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
   const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
   float* out = (p.ksplit == 1) ? Y : static_cast<float*>(ws);
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
-  constexpr int64_t kUnits = kMfmaThreads / kWave;  // units per workgroup
-  if (xdt == RT_F32) {
-    // Eight waves a workgroup when each has a long range of k: they read 2 KB of a row together
-    // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
-    // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
-    // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
-    // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
-    // 49) was no faster here, unlike with binary32 products.
-    const bool wide = p.kper > 768;
-    const int64_t groups = ceil_div(A * p.chunks, wide ? 8 : 4);
-    const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
-#define RT_SPLIT(MTV, NTV)                                                                          \
-  ttm_split_f32_kernel<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const float*>(X), A, K, B,        \
-                                                       static_cast<const float*>(Mop), m, p.chunks, \
-                                                       groups, p.kper, out)
-#define RT_SPLIT_W(MTV)              \
-  do {                               \
-    if (wide) RT_SPLIT(MTV, 512);    \
-    else RT_SPLIT(MTV, 256);         \
+  // The waves of a workgroup share the k range.  Binary32: eight waves a workgroup when each has a
+  // long range of k: they read 2 KB of a row together
+  // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
+  // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
+  // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
+  // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
+  // 49) was no faster here, unlike with binary32 products.
+  const bool wide = xdt == RT_F32 ? p.kper > 768 : MT == 4;
+  const int64_t groups = ceil_div(A * p.chunks, wide ? 8 : 4);
+  const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
+#define RT_TTM(KERNEL, TX, MTV, NTV)                                                                      \
+  KERNEL<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const TX*>(X), A, K, B, static_cast<const TX*>(Mop), \
+                                         m, p.chunks, groups, p.kper, out)
+#define RT_TTM_ANY(MTV)                                          \
+  do {                                                           \
+    if (xdt == RT_BF16 && wide) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 512); \
+    else if (xdt == RT_BF16) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 256); \
+    else if (wide) RT_TTM(ttm_split_f32_kernel, float, MTV, 512);  \
+    else RT_TTM(ttm_split_f32_kernel, float, MTV, 256);          \
   } while (0)
-    switch (MT) {
-      case 1: RT_SPLIT_W(1); break;
-      case 2: RT_SPLIT_W(2); break;
-      case 3: RT_SPLIT_W(3); break;
-      default: RT_SPLIT_W(4); break;
-    }
-#undef RT_SPLIT_W
-#undef RT_SPLIT
-  } else {
-    const unsigned grid = static_cast<unsigned>(ceil_div(A * p.chunks * p.ksplit, kUnits));
-#define RT_LAUNCH_BF16(MTV)                                                                                 \
-  ttm_mfma_bf16_kernel<MTV><<<grid, kMfmaThreads, 0, st>>>(static_cast<const bf16_t*>(X), A, K, B,          \
-                                                           static_cast<const bf16_t*>(Mop), m, p.chunks,    \
-                                                           p.ksplit, p.kper, out)
-    switch (MT) {
-      case 1: RT_LAUNCH_BF16(1); break;
-      case 2: RT_LAUNCH_BF16(2); break;
-      case 3: RT_LAUNCH_BF16(3); break;
-      default: RT_LAUNCH_BF16(4); break;
-    }
-#undef RT_LAUNCH_BF16
+  switch (MT) {
+    case 1: RT_TTM_ANY(1); break;
+    case 2: RT_TTM_ANY(2); break;
+    case 3: RT_TTM_ANY(3); break;
+    default: RT_TTM_ANY(4); break;
   }
+#undef RT_TTM_ANY
+#undef RT_TTM
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.ksplit == 1) return e;
   const int64_t n = A * m * B;
@@ -976,7 +1061,9 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStre
   return hipGetLastError();
 }
 
-bool ttm_mfma_last_ok(int64_t A, int64_t K, int64_t m) { return A >= 1 && m >= 1 && m <= 64 && K >= 4 && K % 4 == 0; }
+bool ttm_mfma_last_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t m) {
+  return (xdt == RT_F32 || xdt == RT_BF16) && A >= 1 && m >= 1 && m <= 64 && K >= 4;
+}
 
 namespace {
 struct LastPlan {
@@ -989,7 +1076,7 @@ LastPlan last_plan(int64_t A, int64_t K, int64_t m) {
   int ks = 1;
   while (units * ks < 2048 && K / (ks * 2) >= 64 && ks < 16 && 2 * ks * A * m * 4 <= A * K * 4) ks *= 2;
   p.ksplit = ks;
-  p.kper = ceil_div(ceil_div(K, ks), 16) * 16;
+  p.kper = ceil_div(ceil_div(K, ks), 32) * 32;
   return p;
 }
 }  // namespace
@@ -999,15 +1086,22 @@ size_t ttm_mfma_last_ws(int64_t A, int64_t K, int64_t m, bool f64_out) {
   return (p.ksplit == 1 && !f64_out) ? 0 : align256(static_cast<size_t>(p.ksplit) * A * m * sizeof(float));
 }
 
-hipError_t launch_ttm_mfma_last(const float* X, int64_t A, int64_t K, const float* Mop, int64_t m, float* Y,
+hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t K, const void* Mop, int64_t m, float* Y,
                                 void* ws, hipStream_t st, double* Y64) {
   const LastPlan p = last_plan(A, K, m);
   float* out = (p.ksplit == 1 && !Y64) ? Y : static_cast<float*>(ws);
   const int64_t units = ceil_div(A, 64) * p.ksplit;
   const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
-#define RT_LAUNCH_LAST(MTV) \
-  ttm_mfma_f32_last_kernel<MTV><<<grid, kMfmaThreads, 0, st>>>(X, A, K, Mop, m, p.ksplit, p.kper, out)
+#define RT_LAUNCH_LAST(MTV)                                                                                       \
+  do {                                                                                                            \
+    if (xdt == RT_F32)                                                                                            \
+      ttm_mfma_last_kernel<float, MTV><<<grid, kMfmaThreads, 0, st>>>(                                            \
+          static_cast<const float*>(X), A, K, static_cast<const float*>(Mop), m, p.ksplit, p.kper, out);          \
+    else                                                                                                          \
+      ttm_mfma_last_kernel<bf16_t, MTV><<<grid, kMfmaThreads, 0, st>>>(                                           \
+          static_cast<const bf16_t*>(X), A, K, static_cast<const bf16_t*>(Mop), m, p.ksplit, p.kper, out);        \
+  } while (0)
   switch (MT) {
     case 1: RT_LAUNCH_LAST(1); break;
     case 2: RT_LAUNCH_LAST(2); break;

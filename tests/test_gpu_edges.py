@@ -195,3 +195,54 @@ def test_contraction_f32_largest_entry():
     ref = np.zeros((1, 20, 64))
     ref[0, 19, 9] = 0.5 * X[0, 7, 9]
     assert np.array_equal(_contract(X, U), ref)
+
+
+# ------------------------------------------------------------------ bfloat16 contraction
+# 128-column waves (eight columns a lane, at any 2-byte boundary), 16-row tiles of M, 32-k blocks, 64-k
+# windows, rows past the range.  Products of bfloat16 values are exact; binary32 sums as above.
+@pytest.mark.parametrize("shape,m", [
+    ((256, 1, 64), 1), ((250, 5, 65), 16), ((130, 31, 131), 17), ((256, 33, 71), 33), ((43, 64, 390), 32),
+    ((256, 65, 127), 49), ((3, 100, 16001), 64), ((128, 513, 129), 18), ((2, 96, 136), 20), ((300, 200, 64), 50),
+])
+@pytest.mark.parametrize("skew", [0, 1])
+@pytest.mark.parametrize("bad", [False, True])
+def test_contraction_bf16_tiles(shape, m, skew, bad):
+    rng = np.random.default_rng(sum(shape) + m)
+    X = torch.from_numpy(rng.standard_normal(shape)).to(torch.bfloat16).double().numpy()
+    U = torch.from_numpy(rng.standard_normal((shape[1], m))).to(torch.bfloat16).double().numpy()
+    fin = np.ones((shape[0], shape[2]), dtype=bool)
+    if bad:
+        X[0, shape[1] - 1, shape[2] - 1] = np.inf
+        fin[0, shape[2] - 1] = False
+    got = rt.rtucker_core(_dev(X, torch.bfloat16, skew), [None, _dev(U), None], modes=[1]).double().cpu().numpy()
+    Xf = np.where(np.isfinite(X), X, 0.0)
+    ref = np.moveaxis(np.einsum("akb,km->amb", Xf, U, optimize=True), 1, 2)[fin]
+    mag = np.moveaxis(np.einsum("akb,km->amb", np.abs(Xf), np.abs(U), optimize=True), 1, 2)[fin]
+    assert np.all(np.abs(np.moveaxis(got, 1, 2)[fin] - ref) <= 2 * (shape[1] + 8) * 2.0 ** -24 * mag)
+    if bad:
+        want = np.sign(U[-1]) * np.inf
+        assert np.array_equal(got[0, :, -1][U[-1] != 0], want[U[-1] != 0])
+
+
+# ------------------------------------------------------------------ contraction of the contiguous last mode
+# 64-row waves, 16-row tiles of M, 16-k (binary32) or 32-k (bfloat16) steps cut anywhere by the row's end,
+# splits of k, rows at any boundary.
+@pytest.mark.parametrize("shape,m", [((4, 1, 5), 1), ((2, 3, 16), 16), ((63, 1, 31), 17), ((13, 5, 33), 33), ((2, 64, 63), 64),
+                                     ((3, 43, 130), 20), ((65, 1, 257), 49), ((40, 50, 519), 24)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("skew", [0, 1])
+@pytest.mark.parametrize("bad", [False, True])
+def test_contraction_last_mode_tiles(shape, m, dtype, skew, bad):
+    rng = np.random.default_rng(sum(shape) + m)
+    K = shape[2]
+    X = torch.from_numpy(rng.standard_normal(shape)).to(dtype).double().numpy()
+    U = torch.from_numpy(rng.standard_normal((K, m))).to(dtype).double().numpy()
+    fin = np.ones(shape[:2], dtype=bool)
+    if bad:
+        X[-1, -1, K - 1] = np.inf
+        fin[-1, -1] = False
+    got = rt.rtucker_core(_dev(X, dtype, skew), [None, None, _dev(U)], modes=[2]).double().cpu().numpy()
+    Xf = np.where(np.isfinite(X), X, 0.0)
+    assert np.all(np.abs(got - Xf @ U)[fin] <= (2 * (K + 8) * 2.0 ** -24 * (np.abs(Xf) @ np.abs(U)))[fin])
+    if bad:
+        assert np.array_equal(got[-1, -1], np.sign(U[-1]) * np.inf)
