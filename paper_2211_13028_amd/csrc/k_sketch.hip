@@ -125,41 +125,53 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const TC* __restrict__ p
 // Same two contractions on MFMA (v_mfma_f32_16x16x32_bf16, binary32 accumulation).
 // FP8 e4m3 data is widened exactly to bfloat16 as it is loaded, so it streams at
 // one byte per element and multiplies as the FP8 values themselves.
-// A workgroup of four waves covers 512 columns of a row range; wave w owns the
-// 128 columns q0 + 128 w .. + 127 and all waves step through the rows together,
-// 32 at a time:
+// A wave owns 128 columns of a slab X[a]; CW waves side by side cover the column block (up to 512
+// columns) and the workgroup takes 4 / CW slabs (a short last mode keeps all waves busy).  All
+// waves step through the same rows, 32 at a time:
 //  * W^T tile: out[c][q] = sum_p PhiP[c][p] X[p][q].  Each lane loads an 8 x 8
 //    block (8 rows, 8 consecutive columns, 16 bytes per row) and re-packs it in
 //    registers into 8 operands holding 8 consecutive p of one column; the wave
 //    keeps its 16 x 128 accumulator for the whole row range (no cross-wave sum).
 //  * Z tile: out[p][c] = sum_q X[p][q] PhiQ[c][q] over the wave's 128 columns,
 //    with the X rows staged row-major in the wave's LDS area as the A operand;
-//    the four waves' partial Z rows are added in LDS in a fixed order, one
+//    the CW waves' partial Z rows are added in LDS in a fixed order, one
 //    barrier per step (double-buffered partials).
-// The next 32 rows are loaded while the current ones are used.  Rows beyond P and
-// operand rows beyond s are zero.  Requires P % 8 == 0, Q % 8 == 0, s <= 8.
+// The next 32 rows are loaded while the current ones are used.  Rows may start at any boundary:
+// a group of eight columns that the row's end cuts runs into the next row (masked when it is
+// taken over), except in the tensor's last rows, where it is loaded entry by entry.  Rows beyond P and
+// operand rows beyond s are zero.  P, Q >= 16, s <= 8.  EVEN (P, Q multiples of eight): groups lie
+// wholly inside or outside the range, and the loads carry no conditions at all: one past the
+// range reads the last group in it, zeroed when it is taken over (260 us for 1024 x 1024 x 512
+// bfloat16 sketches, 281 with the other form).  (Sizes off the 16-byte grid ran on the
+// vector-ALU pass before: ZW16_FIGURES)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(1)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int kZWColsMfma = 512;
 constexpr int kTileStride = 136;  // bf16 per staged row: 128 columns + 8 padding (spreads LDS banks)
 
-__device__ __forceinline__ u32x4 ld16(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
-
-// Raw loads of an 8-row x 8-column block (row t: 8 consecutive columns) and their
-// widening to bfloat16 pairs.  The widening happens when a prefetched block is
-// used, so the loads stay in flight across the previous step.
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
+// Raw loads of eight consecutive entries and their widening to bfloat16 pairs.  The widening
+// happens when a prefetched block is used, so the loads stay in flight across the previous step.
+// part: the first n of them, the others zero.
 template <typename TX>
 struct BlockIO;
 
 template <>
 struct BlockIO<bf16_t> {
   typedef u32x4 raw_t;  // 8 bfloat16
-  static __device__ __forceinline__ raw_t load(const bf16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
-  static __device__ __forceinline__ raw_t zero() { return u32x4{0u, 0u, 0u, 0u}; }
+  static __device__ __forceinline__ raw_t load(const bf16_t* p) { return *reinterpret_cast<const u32x4u*>(p); }
+  static __device__ __forceinline__ raw_t part(const bf16_t* p, int n) {
+    raw_t v;
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      v[w] = (2 * w < n ? p[2 * w] : 0u) | (2 * w + 1 < n ? static_cast<uint32_t>(p[2 * w + 1]) << 16 : 0u);
+    return v;
+  }
   static __device__ __forceinline__ u32x4 widen(raw_t v) { return v; }
 };
 
@@ -168,8 +180,14 @@ struct BlockIO<bf16_t> {
 template <>
 struct BlockIO<f8_t> {
   typedef u32x2 raw_t;
-  static __device__ __forceinline__ raw_t load(const f8_t* p) { return *reinterpret_cast<const u32x2*>(p); }
-  static __device__ __forceinline__ raw_t zero() { return u32x2{0u, 0u}; }
+  static __device__ __forceinline__ raw_t load(const f8_t* p) { return *reinterpret_cast<const u32x2u*>(p); }
+  static __device__ __forceinline__ raw_t part(const f8_t* p, int n) {
+    raw_t v = u32x2{0u, 0u};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (e < n) v[e / 4] |= static_cast<uint32_t>(p[e]) << (8 * (e % 4));
+    return v;
+  }
   static __device__ __forceinline__ u32x4 widen(raw_t v) {
     return u32x4{__builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[0], 1.0f, false)),
                  __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v[0], 1.0f, true)),
@@ -178,121 +196,178 @@ struct BlockIO<f8_t> {
   }
 };
 
-template <typename TX>
+// entries of a group of eight that lie before `end` (first: entry 0)
+__device__ __forceinline__ int group_count(int64_t first, int64_t end) {
+  return first + 8 <= end ? 8 : (first < end ? static_cast<int>(end - first) : 0);
+}
+
+template <typename TX, bool EVEN, int CW>
 __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3))) void sketch_zw_bf16_mfma_kernel(
     const TX* __restrict__ X, int64_t A, int64_t P, int64_t Q, const bf16_t* __restrict__ phiP, int sP,
-    const bf16_t* __restrict__ phiQ, int sQ, int64_t rows_per_block, int qblocks, int pblocks,
+    const bf16_t* __restrict__ phiQ, int sQ, int64_t rows_per_block, int64_t qcols, int qblocks, int pblocks,
     float* __restrict__ Zo, float* __restrict__ Wo) {
-  __shared__ bf16_t tile[kZWWaves][32 * kTileStride];
-  __shared__ float zpart[2][kZWWaves][32 * 16];
+  typedef BlockIO<TX> IO;
+  constexpr int kSlabs = kZWWaves / CW;
+  __shared__ __align__(16) bf16_t tile[kZWWaves][32 * kTileStride];
+  __shared__ float zpart[2][CW > 1 ? kZWWaves : 1][CW > 1 ? 32 * 16 : 1];
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int64_t blk = blockIdx.x;
   const int qblk = static_cast<int>(blk % qblocks);
   const int64_t rest = blk / qblocks;
   const int pblk = static_cast<int>(rest % pblocks);
-  const int64_t a = rest / pblocks;
-  const int64_t q0 = static_cast<int64_t>(qblk) * kZWColsMfma;
-  const int64_t qend = (q0 + kZWColsMfma < Q) ? q0 + kZWColsMfma : Q;
-  const int64_t qw = q0 + 128 * wave;  // this wave's columns
+  const int64_t a_raw = (rest / pblocks) * kSlabs + wave / CW;
+  const int64_t a = a_raw < A ? a_raw : A - 1;
+  const int64_t q0 = static_cast<int64_t>(qblk) * qcols;
+  const int64_t qend = (q0 + qcols < Q) ? q0 + qcols : Q;
+  const int64_t qw = q0 + 128 * (wave % CW);  // this wave's columns
+  const bool on = a_raw < A && qw < qend;     // waves past the last slab or column only keep the barriers
   const bool needZ = Zo != nullptr, needW = Wo != nullptr;
   const int li = lane % 16, kg = lane / 16;
   const int64_t pbeg = static_cast<int64_t>(pblk) * rows_per_block;
   const int64_t pend = (pbeg + rows_per_block < P) ? pbeg + rows_per_block : P;
   const TX* xa = X + a * P * Q;
+  float* zout = needZ ? Zo + (static_cast<int64_t>(qblk) * A + a) * P * sQ : nullptr;
   bf16_t* my = tile[wave];
   const int64_t qc = qw + 8 * li;
-  const bool colok = qc < qend;
+  const int ncol = group_count(qc, qend);
+  u32x4 cmask;  // the lane's columns that exist
+#pragma unroll
+  for (int w = 0; w < 4; ++w) cmask[w] = (2 * w < ncol ? 0xffffu : 0u) | (2 * w + 1 < ncol ? 0xffff0000u : 0u);
 
   // loop-invariant PhiQ operands of the Z product: row c = li, 8 columns per k group
   u32x4 bq[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
     const int64_t qk = qw + 32 * ks + 8 * kg;
-    bq[ks] = (needZ && qk < qend) ? ld16(phiQ + static_cast<int64_t>(li) * Q + qk) : u32x4{0u, 0u, 0u, 0u};
+    const int n = needZ ? group_count(qk, qend) : 0;
+    const bf16_t* src = phiQ + static_cast<int64_t>(li) * Q + qk;
+    bq[ks] = n == 8 ? BlockIO<bf16_t>::load(src) : BlockIO<bf16_t>::part(src, n);
   }
   f32x4 wacc[8];
 #pragma unroll
   for (int c = 0; c < 8; ++c) wacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Lane (li, kg) loads rows p0 + 8 kg + t (t < 8), columns qc..qc+7.  Loads carry no
-  // conditions: an 8-row group past pend reads the last 8 rows of the range and a column
-  // group past qend the last 8 columns of the block (8-row groups lie wholly inside or
-  // outside [pbeg, pend) because P % 8 == 0 and steps are 32 rows; Q % 8 == 0); such
-  // values are zeroed when the block is taken over.
-  const int64_t qcc = colok ? qc : qend - 8;
-  // The PhiP operand of the W product (row c = li, columns pc .. pc + 7) comes with the
-  // rows, clamped and zeroed the same way.
-  typename BlockIO<TX>::raw_t rn[8];
+  // Lane (li, kg) loads rows p0 + 8 kg + t (t < 8), columns qc..qc+7, and the PhiP operand of the
+  // W product (row c = li, columns p0 + 8 kg ..).  A column group past qend reads the row's last
+  // eight entries; such values are masked when the block is taken over.  In the range's last step
+  // a row past pend reads row pend - 1 (zeroed when taken over).
+  const int64_t qcc = ncol > 0 ? qc : Q - 8;
+  typename IO::raw_t rn[8];
   u32x4 ppn = u32x4{0u, 0u, 0u, 0u};
+  const TX* xp = xa + (pbeg + 8 * kg) * Q + qcc;  // the lane's rows of the next step
+  const bf16_t* fp = phiP + (needW ? static_cast<int64_t>(li) * P + pbeg + 8 * kg : 0);
   const auto load = [&](int64_t pb) {
-    const int64_t p = pb + 8 * kg;
-    const int64_t pc = (p < pend) ? p : pend - 8;
-    // without W the load reads an entry of PhiQ (in bounds: Z is then computed) and is unused
-    ppn = ld16(needW ? phiP + static_cast<int64_t>(li) * P + pc : phiQ + static_cast<int64_t>(li) * Q + (qend - 8));
+    if constexpr (EVEN) {
+      const int64_t p = pb + 8 * kg;
+      const int64_t pc = p < pend ? p : pend - 8;
+      // without W the load reads an entry of PhiQ (in bounds: Z is then computed) and is unused
+      ppn = BlockIO<bf16_t>::load(needW ? phiP + static_cast<int64_t>(li) * P + pc
+                                        : phiQ + static_cast<int64_t>(li) * Q + (Q - 8));
 #pragma unroll
-    for (int t = 0; t < 8; ++t) rn[t] = BlockIO<TX>::load(xa + (pc + t) * Q + qcc);
-  };
-  if (pbeg < pend) load(pbeg);
-  int buf = 0;
-  for (int64_t pb = pbeg; pb < pend; pb += 32) {
-    const int64_t pc = pb + 8 * kg;
-    const bool in = colok && pc < pend;
-    u32x4 r[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const u32x4 w = BlockIO<TX>::widen(rn[t]);
-      r[t] = in ? w : u32x4{0u, 0u, 0u, 0u};
+      for (int t = 0; t < 8; ++t) rn[t] = IO::load(xa + (pc + t) * Q + qcc);
+      return;
     }
-    const u32x4 pp = (pc < pend) ? ppn : u32x4{0u, 0u, 0u, 0u};
-    __builtin_amdgcn_sched_barrier(0);
-    load(pb + 32);  // past pend: clamped, never used
-    __builtin_amdgcn_sched_barrier(0);
-    if (needZ) {
-      __builtin_amdgcn_wave_barrier();  // the previous step's reads of the staging area stay above
+    if (pb + 32 <= pend && !(a == A - 1 && pb + 32 >= P)) {
+      if (needW) ppn = BlockIO<bf16_t>::load(fp);
 #pragma unroll
-      for (int t = 0; t < 8; ++t) *reinterpret_cast<u32x4*>(my + (8 * kg + t) * kTileStride + 8 * li) = r[t];
-      __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
-      f32x4 zacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+      for (int t = 0; t < 8; ++t) rn[t] = IO::load(xp + t * Q);
+    } else if (pb < pend) {
+      const int left = static_cast<int>(pend - pb) - 8 * kg;  // rows of the lane's group that exist
+      if (needW) ppn = BlockIO<bf16_t>::part(fp, left);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-          const u32x4 xr = *reinterpret_cast<const u32x4*>(my + (16 * mt + li) * kTileStride + 32 * ks + 8 * kg);
-          zacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xr),
-                                                              __builtin_bit_cast(bf16x8, bq[ks]), zacc[mt], 0, 0, 0);
-        }
-      // partial Z rows of this wave: D layout row 16 mt + 4 kg + v, column c = li
-      float* zp = zpart[buf][wave];
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) zp[(16 * mt + 4 * kg + v) * 16 + li] = zacc[mt][v];
-      lds_barrier();  // the next rows' loads stay in flight
-      // wave w finishes rows 8 w .. 8 w + 7 of the step: lane -> (row, c < 8)
-      const int row = 8 * wave + lane / 8, c = lane % 8;
-      const int64_t p = pb + row;
-      float z = zpart[buf][0][row * 16 + c];
-#pragma unroll
-      for (int w = 1; w < kZWWaves; ++w) z += zpart[buf][w][row * 16 + c];
-      if (c < sQ && p < pend) Zo[((static_cast<int64_t>(qblk) * A + a) * P + p) * sQ + c] = z;
-      buf ^= 1;
-    }
-    if (needW) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        u32x4 op;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint32_t lo = r[2 * w][c / 2], hi = r[2 * w + 1][c / 2];
-          op[w] = (c % 2 == 0) ? ((lo & 0xffffu) | (hi << 16)) : ((lo >> 16) | (hi & 0xffff0000u));
-        }
-        wacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pp),
-                                                          __builtin_bit_cast(bf16x8, op), wacc[c], 0, 0, 0);
+      for (int t = 0; t < 8; ++t) {
+        const TX* src = t < left ? xp + t * Q : xa + (pend - 1) * Q + qcc;
+        rn[t] = (ncol == 8 || ncol == 0) ? IO::load(src) : IO::part(src, ncol);
+        __builtin_amdgcn_sched_barrier(0);  // (the rows' entry loads all at once need too many registers)
       }
     }
+    xp += 32 * Q;
+    fp += 32;
+  };
+  if (CW > 1 && !on)  // a wave without columns adds zeros
+    for (int g = lane; g < 2 * 512; g += kWave) zpart[g / 512][wave][g % 512] = 0.f;
+  if (CW > 1) __syncthreads();
+  if (on) load(pbeg);
+  int buf = 0;
+  for (int64_t pb = pbeg; pb < pend; pb += 32) {
+    if (on) {
+      u32x4 r[8];
+      const bool in = pb + 8 * kg < pend;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        r[t] = IO::widen(rn[t]);
+        if constexpr (EVEN) {
+          r[t] = (in && ncol > 0) ? r[t] : u32x4{0u, 0u, 0u, 0u};
+        } else {
+#pragma unroll
+          for (int w = 0; w < 4; ++w) r[t][w] &= cmask[w];
+          if (pb + 8 * kg + t >= pend) r[t] = u32x4{0u, 0u, 0u, 0u};
+        }
+      }
+      const u32x4 pp = (!EVEN || in) ? ppn : u32x4{0u, 0u, 0u, 0u};
+      __builtin_amdgcn_sched_barrier(0);
+      load(pb + 32);
+      __builtin_amdgcn_sched_barrier(0);
+      if (needZ) {
+        __builtin_amdgcn_wave_barrier();  // the previous step's reads of the staging area stay above
+#pragma unroll
+        for (int t = 0; t < 8; ++t) *reinterpret_cast<u32x4*>(my + (8 * kg + t) * kTileStride + 8 * li) = r[t];
+        __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
+        f32x4 zacc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            const u32x4 xr = *reinterpret_cast<const u32x4*>(my + (16 * mt + li) * kTileStride + 32 * ks + 8 * kg);
+            zacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xr),
+                                                                __builtin_bit_cast(bf16x8, bq[ks]), zacc[mt], 0, 0, 0);
+          }
+        // D layout: row 16 mt + 4 kg + v, column c = li
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int row = 16 * mt + 4 * kg + v;
+            if constexpr (CW > 1)
+              zpart[buf][wave][row * 16 + li] = zacc[mt][v];
+            else if (li < sQ && pb + row < pend)
+              zout[(pb + row) * sQ + li] = zacc[mt][v];
+          }
+      }
+      if (needW) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          u32x4 op;
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const uint32_t lo = r[2 * w][c / 2], hi = r[2 * w + 1][c / 2];
+            op[w] = (c % 2 == 0) ? ((lo & 0xffffu) | (hi << 16)) : ((lo >> 16) | (hi & 0xffff0000u));
+          }
+          wacc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pp),
+                                                            __builtin_bit_cast(bf16x8, op), wacc[c], 0, 0, 0);
+        }
+      }
+    }
+    if (CW > 1 && needZ) {
+      lds_barrier();  // the next rows' loads stay in flight
+      // the waves of a slab finish 32 / CW rows of the step each, eight at a time: lane -> (row, c < 8)
+      const int first = wave - wave % CW, c = lane % 8;
+#pragma unroll
+      for (int i = 0; i < 4 / CW; ++i) {
+        const int row = (32 / CW) * (wave % CW) + 8 * i + lane / 8;
+        const int64_t p = pb + row;
+        if (c < sQ && p < pend && a_raw < A) {
+          float z = zpart[buf][first][row * 16 + c];
+#pragma unroll
+          for (int w = 1; w < CW; ++w) z += zpart[buf][first + w][row * 16 + c];
+          zout[p * sQ + c] = z;
+        }
+      }
+      buf ^= 1;
+    }
   }
-  if (!needW || !colok) return;
+  if (!needW || !on || ncol == 0) return;
   // W^T accumulators: row cp = 4 kg + v, column qc + c
   float* wout = Wo + (static_cast<int64_t>(pblk) * A + a) * sP * Q;
 #pragma unroll
@@ -300,8 +375,14 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
     const int cp = 4 * kg + v;
     if (cp >= sP) continue;
     float* dst = wout + static_cast<int64_t>(cp) * Q + qc;
-    *reinterpret_cast<f32x4*>(dst) = f32x4{wacc[0][v], wacc[1][v], wacc[2][v], wacc[3][v]};
-    *reinterpret_cast<f32x4*>(dst + 4) = f32x4{wacc[4][v], wacc[5][v], wacc[6][v], wacc[7][v]};
+    if (ncol == 8) {
+      reinterpret_cast<f32x4u*>(dst)[0] = f32x4{wacc[0][v], wacc[1][v], wacc[2][v], wacc[3][v]};
+      reinterpret_cast<f32x4u*>(dst)[1] = f32x4{wacc[4][v], wacc[5][v], wacc[6][v], wacc[7][v]};
+    } else {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (c < ncol) dst[c] = wacc[c][v];
+    }
   }
 }
 
@@ -331,7 +412,6 @@ constexpr int kF32Stride = 68;  // floats per staged row: 64 + 4 padding (rows f
 constexpr int kPhiQRows = 8;
 constexpr int kPhiQStride = kZWColsMfma + 8;     // floats per row: 16-byte rows, rows 8 banks apart
 constexpr int kPhiPWin = 64;                     // rows of PhiP per staged window
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 template <bool NZ, bool NW, bool VEC, int CW>
 __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3))) void sketch_zw_f32_mfma_kernel(
@@ -591,17 +671,16 @@ bool sketch_zw_ok(rt_dtype, int64_t sP, int64_t sQ) { return sP >= 1 && sQ >= 1 
 ZWPlan sketch_zw_plan(rt_dtype xdt, int64_t A, int64_t P, int64_t Q, int64_t sP, int64_t sQ, bool needZ,
                       bool needW) {
   ZWPlan p;
-  const bool mf16 = (xdt == RT_BF16 || xdt == RT_F8E4M3) && (P % 8 == 0) && (Q % 8 == 0) && P >= 32;
   // (below 16 entries a row or 16 rows, most of a step's matrix-core tile would be padding)
-  const bool mf32 = (xdt == RT_F32) && Q >= 16 && P >= 16;
-  p.mfma = mf16 || mf32;
+  p.mfma = xdt != RT_F64 && Q >= 16 && P >= 16;
+  const bool mf32 = xdt == RT_F32;
   const int nq = pick_nq(xdt, Q);
   p.qblocks = p.mfma ? ceil_div(Q, kZWColsMfma) : ceil_div(Q, 64 * nq);
   p.qcols = p.mfma ? kZWColsMfma : 64 * nq;
   p.waves_per_slab = kZWWaves;
-  if (mf32) {
-    // binary32: the column blocks share the 128-column units evenly, and a block of one or two
-    // units leaves waves for further slabs
+  if (p.mfma) {
+    // the column blocks share the 128-column units evenly, and a block of one or two units leaves
+    // waves for further slabs
     const int64_t units = ceil_div(ceil_div(Q, 128), p.qblocks);
     p.qcols = 128 * units;
     p.waves_per_slab = units > 2 ? 4 : static_cast<int>(units);
@@ -673,11 +752,10 @@ hipError_t launch_sketch_zw(const void* X, rt_dtype xdt, int64_t A, int64_t P, i
   hipError_t e;
   const int isP = static_cast<int>(sP), isQ = static_cast<int>(sQ);
   if (plan.mfma) {
-    const int64_t blocks = A * plan.pblocks * plan.qblocks;
+    const int64_t groups = ceil_div(A, kZWWaves / plan.waves_per_slab) * plan.pblocks * plan.qblocks;
+    const unsigned g = static_cast<unsigned>(groups);
     if (xdt == RT_F32) {
       const bool vec = Q % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
-      const int64_t groups = ceil_div(A, kZWWaves / plan.waves_per_slab) * plan.pblocks * plan.qblocks;
-      const unsigned g = static_cast<unsigned>(groups);
 #define RT_ZWF(NZV, NWV, VV, CWV)                                                                                    \
   sketch_zw_f32_mfma_kernel<NZV, NWV, VV, CWV><<<g, kZWThreads, 0, st>>>(                                            \
       static_cast<const float*>(X), A, P, Q, static_cast<const float*>(phiP16), isP, static_cast<const float*>(phiQ16), \
@@ -701,16 +779,30 @@ hipError_t launch_sketch_zw(const void* X, rt_dtype xdt, int64_t A, int64_t P, i
 #undef RT_ZWF_W
 #undef RT_ZWF
     }
-    else if (xdt == RT_F8E4M3)
-      sketch_zw_bf16_mfma_kernel<f8_t><<<static_cast<unsigned>(blocks), kZWThreads, 0, st>>>(
-          static_cast<const f8_t*>(X), A, P, Q, static_cast<const bf16_t*>(phiP16), isP,
-          static_cast<const bf16_t*>(phiQ16), isQ, plan.rows_per_block, static_cast<int>(plan.qblocks),
-          static_cast<int>(plan.pblocks), static_cast<float*>(zdst), static_cast<float*>(wdst));
-    else
-      sketch_zw_bf16_mfma_kernel<bf16_t><<<static_cast<unsigned>(blocks), kZWThreads, 0, st>>>(
-          static_cast<const bf16_t*>(X), A, P, Q, static_cast<const bf16_t*>(phiP16), isP,
-          static_cast<const bf16_t*>(phiQ16), isQ, plan.rows_per_block, static_cast<int>(plan.qblocks),
-          static_cast<int>(plan.pblocks), static_cast<float*>(zdst), static_cast<float*>(wdst));
+    else {
+      const bool even = P % 8 == 0 && Q % 8 == 0;
+#define RT_ZWB(TXV, EV, CWV)                                                                                  \
+  sketch_zw_bf16_mfma_kernel<TXV, EV, CWV><<<g, kZWThreads, 0, st>>>(                                         \
+      static_cast<const TXV*>(X), A, P, Q, static_cast<const bf16_t*>(phiP16), isP,                           \
+      static_cast<const bf16_t*>(phiQ16), isQ, plan.rows_per_block, plan.qcols, static_cast<int>(plan.qblocks), \
+      static_cast<int>(plan.pblocks), static_cast<float*>(zdst), static_cast<float*>(wdst))
+#define RT_ZWB_T(EV, CWV)                              \
+  do {                                                 \
+    if (xdt == RT_F8E4M3) RT_ZWB(f8_t, EV, CWV);       \
+    else RT_ZWB(bf16_t, EV, CWV);                      \
+  } while (0)
+#define RT_ZWB_E(CWV)                 \
+  do {                                \
+    if (even) RT_ZWB_T(true, CWV);    \
+    else RT_ZWB_T(false, CWV);        \
+  } while (0)
+      if (plan.waves_per_slab == 1) RT_ZWB_E(1);
+      else if (plan.waves_per_slab == 2) RT_ZWB_E(2);
+      else RT_ZWB_E(4);
+#undef RT_ZWB_E
+#undef RT_ZWB_T
+#undef RT_ZWB
+    }
     e = hipGetLastError();
   } else
   switch (xdt) {

@@ -112,13 +112,12 @@ hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t 
 // phiP/phiQ: compute type (binary64 for F64 X, else binary32 holding values
 // already rounded to X's dtype), row-major sP x P and sQ x Q.
 // Either output may be skipped (null).  Z/W in the compute type.
-// bfloat16 or FP8 e4m3 X with P, Q multiples of 8, and binary32 X with P, Q >= 16, run on
-// matrix cores (plan.mfma) and also need phiP16 / phiQ16: the factors rounded to X's dtype,
+// binary32, bfloat16 and FP8 e4m3 X with P, Q >= 16 run on matrix cores (plan.mfma) and also need phiP16 / phiQ16: the factors rounded to X's dtype,
 // stored as bfloat16 (exact) or binary32, zero-padded to 16 rows.
 struct ZWPlan {
   int64_t qblocks, pblocks, rows_per_block;
   int64_t qcols;       // columns per block
-  int waves_per_slab;  // waves side by side over a block's columns (binary32 on matrix cores)
+  int waves_per_slab;  // waves side by side over a block's columns (matrix cores)
   size_t ws_bytes;
   bool mfma;
 };

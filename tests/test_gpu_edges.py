@@ -246,3 +246,47 @@ def test_contraction_last_mode_tiles(shape, m, dtype, skew, bad):
     assert np.all(np.abs(got - Xf @ U)[fin] <= (2 * (K + 8) * 2.0 ** -24 * (np.abs(Xf) @ np.abs(U)))[fin])
     if bad:
         assert np.array_equal(got[-1, -1], np.sign(U[-1]) * np.inf)
+
+
+# ------------------------------------------------------------------ 16- and 8-bit sketch pass
+# 128-column waves (1, 2 or 4 a slab, several column blocks), 32-row steps, eight-row and eight-column groups
+# cut anywhere, row splits, rows at any boundary.  The products are exact; binary32 sums as above.
+@pytest.mark.parametrize("dims,sp,sl", [
+    ((5, 16, 16), 3, 2), ((5, 17, 19), 4, 8), ((4, 63, 127), 8, 5), ((7, 65, 128), 3, 3), ((3, 64, 129), 2, 7),
+    ((2, 3, 130, 131), 5, 4), ((6, 80, 255), 4, 4), ((3, 81, 257), 7, 6), ((2, 100, 389), 7, 7),
+    ((1, 700, 513), 3, 8), ((2, 40, 640), 8, 1), ((1, 1100, 66), 5, 5), ((1, 33, 1027), 6, 2), ((2, 96, 512), 4, 4),
+])
+@pytest.mark.parametrize("want", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float8_e4m3fn])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_sketch_pass_narrow_tiles(dims, sp, sl, want, dtype, skew):
+    rng = np.random.default_rng(sum(dims) + sp)
+
+    def draw(shape):  # multiples of 1/8 up to 15/8 are exact in both types
+        return rng.integers(-15, 16, size=shape) / 8.0
+
+    X, fp, fl = draw(dims), draw((sp, dims[-2])), draw((sl, dims[-1]))
+    Xd = _dev(X, torch.float32).to(dtype)
+    if skew:
+        buf = torch.zeros(Xd.numel() + 1, dtype=dtype, device="cuda")
+        buf.view(torch.uint8)[Xd.element_size():] = Xd.reshape(-1).view(torch.uint8)
+        Xd = buf[1:].view(dims)
+    Z, W = rt.rtucker_sketch_pass(Xd, _dev(fp), _dev(fl), want=want)
+    for got, on, ref, mag in ((Z, want[0], X @ fl.T, np.abs(X) @ np.abs(fl).T),
+                              (W, want[1], fp @ X, np.abs(fp) @ np.abs(X))):
+        assert (got is not None) == on
+        if on:
+            assert np.all(np.abs(got.double().cpu().numpy() - ref) <= 1.4e-4 * mag)
+
+
+def test_sketch_pass_bf16_nonfinite_stays_in_its_row_and_column():
+    dims = (3, 40, 77)
+    X = np.ones(dims)
+    X[1, 17, 76] = np.inf
+    Z, W = rt.rtucker_sketch_pass(_dev(X, torch.bfloat16), _dev(np.ones((2, 40))), _dev(np.ones((2, 77))))
+    Z, W = Z.cpu().numpy(), W.cpu().numpy()
+    want_z = np.full((3, 40, 2), 77.0)
+    want_z[1, 17] = np.inf
+    want_w = np.full((3, 2, 77), 40.0)
+    want_w[1, :, 76] = np.inf
+    assert np.array_equal(Z, want_z) and np.array_equal(W, want_w)
