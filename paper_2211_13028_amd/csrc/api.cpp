@@ -807,12 +807,13 @@ int subspace_top(Ctx& c, const double* M, int64_t n, int64_t r, double* V, int32
   void* wv = c.take(ttm_generic_ws(RT_F64, 1, n, r, n));
   void* wh = c.take(mode_contract_ws(RT_F64, n, b, b, 1));
   double* T = static_cast<double*>(c.take(static_cast<size_t>(n) * b * sizeof(double)));
-  QRJob job{Z, 1, n, b, Q, nullptr};
   void* wq = c.take(orth_ws(n, b));
   c.flush();
   if (c.dry) return RT_OK;
-  c.chk(launch_subspace_start(Z, n, b, c.st));
-  c.chk(launch_qr(&job, 1, RT_F64, wq, c.st));
+  // the start is not orthonormalised: the first check comes after kSubCheck - 1 orthonormal
+  // bases, and the first of them spans M times the start either way
+  static_assert(kSubCheck > 1, "the Rayleigh-Ritz step takes an orthonormal Q");
+  c.chk(launch_subspace_start(Q, n, b, c.st));
   const SmallGemmJob ritz{Q, Yv, V, n, b, static_cast<int32_t>(r)};
   int it = 0;
   bool done = false;

@@ -268,30 +268,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void g
     }
 }
 
-// out[i][j] (m x m) = sum over chunks of the upper tiles' partials, (i, j) below the diagonal
-// tile read transposed from tile (j, i); 16 lanes per element, fixed order
+// out[i][j] (m x m) = sum over chunks of the upper tiles' partials, for i, j on or above the
+// diagonal tile; tiles off the diagonal are stored a second time, transposed.  A workgroup sums
+// half a row of a tile: lanes along 32 consecutive columns (256-byte reads), eight groups
+// of chunks, added in a fixed order.  At 300 x 80000, 6.4 us; with one element to 16 lanes, each
+// reading 8 bytes of a chunk, and four times the chunks 145 us.
+constexpr int kGWRCols = 32, kGWRGroups = 8;
 __global__ __launch_bounds__(256) void gram_wide_reduce(const double* __restrict__ part, int nchunks, int tiles1,
                                                         int64_t m, double* __restrict__ out) {
-  const int64_t total = m * m;
-  const int sub = threadIdx.x % 16;
-  const int64_t idx = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) / 16;
-  const bool valid = idx < total;
-  double s = 0.0;
-  if (valid) {
-    int64_t i = idx / m, j = idx - (idx / m) * m;
-    if (i / kMCTile > j / kMCTile) {
-      const int64_t t = i;
-      i = j;
-      j = t;
-    }
-    const int tile = static_cast<int>((i / kMCTile) * tiles1 + (j / kMCTile));
-    const int64_t off = (i % kMCTile) * kMCTile + (j % kMCTile);
-    const int tiles = tiles1 * tiles1;
-    for (int c = sub; c < nchunks; c += 16) s += part[(static_cast<int64_t>(c) * tiles + tile) * kMCTile * kMCTile + off];
+  __shared__ double sS[kGWRGroups][kGWRCols];
+  constexpr int kParts = kMCTile * kMCTile / kGWRCols;  // workgroups a tile
+  int rem = blockIdx.x / kParts, ti = 0;
+  while (rem >= tiles1 - ti) {
+    rem -= tiles1 - ti;
+    ++ti;
   }
+  const int tj = ti + rem;
+  const int sub = blockIdx.x % kParts;
+  const int row = sub / (kMCTile / kGWRCols), col0 = (sub % (kMCTile / kGWRCols)) * kGWRCols;
+  const int64_t i = static_cast<int64_t>(ti) * kMCTile + row, j0 = static_cast<int64_t>(tj) * kMCTile + col0;
+  if (i >= m || j0 >= m) return;
+  const int lane = threadIdx.x % kGWRCols, grp = threadIdx.x / kGWRCols;
+  const int64_t tiles = static_cast<int64_t>(tiles1) * tiles1;
+  const int64_t step = tiles * kMCTile * kMCTile;
+  const double* p = part + (static_cast<int64_t>(ti) * tiles1 + tj) * kMCTile * kMCTile + row * kMCTile + col0 + lane;
+  double s = 0.0;
+  // columns past the matrix are not always written: they are not read
+  if (j0 + lane < m) {
+#pragma unroll 4
+    for (int c = grp; c < nchunks; c += kGWRGroups) s += p[c * step];
+  }
+  sS[grp][lane] = s;
+  __syncthreads();
+  if (grp == 0 && j0 + lane < m) {
 #pragma unroll
-  for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 16);
-  if (valid && sub == 0) out[idx] = s;
+    for (int g = 1; g < kGWRGroups; ++g) s += sS[g][lane];
+    out[i * m + j0 + lane] = s;
+    if (ti != tj) out[(j0 + lane) * m + i] = s;
+  }
 }
 
 // Gram matrix of one binary64 (A, m, B) view per workgroup (m <= 64), batched
@@ -1431,9 +1445,9 @@ WidePlan wide_plan(int64_t A, int64_t m, int64_t B) {
   p.tiles1 = static_cast<int>(ceil_div(m, kMCTile));
   p.upper = p.tiles1 * (p.tiles1 + 1) / 2;
   const int64_t total = A * B;
-  // at most 4096 working workgroups (four rounds of four per CU, none left for a short
-  // fifth), at least 64 t each
-  int64_t want = 4096 / p.upper;
+  // at most 1024 working workgroups (one round of four per CU: 199 us at 300 x 80000;
+  // four rounds 196 us, and four times the partials to write and add), at least 64 t each
+  int64_t want = 1024 / p.upper;
   if (want < 1) want = 1;
   int64_t chunk = ceil_div(total, want);
   if (chunk < kGWT) chunk = kGWT;
@@ -1464,7 +1478,7 @@ hipError_t launch_gram_wide(const float* X, int64_t A, int64_t m, int64_t B, dou
     gram_wide_kernel<kGWTFast><<<nb, kMCThreads, 0, st>>>(X, A, m, B, p.chunk, p.tiles1, p.upper, work, part);
   else
     gram_wide_kernel<kGWRowFast><<<nb, kMCThreads, 0, st>>>(X, A, m, B, p.chunk, p.tiles1, p.upper, work, part);
-  const unsigned g2 = static_cast<unsigned>(ceil_div(m * m * 16, 256));
+  const unsigned g2 = static_cast<unsigned>(p.upper) * (kMCTile * kMCTile / kGWRCols);
   gram_wide_reduce<<<g2, 256, 0, st>>>(static_cast<const double*>(ws), p.nchunks, p.tiles1, m, out);
   return hipGetLastError();
 }
@@ -1579,30 +1593,38 @@ __global__ __launch_bounds__(256) void subspace_start_kernel(double* __restrict_
 }
 
 // out[0] = max_i ||MV[:, i] - theta_i V[:, i]|| / theta_0 (MV, V: n x r row-major), one
-// workgroup: thread c % r sums column c over every (256 / r)-th row, fixed order
-__global__ __launch_bounds__(256) void ritz_residual_kernel(const double* __restrict__ MV,
-                                                            const double* __restrict__ V,
-                                                            const double* __restrict__ theta, int64_t n, int r,
-                                                            double* __restrict__ out) {
-  __shared__ double part[256];
+// workgroup: thread c % r sums column c over every (1024 / r)-th row, the threads below r add
+// their column's groups, in fixed order (at 400 x 24, 6 us; with 256 threads
+// and one of them adding all the groups 16)
+constexpr int kRitzThreads = 1024;
+__global__ __launch_bounds__(kRitzThreads) void ritz_residual_kernel(const double* __restrict__ MV,
+                                                                     const double* __restrict__ V,
+                                                                     const double* __restrict__ theta, int64_t n, int r,
+                                                                     double* __restrict__ out) {
+  __shared__ double part[kRitzThreads];
   const int t = threadIdx.x;
-  const int per = 256 / r;  // row groups
+  const int per = kRitzThreads / r;  // row groups
   double acc = 0.0;
   const int c = t % r, g = t / r;
-  if (g < per)
+  const double th = theta[c];
+  if (g < per) {
+#pragma unroll 4
     for (int64_t i = g; i < n; i += per) {
-      const double d = MV[i * r + c] - theta[c] * V[i * r + c];
+      const double d = MV[i * r + c] - th * V[i * r + c];
       acc = fma(d, d, acc);
     }
-  part[t] = (g < per) ? acc : 0.0;
+  }
+  part[t] = acc;
+  __syncthreads();
+  double s = 0.0;
+  if (t < r)
+    for (int gg = 0; gg < per; ++gg) s += part[gg * r + t];
+  __syncthreads();
+  if (t < r) part[t] = sqrt(s);
   __syncthreads();
   if (t == 0) {
     double worst = 0.0;
-    for (int cc = 0; cc < r; ++cc) {
-      double s = 0.0;
-      for (int gg = 0; gg < per; ++gg) s += part[gg * r + cc];
-      worst = fmax(worst, sqrt(s));
-    }
+    for (int cc = 0; cc < r; ++cc) worst = fmax(worst, part[cc]);
     out[0] = worst / fmax(fabs(theta[0]), 1e-300);
   }
 }
@@ -1634,7 +1656,7 @@ hipError_t launch_subspace_start(double* Q, int64_t n, int b, hipStream_t st) {
 
 hipError_t launch_ritz_residual(const double* MV, const double* V, const double* theta, int64_t n, int r,
                                 double* out, hipStream_t st) {
-  ritz_residual_kernel<<<1, 256, 0, st>>>(MV, V, theta, n, r, out);
+  ritz_residual_kernel<<<1, kRitzThreads, 0, st>>>(MV, V, theta, n, r, out);
   return hipGetLastError();
 }
 

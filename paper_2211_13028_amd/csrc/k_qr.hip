@@ -715,8 +715,7 @@ hipError_t qr_level(std::vector<Mat>& mats, bool launch, Bump& ws, hipStream_t s
 
 // Plans (and, when launch is true, enqueues) the QR of a set of jobs:
 // CholeskyQR2 with a Householder fallback for m >= n, Householder otherwise.
-hipError_t qr_plan(const QRJob* jobs, int count, rt_dtype ydt, bool launch, Bump& ws, hipStream_t st,
-                   double shift = 0.0) {
+hipError_t qr_plan(const QRJob* jobs, int count, rt_dtype ydt, bool launch, Bump& ws, hipStream_t st) {
   std::vector<Mat> hh;
   CJobTable tab;
   int nc = 0;
@@ -741,7 +740,7 @@ hipError_t qr_plan(const QRJob* jobs, int count, rt_dtype ydt, bool launch, Bump
       J.Q1 = static_cast<double*>(ws.take(static_cast<size_t>(M.m) * M.n * sizeof(double)));
       J.flag = static_cast<int32_t*>(ws.take(sizeof(int32_t)));
       J.Q = M.Q; J.Rout = M.R;
-      J.shift1 = J.shift2 = shift;
+      J.shift1 = J.shift2 = 0.0;
       M.flag = J.flag;
       tab.t[nc++] = J;
       if (J.chunks > max_chunks) max_chunks = J.chunks;
@@ -783,21 +782,70 @@ hipError_t launch_qr(const QRJob* jobs, int count, rt_dtype ydt, void* ws, hipSt
   return qr_plan(jobs, count, ydt, true, b, st);
 }
 
+namespace {
+// Shifted Cholesky QR twice, then CholeskyQR2, as one chain of four factorisations: every
+// application of an inverse leaves the partial Gram of its rows where the next factorisation
+// reads them, and one Householder fallback, on Y itself, stands behind all four.  (As two
+// separate factorisations the step read its input twice more, for the second one's Gram, and
+// launched the fallback twice: five launches and 19 us more at 300 x 64.)
+hipError_t orth_plan(const double* Y, int64_t m, int n, double* T, double* Q, bool launch, Bump& ws, hipStream_t st) {
+  // shift factor 11 (m n + n (n + 1)) u of shifted Cholesky QR, applied to trace(G) >= ||Y||_2^2
+  const double shift = 11.0 * (static_cast<double>(m) * n + static_cast<double>(n) * (n + 1)) * 0x1p-53;
+  CJob J;
+  J.Y = Y; J.A = 1; J.m = m; J.B = n; J.n = n;
+  J.chunks = static_cast<int32_t>(ceil_div(m, kGramRows));
+  const size_t area = static_cast<size_t>(J.chunks) * kCols * kCols;  // the partials of one Gram
+  J.part = static_cast<double*>(ws.take(4 * area * sizeof(double)));
+  J.R1 = static_cast<double*>(ws.take(2 * kCols * kCols * sizeof(double)));
+  J.R2 = static_cast<double*>(ws.take(2 * kCols * kCols * sizeof(double)));
+  J.Q1 = T;
+  J.flag = static_cast<int32_t*>(ws.take(sizeof(int32_t)));
+  J.Q = Q; J.Rout = nullptr;
+  J.shift1 = shift; J.shift2 = 0.0;
+  double* T2 = static_cast<double*>(ws.take(static_cast<size_t>(m) * n * sizeof(double)));
+  if (launch) {
+    const dim3 g(static_cast<unsigned>(J.chunks), 1);
+    CJobTable tab;
+    tab.t[0] = J;
+    const CTabVal first{tab};
+    cq_gram_kernel<double><<<g, 256, 0, st>>>(first);
+    cq_chol_kernel<CTabVal, kCols, 512><<<1, 512, 0, st>>>(first, 0);
+    cq_apply_kernel<double><<<g, 256, 0, st>>>(first, 0);  // Y -> T
+    J.Y = T; J.Q1 = T2; J.part += area;
+    tab.t[0] = J;
+    const CTabVal next{tab};
+    cq_chol_kernel<CTabVal, kCols, 512><<<1, 512, 0, st>>>(next, 0);
+    cq_apply_kernel<double><<<g, 256, 0, st>>>(next, 0);  // T -> T2
+    J.Y = T2; J.Q1 = T; J.part += area; J.shift1 = 0.0;
+    tab.t[0] = J;
+    const CTabVal last{tab};
+    cq_chol_kernel<CTabVal, kCols, 512><<<1, 512, 0, st>>>(last, 0);
+    cq_apply_kernel<double><<<g, 256, 0, st>>>(last, 0);  // T2 -> T
+    cq_chol_kernel<CTabVal, kCols, 512><<<1, 512, 0, st>>>(last, 1);
+    cq_apply_kernel<double><<<g, 256, 0, st>>>(last, 1);  // T -> Q
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  Mat M;
+  M.src = Y; M.f64 = true;
+  M.A = 1; M.m = m; M.B = n; M.n = n;
+  M.Q = Q; M.ldq = n; M.qcols = n;
+  M.R = nullptr; M.rrows = n;
+  M.flag = J.flag;
+  std::vector<Mat> hh{M};
+  return qr_level(hh, launch, ws, st);
+}
+}  // namespace
+
 size_t orth_ws(int64_t m, int n) {
-  const QRJob job{nullptr, 1, m, n, nullptr, nullptr};
-  return qr_ws(&job, 1);
+  Bump b{nullptr, 0};
+  (void)orth_plan(nullptr, m, n, nullptr, nullptr, false, b, nullptr);
+  return align256(b.off);
 }
 
 hipError_t launch_orth(const double* Y, int64_t m, int n, double* T, double* Q, void* ws, hipStream_t st) {
-  // shift factor 11 (m n + n (n + 1)) u of shifted Cholesky QR, applied to trace(G) >= ||Y||_2^2
-  const double shift = 11.0 * (static_cast<double>(m) * n + static_cast<double>(n) * (n + 1)) * 0x1p-53;
-  const QRJob pre{Y, 1, m, n, T, nullptr};
   Bump b{static_cast<char*>(ws), 0};
-  hipError_t e = qr_plan(&pre, 1, RT_F64, true, b, st, shift);
-  if (e != hipSuccess) return e;
-  const QRJob fin{T, 1, m, n, Q, nullptr};
-  Bump b2{static_cast<char*>(ws), 0};
-  return qr_plan(&fin, 1, RT_F64, true, b2, st);
+  return orth_plan(Y, m, n, T, Q, true, b, st);
 }
 
 hipError_t launch_qr_grouped(const GQrJob* jobs, int count, rt_dtype ydt, hipStream_t st) {

@@ -144,8 +144,8 @@ size_t qr_ws(const QRJob* jobs, int count);
 hipError_t launch_qr(const QRJob* jobs, int count, rt_dtype ydt, void* ws, hipStream_t st);
 // Orthonormal basis Q (m x n, m >= n) of the columns of a binary64 m x n matrix Y that may
 // be ill-conditioned or numerically rank-deficient (the subspace iteration's M Q): two
-// shifted Cholesky QR passes into T (m x n scratch), then CholeskyQR2 of T (Householder
-// if that breaks down).  ws: orth_ws(m, n) bytes.
+// shifted Cholesky QR passes, then CholeskyQR2 (Householder QR of Y if that breaks down).
+// T: m x n scratch.  ws: orth_ws(m, n) bytes.
 size_t orth_ws(int64_t m, int n);
 hipError_t launch_orth(const double* Y, int64_t m, int n, double* T, double* Q, void* ws, hipStream_t st);
 

@@ -290,3 +290,32 @@ def test_sketch_pass_bf16_nonfinite_stays_in_its_row_and_column():
     want_w = np.full((3, 2, 77), 40.0)
     want_w[1, :, 76] = np.inf
     assert np.array_equal(Z, want_z) and np.array_equal(W, want_w)
+
+
+@pytest.mark.parametrize("dims,skew", [
+    ((65, 7, 5), 0), ((65, 16, 16), 0), ((65, 16, 16), 1), ((127, 9, 10), 0), ((128, 2, 32), 0), ((129, 67, 3), 0),
+    ((192, 64, 3), 0), ((193, 5, 7), 1), ((257, 40, 33), 0), ((70, 1, 1), 0), ((66, 300, 301), 0),
+])
+def test_gram_and_subspace_of_a_long_mode(dims, skew):
+    """Leading eigenvectors of the first mode's Gram matrix, M V = V diag(theta), at the edges of its
+    64-wide tiles, for each of its loads and where M has fewer than 64 eigenvalues above zero.
+
+    The iteration stops at a residual of 1e-12 theta_1; the two sums of M differ by rounding in
+    chunks of at most a few thousand terms, under 1e-12 of its norm, so 2e-12 theta_1 bounds both.
+    """
+    rng = np.random.default_rng(sum(dims))
+    n, rest = dims[0], dims[1] * dims[2]
+    k = min(3, rest)
+    core = np.diag(10.0 * 0.5 ** np.arange(k))
+    left = np.linalg.qr(rng.standard_normal((n, k)))[0]
+    right = np.linalg.qr(rng.standard_normal((rest, k)))[0]
+    X = (left @ core @ right.T + 1e-4 * rng.standard_normal((n, rest))).reshape(dims).astype(np.float32)
+    r = [k, 1, 1]
+    _, Us, _ = rt.rtucker_sthosvd(_dev(X, torch.float32, skew), r)
+    V = Us[0].cpu().numpy()
+    M = X.reshape(n, -1).astype(np.float64)
+    M = M @ M.T
+    theta = np.diag(V.T @ M @ V)
+    np.testing.assert_allclose(V.T @ V, np.eye(k), atol=1e-12)
+    assert np.all(np.linalg.norm(M @ V - V * theta, axis=0) <= 2e-12 * theta[0])
+    np.testing.assert_allclose(theta, np.linalg.eigvalsh(M)[::-1][:k], rtol=0, atol=2e-12 * theta[0])
