@@ -1594,7 +1594,7 @@ __global__ __launch_bounds__(256) void subspace_start_kernel(double* __restrict_
 
 // out[0] = max_i ||MV[:, i] - theta_i V[:, i]|| / theta_0 (MV, V: n x r row-major), one
 // workgroup: thread c % r sums column c over every (1024 / r)-th row, the threads below r add
-// their column's groups, in fixed order (at 400 x 24, 6 us; with 256 threads
+// their column's groups, in fixed order (at 400 x 20, 6 us; with 256 threads
 // and one of them adding all the groups 16)
 constexpr int kRitzThreads = 1024;
 __global__ __launch_bounds__(kRitzThreads) void ritz_residual_kernel(const double* __restrict__ MV,

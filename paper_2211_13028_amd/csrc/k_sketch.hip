@@ -143,7 +143,7 @@ __global__ __launch_bounds__(256) void sum_parts_kernel(const TC* __restrict__ p
 // wholly inside or outside the range, and the loads carry no conditions at all: one past the
 // range reads the last group in it, zeroed when it is taken over (260 us for 1024 x 1024 x 512
 // bfloat16 sketches, 281 with the other form).  (Sizes off the 16-byte grid ran on the
-// vector-ALU pass before: ZW16_FIGURES)
+// vector-ALU pass before: all sketches of a 682 x 960 x 138 bfloat16 tensor 413 us, now 92)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
