@@ -6,19 +6,15 @@
 // in one pass over X.  A slab X[a] (P = I2 rows of Q = I3 contiguous values, Q <= 256)
 // is the unit of work; a 256-thread workgroup takes a run of slabs of one tensor and its
 // four waves take every fourth slab, independently (no barrier after the set-up).
-// A wave walks its slabs in steps of 16 rows:
-//  * lane (li, kg) = (lane % 16, lane / 16) loads rows pb + 4 t + kg (t < 4) at columns
-//    16 g + li (g < NG = ceil(Q / 16)): 16 lanes read 64 consecutive bytes of a row.  The
-//    next step's values are in flight while the current step is multiplied;
+// A wave walks its slabs in steps of 16 rows, whose next values are in flight while the current
+// ones are multiplied:
 //  * W^T accumulates on matrix cores with the loaded values as the B operand
 //    (A = Phi_2[c][p] of the lane's rows), one 16 x 16 tile per 16 columns;
 //  * Z needs the rows as the A operand: the step is staged 64 columns at a time in the
-//    wave's LDS area and read back row-wise; Phi_3 (zero-padded to 16 x 16 NG) sits in
+//    wave's LDS area and read back row-wise; Phi_3, padded with zeros, sits in
 //    LDS for the whole workgroup.
-// Binary32 16x16x4 products for both input types (bfloat16 values widen exactly).
 // (Reading each 16-row block as one flat run, 64 consecutive elements per load, and
-// scattering it into an LDS tile read back for both products measured slower: 0.92 ms
-// against 0.63 ms for the 192-column class of the 512-tensor batch.)
+// scattering it into an LDS tile read back for both products measured slower.)
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -31,12 +27,9 @@ typedef float bf32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBThreads = 256;
 constexpr int kBWaves = kBThreads / kWave;
-constexpr int kStageStride = 84;  // floats per staged row of 64 columns: = 20 mod 64, conflict-free
+constexpr int kStageStride = 84;  // floats per staged row of 64 columns (bfloat16 X): = 20 mod 64, conflict-free
                                   // row-wise reads (lane li reads row li) with at most 2-way
                                   // conflicts on the column-wise stores
-
-// Phi_3 rows in LDS: 16 NG columns (a multiple of 64) + 20, the same residue as the stage
-__host__ __device__ constexpr int phi_stride(int ng) { return 16 * ng + 20; }
 
 template <typename TX>
 __device__ __forceinline__ float widen(TX v);
@@ -45,137 +38,194 @@ __device__ __forceinline__ float widen<float>(float v) { return v; }
 template <>
 __device__ __forceinline__ float widen<bf16_t>(bf16_t v) { return bf16_to_f32(v); }
 
-// two waves per SIMD up to 192 columns; the widest class keeps its registers at one
-template <typename TX, int NG>
-__global__ __launch_bounds__(kBThreads, NG > 12 ? 1 : 2) void zw_batch_kernel(const GZwJob* __restrict__ jobs,
-                                                               const int32_t* __restrict__ blkjob) {
-  constexpr int S = phi_stride(NG);
-  __shared__ float sPhi[16 * S];
-  __shared__ float sStage[kBWaves][16 * kStageStride];
+// binary32 X.  A wave takes the 16 rows of a step 64 columns at a time (a unit): lane (li, kg) holds
+// the rows pb + 4 t + kg (t < 4) at columns 64 j + 4 li .. + 3, one 16-byte load each, at whatever
+// 4-byte boundary the group starts.
+//  * the registers of a unit are refilled with the same columns of the next step as soon as they
+//    are taken over, so a whole step stays in flight without a second set of registers;
+//  * W^T: A = Phi_2 of the unit's rows, B = component c of the groups, which gives the columns
+//    64 j + 4 n + c;
+//  * Z: the unit is staged row-major in the wave's LDS area and read back with lane (row li,
+//    columns 16 kk + 4 kg .. + 3) as A; B = Phi_3.
+// Phi_2 and Phi_3 (at most 8 rows each) are staged once a workgroup, and nothing else is shared:
+// the loop has no barrier.  Rows 8 .. 15 of either operand repeat rows 0 .. 7, and their
+// products are not stored.  Bound: the binary32 matrix cores, busy 53 % of the time, half of that on
+// the padding rows.  512 tensors of 32 .. 192 a mode: 820 us (3.5 TB/s); with 4-byte loads, one
+// per lane, a whole step in two sets of registers, and Phi_2 read from the caches: 1243.
+typedef float bf32x4u __attribute__((ext_vector_type(4), aligned(4)));
+constexpr int kZBRows = 8;         // rows of Phi_2 and Phi_3 at most
+constexpr int kZBMaxP = 256;
+constexpr int kZBStride = 64 + 4;  // floats per staged row: rows four banks apart
+
+template <int NJ>
+__global__ __launch_bounds__(kBThreads) __attribute__((amdgpu_waves_per_eu(NJ == 1 ? 4 : NJ == 2 ? 3 : 2))) void
+zw_batch_f32_kernel(const GZwJob* __restrict__ jobs, const int32_t* __restrict__ blkjob) {
+  constexpr int S = 64 * NJ + 8;  // rows 8 banks apart
+  __shared__ __align__(16) float sStage[kBWaves][16 * kZBStride];
+  __shared__ __align__(16) float sPhiQ[kZBRows * S];
+  __shared__ float sPhiP[kZBMaxP * kZBRows];  // [p][c]
   const GZwJob J = jobs[blkjob[blockIdx.x]];
-  const int64_t P = J.P, Q = J.Q, A = J.A;
+  const int P = static_cast<int>(J.P), Q = static_cast<int>(J.Q);
   const int sP = J.sP, sQ = J.sQ;
-  const bool needZ = J.Z != nullptr, needW = J.W != nullptr;
   const int lane = threadIdx.x % kWave;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int li = lane % 16, kg = lane / 16;
+  const int64_t A = J.A;
   const int64_t local = blockIdx.x - J.blk0;
   const int64_t a_first = local * kBWaves * J.spb + wave;
   const int64_t a_end = (local + 1) * kBWaves * J.spb < A ? (local + 1) * kBWaves * J.spb : A;
-  const int steps = static_cast<int>((P + 15) / 16);
   float* st = sStage[wave];
-  const gptr<const TX> X = global_ptr(static_cast<const TX*>(J.X));
-  const gptr<const float> phiP = global_ptr(J.phiP);
+  const gptr<const float> X = global_ptr(static_cast<const float*>(J.X));
+  const gptr<const float> phiP = global_ptr(J.phiP), phiQ = global_ptr(J.phiQ);
   const gptr<float> Zo = global_ptr(J.Z), Wo = global_ptr(J.W);
 
-  // column offsets and masks of the lane, fixed for the tensor (loads clamp to column Q - 1)
-  uint32_t qoff[NG];
-  bool qok[NG];
+  // Rows past P read row P - 1.  Groups that reach past the row's end read its last group: the
+  // values are `cut` places further on in it when the unit is taken over, which only the last unit has.
+  uint32_t qc[NJ];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const int q = 16 * g + li;
-    qok[g] = q < Q;
-    qoff[g] = static_cast<uint32_t>(q < Q ? q : Q - 1);
+  for (int j = 0; j < NJ; ++j) {
+    const int q = 64 * j + 4 * li;
+    qc[j] = static_cast<uint32_t>(q + 4 <= Q ? q : Q > 4 ? Q - 4 : 0);
   }
-
-  const int pc_lane = li < sP ? li : sP - 1;
-
-  // raw values of the next step (converted and masked when the step is taken over)
-  TX rn[4][NG];
-  float ppn[4];
-  auto load = [&](int64_t a, int64_t pb) {
-    const gptr<const TX> xa = X + a * P * Q;
+  const int q_last = 64 * (NJ - 1) + 4 * li;
+  const int cut = q_last - static_cast<int>(qc[NJ - 1]);
+  bf32x4 rn[NJ][4];
+  auto load = [&](int64_t a, int pb, int j) {
+    const gptr<const float> xa = X + a * P * Q;
+    uint32_t row[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int64_t p = pb + 4 * t + kg;
-      const uint32_t prow = static_cast<uint32_t>((p < P ? p : P - 1) * Q);
-#pragma unroll
-      for (int g = 0; g < NG; ++g) rn[t][g] = xa[prow + qoff[g]];
-      ppn[t] = needW ? phiP[static_cast<int64_t>(pc_lane) * P + (p < P ? p : P - 1)] : 0.f;
+      const int p = pb + 4 * t + kg;
+      row[t] = static_cast<uint32_t>((p < P ? p : P - 1) * Q);
     }
-  };
-  // the wave's first block is in flight while Phi_3 is staged
-  if (a_first < a_end) load(a_first, 0);
-
-  // Phi_3 (sQ x Q) zero-padded to 16 x 16 NG; without Z it is never read
-  for (int idx = threadIdx.x; idx < 16 * S; idx += kBThreads) {
-    const int c = idx / S, q = idx - (idx / S) * S;
-    sPhi[idx] = (needZ && c < sQ && q < Q) ? global_ptr(J.phiQ)[static_cast<int64_t>(c) * Q + q] : 0.f;
-  }
-  __syncthreads();
-  if (a_first >= a_end) return;
-
-  bf32x4 wacc[NG];
+    if (NJ > 1 || Q >= 4) {
 #pragma unroll
-  for (int g = 0; g < NG; ++g) wacc[g] = bf32x4{0.f, 0.f, 0.f, 0.f};
-  int64_t a = a_first;
-  int step = 0;
-  while (true) {
-    const int64_t pb = static_cast<int64_t>(step) * 16;
-    float r[4][NG], pp[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const bool pin = pb + 4 * t + kg < P;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) r[t][g] = (pin && qok[g]) ? widen<TX>(rn[t][g]) : 0.f;
-      pp[t] = (pin && li < sP) ? ppn[t] : 0.f;
-    }
-    // next step: the following row block, or the first block of the wave's next slab
-    const bool last_of_slab = step + 1 == steps;
-    const int64_t a_next = last_of_slab ? a + kBWaves : a;
-    const int step_next = last_of_slab ? 0 : step + 1;
-    if (a_next < a_end) load(a_next, static_cast<int64_t>(step_next) * 16);
-    if (needW) {
+      for (int t = 0; t < 4; ++t) rn[j][t] = *(gptr<const bf32x4u>)(xa + (row[t] + qc[j]));
+    } else {  // rows shorter than a group
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int g = 0; g < NG; ++g) wacc[g] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp[t], r[t][g], wacc[g], 0, 0, 0);
+        for (int c = 0; c < 4; ++c) rn[j][t][c] = xa[row[t] + static_cast<uint32_t>(c < Q ? c : Q - 1)];
     }
-    if (needZ) {
-      // four accumulators in turn: the products of a step do not wait for each other
-      bf32x4 zacc[4];
+  };
+  // the wave's first step is in flight while the operands are staged
+  if (a_first < a_end) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) zacc[u] = bf32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) load(a_first, 0, j);
+  }
+  for (int idx = threadIdx.x; idx < kZBRows * 64 * NJ; idx += kBThreads) {
+    const int c = idx / (64 * NJ), q = idx % (64 * NJ);
+    sPhiQ[c * S + q] = (c < sQ && q < Q) ? phiQ[c * Q + q] : 0.f;
+  }
+  const int prows = (P + 15) / 16 * 16;
+  for (int c = 0; c < kZBRows; ++c)
+    for (int p = threadIdx.x; p < prows; p += kBThreads)
+      sPhiP[p * kZBRows + c] = (c < sP && p < P) ? phiP[c * P + p] : 0.f;
+  __syncthreads();
+  if (a_first >= a_end) return;
+
+  bf32x4 wacc[NJ][4];
 #pragma unroll
-      for (int cb = 0; cb < (NG + 3) / 4; ++cb) {
-        __builtin_amdgcn_wave_barrier();  // the previous block's reads of the stage stay above
+  for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+    for (int c = 0; c < 4; ++c) wacc[j][c] = bf32x4{0.f, 0.f, 0.f, 0.f};
+  int64_t a = a_first;
+  int pb = 0;
+  while (true) {
+    const bool last_of_slab = pb + 16 >= P;
+    const int64_t a_next = last_of_slab ? a + kBWaves : a;
+    const int pb_next = last_of_slab ? 0 : pb + 16;
+    // after the wave's last step the step is loaded again: a condition on the loads would
+    // leave the number in flight open, and the waits would count on none
+    const int64_t a_load = a_next < a_end ? a_next : a;
+    const int pb_load = a_next < a_end ? pb_next : pb;
+    bool pin[4];
+    float pp[4];
 #pragma unroll
-          for (int gg = 0; gg < 4; ++gg)
-            if (4 * cb + gg < NG) st[(4 * t + kg) * kStageStride + 16 * gg + li] = r[t][4 * cb + gg];
-        __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
+    for (int t = 0; t < 4; ++t) {
+      pin[t] = pb + 4 * t + kg < P;
+      pp[t] = sPhiP[(pb + 4 * t + kg) * kZBRows + li % kZBRows];
+    }
+    bf32x4 zacc[2] = {bf32x4{0.f, 0.f, 0.f, 0.f}, bf32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int kb = 0; kb < 16; ++kb) {
-          if (16 * cb + kb >= 4 * NG) break;  // compile-time
-          const float xv = st[li * kStageStride + 4 * kb + kg];
-          const float bq = sPhi[li * S + 64 * cb + 4 * kb + kg];
-          zacc[kb % 4] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, bq, zacc[kb % 4], 0, 0, 0);
+    for (int j = 0; j < NJ; ++j) {
+      // a unit waits for its own loads only: nothing of it moves up into the unit before
+      __builtin_amdgcn_sched_barrier(0);
+      bf32x4 r[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        bf32x4 v = rn[j][t];
+        if (j == NJ - 1) {
+          const bf32x4 u = v;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+#pragma unroll
+            for (int e = 1; c + e < 4; ++e) v[c] = cut == e ? u[c + e] : v[c];
+            v[c] = q_last + c < Q ? v[c] : 0.f;
+          }
         }
-      }
-      const bf32x4 z = (zacc[0] + zacc[1]) + (zacc[2] + zacc[3]);
-      if (li < sQ) {
-        const gptr<float> zo = Zo + (a * P + pb) * sQ + li;
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (pb + 4 * kg + v < P) zo[(4 * kg + v) * sQ] = z[v];
+        for (int c = 0; c < 4; ++c) r[t][c] = pin[t] ? v[c] : 0.f;
+        // the values are formed here: formed after the loads below, they would keep the old
+        // registers live beside the new ones, and the copies at the loop's end would wait for the loads
+        asm volatile("" : "+v"(r[t]));
       }
+      __builtin_amdgcn_sched_barrier(0);
+      load(a_load, pb_load, j);
+      __builtin_amdgcn_wave_barrier();  // the previous unit's reads of the stage stay above
+#pragma unroll
+      for (int t = 0; t < 4; ++t) *reinterpret_cast<bf32x4*>(st + (4 * t + kg) * kZBStride + 4 * li) = r[t];
+      __builtin_amdgcn_wave_barrier();  // cross-lane: stores before the reads below
+      bf32x4 xr[4], bq[4];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        xr[kk] = *reinterpret_cast<const bf32x4*>(st + li * kZBStride + 16 * kk + 4 * kg);
+        bq[kk] = *reinterpret_cast<const bf32x4*>(sPhiQ + (li % kZBRows) * S + 64 * j + 16 * kk + 4 * kg);
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          wacc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp[t], r[t][c], wacc[j][c], 0, 0, 0);
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        if (j == NJ - 1 && 64 * j + 16 * kk >= Q) break;  // uniform
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          zacc[c % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[kk][c], bq[kk][c], zacc[c % 2], 0, 0, 0);
+      }
+    }
+    const bf32x4 z = zacc[0] + zacc[1];
+    if (li < sQ) {
+      const gptr<float> zo = Zo + (a * P + pb) * sQ + li;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (pb + 4 * kg + v < P) zo[(4 * kg + v) * sQ] = z[v];
     }
     if (last_of_slab) {
-      if (needW) {
-        const gptr<float> wo = Wo + a * sP * Q;
+      const gptr<float> wo = Wo + a * sP * Q;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
+      for (int j = 0; j < NJ; ++j) {
+        const int q = 64 * j + 4 * li;
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (4 * kg + v < sP && qok[g]) wo[(4 * kg + v) * Q + 16 * g + li] = wacc[g][v];
-          wacc[g] = bf32x4{0.f, 0.f, 0.f, 0.f};
+        for (int v = 0; v < 4; ++v) {
+          const int cp = 4 * kg + v;
+          if (cp >= sP) continue;
+          if (q + 4 <= Q) {
+            *(gptr<bf32x4u>)(wo + (cp * Q + q)) = bf32x4{wacc[j][0][v], wacc[j][1][v], wacc[j][2][v], wacc[j][3][v]};
+          } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (q + c < Q) wo[cp * Q + q + c] = wacc[j][c][v];
+          }
         }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) wacc[j][c] = bf32x4{0.f, 0.f, 0.f, 0.f};
       }
       a = a_next;
       if (a >= a_end) break;
     }
-    step = step_next;
+    pb = pb_next;
   }
 }
 
@@ -569,17 +619,14 @@ hipError_t launch_zw_batch(const GZwJob* jobs, const int32_t* blkjob, int64_t to
                            hipStream_t st) {
   if (total_blocks == 0) return hipSuccess;
   const unsigned g = static_cast<unsigned>(total_blocks);
-#define RT_ZWB(TX, N) zw_batch_kernel<TX, N><<<g, kBThreads, 0, st>>>(jobs, blkjob)
-#define RT_ZWB_NG(TX)                 \
-  switch (ng) {                       \
-    case 4: RT_ZWB(TX, 4); break;     \
-    case 8: RT_ZWB(TX, 8); break;     \
-    case 12: RT_ZWB(TX, 12); break;   \
-    case 16: RT_ZWB(TX, 16); break;   \
-    default: return hipErrorInvalidValue; \
-  }
   if (xdt == RT_F32) {
-    RT_ZWB_NG(float)
+    switch (ng) {
+      case 4: zw_batch_f32_kernel<1><<<g, kBThreads, 0, st>>>(jobs, blkjob); break;
+      case 8: zw_batch_f32_kernel<2><<<g, kBThreads, 0, st>>>(jobs, blkjob); break;
+      case 12: zw_batch_f32_kernel<3><<<g, kBThreads, 0, st>>>(jobs, blkjob); break;
+      case 16: zw_batch_f32_kernel<4><<<g, kBThreads, 0, st>>>(jobs, blkjob); break;
+      default: return hipErrorInvalidValue;
+    }
   } else if (xdt == RT_BF16) {
     switch (ng) {
       case 4: zw_batch_bf16_kernel<4><<<g, kBThreads, 0, st>>>(jobs, blkjob); break;
@@ -591,8 +638,6 @@ hipError_t launch_zw_batch(const GZwJob* jobs, const int32_t* blkjob, int64_t to
   } else {
     return hipErrorInvalidValue;
   }
-#undef RT_ZWB_NG
-#undef RT_ZWB
   return hipGetLastError();
 }
 
