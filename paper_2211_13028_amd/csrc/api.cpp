@@ -278,6 +278,7 @@ void sketch_impl(Ctx& c, const Ten& X, const double* const* phi, const int64_t* 
       if (std::find(keys.begin(), keys.end(), key) == keys.end()) keys.push_back(key);
     }
     std::vector<F32Contraction> group;
+    std::vector<SplitSum> sums;
     std::vector<NodeKey> generic_keys, last_keys;
     std::vector<void*> last_ws;
     for (const NodeKey& key : keys) {
@@ -313,14 +314,30 @@ void sketch_impl(Ctx& c, const Ten& X, const double* const* phi, const int64_t* 
         const int k = key.second.back();
         const Ten& t = node.at(NodeKey{key.first, std::vector<int>(key.second.begin(), key.second.end() - 1)});
         c.chk(launch_ttm_mfma_last(t.p, RT_F32, t.before(k), t.dims[k], opm[k], s[k],
-                                   static_cast<float*>(const_cast<void*>(node.at(key).p)), last_ws[i], c.st));
+                                   static_cast<float*>(const_cast<void*>(node.at(key).p)), last_ws[i], c.st,
+                                   nullptr, &sums));
       }
-      c.chk(launch_ttm_mfma_f32_group(group.data(), static_cast<int>(group.size()), c.st));
+      c.chk(launch_ttm_mfma_f32_group(group.data(), static_cast<int>(group.size()), sums, c.st));
     }
+    std::vector<GenericContraction> generic;
     for (const NodeKey& key : generic_keys) {
       const int k = key.second.back();
-      const Ten t = node.at(NodeKey{key.first, std::vector<int>(key.second.begin(), key.second.end() - 1)});
-      node[key] = ttm(c, t, k, op[k], s[k]);
+      const Ten& t = node.at(NodeKey{key.first, std::vector<int>(key.second.begin(), key.second.end() - 1)});
+      Ten o;
+      o.dims = t.dims;
+      o.dims[k] = s[k];
+      o.dt = ct;
+      const int64_t Ab = t.before(k), K = t.dims[k], Bb = t.after(k), m = s[k];
+      void* y = c.take(static_cast<size_t>(Ab) * m * Bb * dtype_size(ct));
+      void* w = c.take(ttm_generic_ws(ct, Ab, K, Bb, m));
+      generic.push_back(GenericContraction{t.p, Ab, K, Bb, op[k], m, y, w});
+      o.p = y;
+      node[key] = o;
+    }
+    c.flush();
+    if (!c.dry) {
+      c.chk(launch_ttm_generic_group(generic.data(), static_cast<int>(generic.size()), ct, sums, c.st));
+      c.chk(launch_split_sums(sums, ct, c.st));
     }
   }
   std::vector<Ten> cur(d);
@@ -591,10 +608,11 @@ int plan_sketch(Ctx& c, const rt_tensor* X, const double* const* phi, const int6
   sketch_impl(c, T, phi, s, mask, outs);
   const size_t es = dtype_size(ctype(X->dtype));
   c.flush();
-  for (int n = 0; n < d; ++n) {
-    if (!(mask >> n & 1u)) continue;
-    if (!c.dry) c.chk(launch_unfold(outs[n].Y.p, es, outs[n].A, outs[n].m, outs[n].B, Y[n], c.st));
-  }
+  if (c.dry) return RT_OK;
+  std::vector<UnfoldJob> jobs;
+  for (int n = 0; n < d; ++n)
+    if (mask >> n & 1u) jobs.push_back(UnfoldJob{outs[n].Y.p, Y[n], outs[n].A, outs[n].m, outs[n].B, 0});
+  c.chk(launch_unfold(jobs.data(), static_cast<int>(jobs.size()), es, c.st));
   return RT_OK;
 }
 

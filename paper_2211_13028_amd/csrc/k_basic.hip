@@ -179,16 +179,20 @@ __global__ __launch_bounds__(kThreads) void copy_f64_grouped_kernel(const GCopyJ
     J.dst[t] = static_cast<double>(J.src[t]);
 }
 
+// every unfolding of a call in one launch: job q covers the flat indices [off_q, off_q + A m B)
 template <typename T>
-__global__ __launch_bounds__(kThreads) void unfold_kernel(const T* src, int64_t A, int64_t m, int64_t B, T* dst) {
-  const int64_t total = A * m * B;
+__global__ __launch_bounds__(kThreads) void unfold_kernel(UnfoldTable tab, int64_t total) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
-  for (int64_t t = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; t < total; t += stride) {
-    // t indexes the destination (i, a, b)
-    const int64_t i = t / (A * B);
-    const int64_t rem = t - i * (A * B);
-    const int64_t a = rem / B, b = rem - a * B;
-    dst[t] = src[a * m * B + i * B + b];
+  for (int64_t g = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; g < total; g += stride) {
+    int q = 0;
+    for (int t = 1; t < tab.count; ++t)
+      if (g >= tab.j[t].off) q = t;
+    const UnfoldJob& J = tab.j[q];
+    const int64_t t = g - J.off;  // indexes the destination (i, a, b)
+    const int64_t i = t / (J.A * J.B);
+    const int64_t rem = t - i * (J.A * J.B);
+    const int64_t a = rem / J.B, b = rem - a * J.B;
+    static_cast<T*>(J.dst)[t] = static_cast<const T*>(J.src)[a * J.m * J.B + i * J.B + b];
   }
 }
 
@@ -335,16 +339,21 @@ hipError_t launch_copy_f64_grouped(const GCopyJob* jobs, int count, int64_t max_
   return hipGetLastError();
 }
 
-hipError_t launch_unfold(const void* src, size_t esize, int64_t A, int64_t m, int64_t B, void* dst,
-                         hipStream_t st) {
-  const int64_t n = A * m * B;
-  if (n == 0) return hipSuccess;
+hipError_t launch_unfold(const UnfoldJob* jobs, int count, size_t esize, hipStream_t st) {
+  if (count > kMaxUnfold) return hipErrorInvalidValue;
+  UnfoldTable tab{};
+  int64_t total = 0;
+  for (int i = 0; i < count; ++i) {
+    UnfoldJob& J = tab.j[tab.count++];
+    J = jobs[i];
+    J.off = total;
+    total += J.A * J.m * J.B;
+  }
+  if (total == 0) return hipSuccess;
   if (esize == 8)
-    unfold_kernel<double><<<grid_for(n), kThreads, 0, st>>>(static_cast<const double*>(src), A, m, B,
-                                                            static_cast<double*>(dst));
+    unfold_kernel<double><<<grid_for(total), kThreads, 0, st>>>(tab, total);
   else
-    unfold_kernel<float><<<grid_for(n), kThreads, 0, st>>>(static_cast<const float*>(src), A, m, B,
-                                                           static_cast<float*>(dst));
+    unfold_kernel<float><<<grid_for(total), kThreads, 0, st>>>(tab, total);
   return hipGetLastError();
 }
 

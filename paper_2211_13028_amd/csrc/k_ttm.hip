@@ -70,14 +70,15 @@ __device__ __forceinline__ void generic_accumulate(const TX* __restrict__ xp, in
   }
 }
 
+// one block: columns bx blockDim.x .., rows MT by .., part bz of K
 template <typename TX, typename TC, int MT>
-__global__ __launch_bounds__(kGenThreads) void ttm_generic_kernel(const TX* __restrict__ X, int64_t A, int64_t K,
-                                                                  int64_t B, const TC* __restrict__ M, int64_t m,
-                                                                  int64_t kper, bool mtrans, TC* __restrict__ Y) {
-  __shared__ TC sM[MT][kGenKC];
-  const int64_t col = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t i0 = static_cast<int64_t>(blockIdx.y) * MT;
-  const int64_t kb = static_cast<int64_t>(blockIdx.z) * kper;
+__device__ __forceinline__ void generic_block(const TX* __restrict__ X, int64_t A, int64_t K, int64_t B,
+                                              const TC* __restrict__ M, int64_t m, int64_t kper, bool mtrans,
+                                              TC* __restrict__ Y, int64_t bx, int64_t by, int64_t bz,
+                                              TC (&sM)[MT][kGenKC]) {
+  const int64_t col = bx * blockDim.x + threadIdx.x;
+  const int64_t i0 = by * MT;
+  const int64_t kb = bz * kper;
   const int64_t ke = (kb + kper < K) ? kb + kper : K;
   const bool active = col < A * B;
   const int64_t a = active ? col / B : 0;
@@ -87,11 +88,90 @@ __global__ __launch_bounds__(kGenThreads) void ttm_generic_kernel(const TX* __re
   for (int ii = 0; ii < MT; ++ii) acc[ii] = TC(0);
   generic_accumulate<TX, TC, MT>(X + a * K * B + b, B, M, m, K, i0, kb, ke, mtrans, active, sM, acc);
   if (active) {
-    TC* y = Y + static_cast<int64_t>(blockIdx.z) * A * m * B;
+    TC* y = Y + bz * A * m * B;
 #pragma unroll
     for (int ii = 0; ii < MT; ++ii)
       if (i0 + ii < m) y[a * m * B + (i0 + ii) * B + b] = acc[ii];
   }
+}
+
+template <typename TX, typename TC, int MT>
+__global__ __launch_bounds__(kGenThreads) void ttm_generic_kernel(const TX* __restrict__ X, int64_t A, int64_t K,
+                                                                  int64_t B, const TC* __restrict__ M, int64_t m,
+                                                                  int64_t kper, bool mtrans, TC* __restrict__ Y) {
+  __shared__ TC sM[MT][kGenKC];
+  generic_block<TX, TC, MT>(X, A, K, B, M, m, kper, mtrans, Y, blockIdx.x, blockIdx.y, blockIdx.z, sM);
+}
+
+// Several such contractions with few output columns (one wave a block, four rows of M) in one
+// launch: the blocks of job q start at blk0.  They are bound by their latency, so one after the
+// other they take a launch's time each (the second level of a 701 x 523 x 389 binary32
+// sketch, with its sums: 46 us in six launches, 28 in three).
+constexpr int kGenGroupRows = 4;
+struct GenJob {
+  const void* X;
+  const void* M;
+  void* out;
+  int64_t A, K, B, m, kper, blk0, gx, gy;
+};
+struct GenJobTable {
+  GenJob j[kMaxF32Group];
+  int count;
+};
+template <typename T>
+__global__ __launch_bounds__(kWave) void ttm_generic_group_kernel(GenJobTable tab) {
+  __shared__ T sM[kGenGroupRows][kGenKC];
+  int q = 0;
+  for (int t = 1; t < tab.count; ++t)
+    if (static_cast<int64_t>(blockIdx.x) >= tab.j[t].blk0) q = t;
+  const GenJob& J = tab.j[q];
+  const int64_t local = blockIdx.x - J.blk0;
+  const int64_t bx = local % J.gx, rest = local / J.gx;
+  generic_block<T, T, kGenGroupRows>(static_cast<const T*>(J.X), J.A, J.K, J.B, static_cast<const T*>(J.M), J.m, J.kper,
+                                     false, static_cast<T*>(J.out), bx, rest % J.gy, rest / J.gy, sM);
+}
+
+// Split sums of several jobs in one launch: job q covers the flat indices [off_q, off_q + n_q).
+template <typename T>
+struct SumJob {
+  const T* part;
+  T* Y;
+  int64_t n, off;
+  int ksplit;
+};
+template <typename T>
+struct SumJobTable {
+  SumJob<T> j[kMaxF32Group];
+  int count;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void sum_splits_grouped_kernel(SumJobTable<T> tab, int64_t total) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+  for (int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; g < total; g += stride) {
+    int q = 0;
+    for (int t = 1; t < tab.count; ++t)
+      if (g >= tab.j[t].off) q = t;
+    const SumJob<T>& J = tab.j[q];
+    const int64_t i = g - J.off;
+    T acc = J.part[i];
+    for (int k = 1; k < J.ksplit; ++k) acc += J.part[k * J.n + i];
+    J.Y[i] = acc;
+  }
+}
+template <typename T>
+hipError_t split_sums(const std::vector<SplitSum>& sums, hipStream_t st) {
+  for (size_t i0 = 0; i0 < sums.size(); i0 += kMaxF32Group) {
+    SumJobTable<T> tab{};
+    int64_t total = 0;
+    for (size_t i = i0; i < sums.size() && tab.count < kMaxF32Group; ++i) {
+      tab.j[tab.count++] = SumJob<T>{static_cast<const T*>(sums[i].part), static_cast<T*>(sums[i].Y), sums[i].n, total,
+                                     sums[i].ksplit};
+      total += sums[i].n;
+    }
+    const unsigned g = static_cast<unsigned>(ceil_div(total, 256) > 8192 ? 8192 : ceil_div(total, 256));
+    sum_splits_grouped_kernel<T><<<g, 256, 0, st>>>(tab, total);
+  }
+  return hipGetLastError();
 }
 
 template <typename TC>
@@ -113,12 +193,14 @@ int generic_ksplit(int64_t A, int64_t K, int64_t B) {
   return ks;
 }
 
+// few output columns: one-wave blocks, so that more CUs share the work
+int generic_threads(int64_t A, int64_t B) { return A * B < 32768 ? kWave : kGenThreads; }
+
 template <typename TX, typename TC>
 hipError_t generic_dispatch(const TX* X, int64_t A, int64_t K, int64_t B, const TC* M, int64_t m, TC* Y, TC* ws,
                             hipStream_t st, bool mtrans) {
   const int64_t cols = A * B;
-  // few output columns: one-wave blocks, so that more CUs share the work
-  const int threads = cols < 32768 ? kWave : kGenThreads;
+  const int threads = generic_threads(A, B);
   const unsigned gx = static_cast<unsigned>(ceil_div(cols, threads));
   const int ks = generic_ksplit(A, K, B);
   const int64_t kper = ceil_div(K, ks);
@@ -139,6 +221,28 @@ hipError_t generic_dispatch(const TX* X, int64_t A, int64_t K, int64_t B, const 
   const int64_t n = A * m * B;
   const unsigned g2 = static_cast<unsigned>(ceil_div(n, 256) > 4096 ? 4096 : ceil_div(n, 256));
   generic_sum_kernel<TC><<<g2, 256, 0, st>>>(out, ks, n, Y);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t generic_group(const GenericContraction* c, int count, std::vector<SplitSum>& sums, hipStream_t st) {
+  GenJobTable tab{};
+  int64_t blocks = 0;
+  for (int i = 0; i < count; ++i) {
+    const int ks = generic_ksplit(c[i].A, c[i].K, c[i].B);
+    GenJob& J = tab.j[tab.count++];
+    J.X = c[i].X;
+    J.M = c[i].M;
+    J.out = ks > 1 ? c[i].ws : c[i].Y;
+    J.A = c[i].A; J.K = c[i].K; J.B = c[i].B; J.m = c[i].m;
+    J.kper = ceil_div(J.K, ks);
+    J.blk0 = blocks;
+    J.gx = ceil_div(J.A * J.B, kWave);
+    J.gy = ceil_div(J.m, kGenGroupRows);
+    blocks += J.gx * J.gy * ks;
+    if (ks > 1) sums.push_back(SplitSum{c[i].ws, c[i].Y, J.A * J.m * J.B, ks});
+  }
+  ttm_generic_group_kernel<T><<<static_cast<unsigned>(blocks), kWave, 0, st>>>(tab);
   return hipGetLastError();
 }
 
@@ -568,31 +672,6 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_grouped_kernel(F32J
   ttm_f32_unit<MT, VM>(J.X, J.A, J.K, J.B, J.Mop, J.m, J.chunks, J.ksplit, J.kper, J.out, local);
 }
 
-// Split sums of several jobs in one launch: job q covers the flat indices [off_q, off_q + n_q).
-struct SumJob {
-  const float* part;
-  float* Y;
-  int64_t n, off;
-  int ksplit;
-};
-struct SumJobTable {
-  SumJob j[kMaxF32Group];
-  int count;
-};
-__global__ __launch_bounds__(256) void sum_splits_grouped_kernel(SumJobTable tab, int64_t total) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; g < total; g += stride) {
-    int q = 0;
-    for (int t = 1; t < tab.count; ++t)
-      if (g >= tab.j[t].off) q = t;
-    const SumJob& J = tab.j[q];
-    const int64_t i = g - J.off;
-    float acc = J.part[i];
-    for (int k = 1; k < J.ksplit; ++k) acc += J.part[k * J.n + i];
-    J.Y[i] = acc;
-  }
-}
-
 // Last-mode contraction (B == 1): Y[a, i] = sum_k X[a, k] M[i, k], a GEMM with
 // the long contiguous rows of X as the reduction axis.  A wave owns 64 rows of X
 // (four 16-row MFMA tiles) and reads them with 16-byte loads along k, at whatever boundary the
@@ -930,6 +1009,26 @@ hipError_t launch_ttm_generic(const void* X, rt_dtype xdt, int64_t A, int64_t K,
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_ttm_generic_group(const GenericContraction* c, int count, rt_dtype dt, std::vector<SplitSum>& sums,
+                                    hipStream_t st) {
+  if (dt != RT_F32 && dt != RT_F64) return hipErrorInvalidValue;
+  bool few = count > 1 && count <= kMaxF32Group;
+  for (int i = 0; i < count; ++i)
+    if (c[i].A * c[i].B == 0 || c[i].m == 0 || generic_threads(c[i].A, c[i].B) != kWave) few = false;
+  if (few) return dt == RT_F32 ? generic_group<float>(c, count, sums, st) : generic_group<double>(c, count, sums, st);
+  for (int i = 0; i < count; ++i) {
+    const hipError_t e = launch_ttm_generic(c[i].X, dt, c[i].A, c[i].K, c[i].B, c[i].M, c[i].m, c[i].Y, c[i].ws, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_split_sums(const std::vector<SplitSum>& sums, rt_dtype dt, hipStream_t st) {
+  if (sums.empty()) return hipSuccess;
+  if (dt == RT_F32) return split_sums<float>(sums, st);
+  return dt == RT_F64 ? split_sums<double>(sums, st) : hipErrorInvalidValue;
+}
+
 int64_t ttm_mfma_mpad(int64_t m) { return ceil_div(m, 16) * 16; }
 
 bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
@@ -951,7 +1050,7 @@ size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
 }
 
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop,
-                              int64_t m, float* Y, void* ws, hipStream_t st) {
+                              int64_t m, float* Y, void* ws, hipStream_t st, std::vector<SplitSum>* later) {
   const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
   float* out = (p.ksplit == 1) ? Y : static_cast<float*>(ws);
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
@@ -986,12 +1085,16 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || p.ksplit == 1) return e;
   const int64_t n = A * m * B;
+  if (later) {
+    later->push_back(SplitSum{out, Y, n, p.ksplit});
+    return hipSuccess;
+  }
   const unsigned g2 = static_cast<unsigned>(ceil_div(n, 256) > 8192 ? 8192 : ceil_div(n, 256));
   sum_splits_kernel<float><<<g2, 256, 0, st>>>(out, p.ksplit, n, Y);
   return hipGetLastError();
 }
 
-hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStream_t st) {
+hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, std::vector<SplitSum>& sums, hipStream_t st) {
   if (count <= 0) return hipSuccess;
   // one launch needs one kernel instance: every job with the same tile count and M load, and
   // rows that start on 16-byte boundaries
@@ -1011,15 +1114,14 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStre
   if (!same || count == 1) {
     for (int i = 0; i < count; ++i) {
       const hipError_t e =
-          launch_ttm_mfma_ws(c[i].X, RT_F32, c[i].A, c[i].K, c[i].B, c[i].Mop, c[i].m, c[i].Y, c[i].ws, st);
+          launch_ttm_mfma_ws(c[i].X, RT_F32, c[i].A, c[i].K, c[i].B, c[i].Mop, c[i].m, c[i].Y, c[i].ws, st, &sums);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   }
   F32JobTable tab{};
-  SumJobTable sums{};
   tab.count = count;
-  int64_t units = 0, sum_total = 0;
+  int64_t units = 0;
   for (int i = 0; i < count; ++i) {
     const MfmaPlan p = mfma_plan(RT_F32, c[i].A, c[i].K, c[i].B, c[i].m, kUnitCols);
     F32Job& J = tab.j[i];
@@ -1032,15 +1134,7 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStre
     J.ksplit = p.ksplit;
     J.unit0 = units;
     units += c[i].A * p.chunks * p.ksplit;
-    if (p.ksplit > 1) {
-      SumJob& S = sums.j[sums.count++];
-      S.part = J.out;
-      S.Y = c[i].Y;
-      S.n = c[i].A * c[i].m * c[i].B;
-      S.off = sum_total;
-      S.ksplit = p.ksplit;
-      sum_total += S.n;
-    }
+    if (p.ksplit > 1) sums.push_back(SplitSum{J.out, c[i].Y, c[i].A * c[i].m * c[i].B, p.ksplit});
   }
   const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
 #define RT_LAUNCH_GROUP(MTV)                                                                     \
@@ -1055,10 +1149,6 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStre
     default: RT_LAUNCH_GROUP(4); break;
   }
 #undef RT_LAUNCH_GROUP
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || sums.count == 0) return e;
-  const unsigned g2 = static_cast<unsigned>(ceil_div(sum_total, 256) > 8192 ? 8192 : ceil_div(sum_total, 256));
-  sum_splits_grouped_kernel<<<g2, 256, 0, st>>>(sums, sum_total);
   return hipGetLastError();
 }
 
@@ -1088,7 +1178,7 @@ size_t ttm_mfma_last_ws(int64_t A, int64_t K, int64_t m, bool f64_out) {
 }
 
 hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t K, const void* Mop, int64_t m, float* Y,
-                                void* ws, hipStream_t st, double* Y64) {
+                                void* ws, hipStream_t st, double* Y64, std::vector<SplitSum>* later) {
   const LastPlan p = last_plan(A, K, m);
   float* out = (p.ksplit == 1 && !Y64) ? Y : static_cast<float*>(ws);
   const int64_t units = ceil_div(A, 64) * p.ksplit;
@@ -1113,6 +1203,10 @@ hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || (p.ksplit == 1 && !Y64)) return e;
   const int64_t n = A * m;
+  if (later && !Y64) {
+    later->push_back(SplitSum{out, Y, n, p.ksplit});
+    return hipSuccess;
+  }
   const unsigned g2 = static_cast<unsigned>(ceil_div(n, 256) > 8192 ? 8192 : ceil_div(n, 256));
   if (Y64)
     sum_splits_kernel<double><<<g2, 256, 0, st>>>(out, p.ksplit, n, Y64);

@@ -2,6 +2,8 @@
 // Every launcher enqueues on `st` and returns the launch status.
 #pragma once
 
+#include <vector>
+
 #include "common.hpp"
 
 namespace rt {
@@ -47,9 +49,20 @@ hipError_t launch_prep_batch(const PrepTask* tasks, int count, hipStream_t st);
 hipError_t launch_pack_f32(const float* src, int64_t m, int64_t K, bool trans, int64_t m_pad, float* dst,
                            hipStream_t st);
 
-// dst[i * (A*B) + a*B + b] = src[a*m*B + i*B + b]   (mode-n unfolding of an (A, m, B) view)
-hipError_t launch_unfold(const void* src, size_t esize, int64_t A, int64_t m, int64_t B, void* dst,
-                         hipStream_t st);
+// dst[i * (A*B) + a*B + b] = src[a*m*B + i*B + b]   (mode-n unfolding of an (A, m, B) view),
+// for every mode of a call in one launch; off is the launch's own
+struct UnfoldJob {
+  const void* src;
+  void* dst;
+  int64_t A, m, B;
+  int64_t off;
+};
+constexpr int kMaxUnfold = RT_MAX_D;
+struct UnfoldTable {
+  UnfoldJob j[kMaxUnfold];
+  int count;
+};
+hipError_t launch_unfold(const UnfoldJob* jobs, int count, size_t esize, hipStream_t st);
 
 // Elementwise R = A - B (R may be null) and out[0] = sum (A-B)^2 in binary64, deterministic.
 size_t sq_residual_ws(int64_t n);
@@ -70,6 +83,31 @@ hipError_t launch_ttm_generic(const void* X, rt_dtype xdt, int64_t A, int64_t K,
                               const void* M, int64_t m, void* Y, void* ws, hipStream_t st,
                               bool mtrans = false);
 
+// Sum of the split parts of a contraction, Y[i] = sum_k part[k n + i] in order of k, that a launch
+// below leaves to launch_split_sums: one launch for those of several contractions.
+struct SplitSum {
+  const void* part;
+  void* Y;
+  int64_t n;
+  int ksplit;
+};
+hipError_t launch_split_sums(const std::vector<SplitSum>& sums, rt_dtype dt, hipStream_t st);
+
+// Independent contractions on the generic kernel, binary32 or binary64 all of them (each as
+// launch_ttm_generic): one launch, with the sums of split parts left in `sums`, when every one has few
+// output columns.
+constexpr int kMaxF32Group = 8;  // contractions in one grouped launch
+struct GenericContraction {
+  const void* X;
+  int64_t A, K, B;
+  const void* M;
+  int64_t m;
+  void* Y;
+  void* ws;  // ttm_generic_ws(dt, A, K, B, m) bytes
+};
+hipError_t launch_ttm_generic_group(const GenericContraction* c, int count, rt_dtype dt, std::vector<SplitSum>& sums,
+                                    hipStream_t st);
+
 // MFMA path for X in binary32 or bfloat16 (binary32 accumulation, binary32 output).
 //  Operand Mop prepared by launch_prep_matrix with store = xdt (F32 or BF16),
 //  m_pad = ttm_mfma_mpad(m).  Requires ttm_mfma_ok().
@@ -78,12 +116,12 @@ bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m);
 int64_t ttm_mfma_mpad(int64_t m);
 size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m);
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B,
-                              const void* Mop, int64_t m, float* Y, void* ws, hipStream_t st);
+                              const void* Mop, int64_t m, float* Y, void* ws, hipStream_t st,
+                              std::vector<SplitSum>* later = nullptr);
 
 // Several independent binary32 contractions (X binary32, M packed as above) in one kernel
-// launch plus one launch for their split sums; jobs whose tile count or M alignment differ
+// launch, with the sums of split parts left in `sums`; jobs whose tile count or M alignment differ
 // from the first job's run as separate launches.
-constexpr int kMaxF32Group = 8;
 struct F32Contraction {
   const float* X;
   int64_t A, K, B;
@@ -92,18 +130,18 @@ struct F32Contraction {
   float* Y;
   void* ws;  // ttm_mfma_ws(RT_F32, A, K, B, m) bytes
 };
-hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, hipStream_t st);
+hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, std::vector<SplitSum>& sums, hipStream_t st);
 
 // Matrix-core contraction of the last mode (B == 1): Y[a, i] = sum_k X[a, k] Mop[i, k],
 // X A x K row-major and Mop (packed to ttm_mfma_mpad(m) rows) both binary32 or both bfloat16;
 // K >= 4, m <= 64.
 // With Y64 given, the result is written as binary64 there instead (the binary32 sum of
 // the split parts, widened exactly), and Y is not used; the workspace query then needs
-// f64_out set.
+// f64_out set.  With `later` given, the sum of split parts into Y is left there.
 bool ttm_mfma_last_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t m);
 size_t ttm_mfma_last_ws(int64_t A, int64_t K, int64_t m, bool f64_out = false);
 hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t K, const void* Mop, int64_t m, float* Y,
-                                void* ws, hipStream_t st, double* Y64 = nullptr);
+                                void* ws, hipStream_t st, double* Y64 = nullptr, std::vector<SplitSum>* later = nullptr);
 
 // ------------------------------------------------------------------ k_sketch.hip
 // First level of the sketch dimension tree over X viewed as (A, P, Q):

@@ -352,3 +352,36 @@ def test_batched_sketch_tiles(last, skew):
         X, G, U = X.cpu().numpy().astype(np.float64), G.cpu().numpy(), [u.cpu().numpy() for u in U]
         back = np.einsum("abc,ia,jb,kc->ijk", G, *U)
         assert np.linalg.norm(back - X) <= 1.5e-5 * np.linalg.norm(X), d
+
+
+# ------------------------------------------------------------------ grouped contractions of a sketch
+# Short last modes put the second level of the tree on the generic kernel: its contractions run as one
+# launch when each has fewer than 32768 columns, with the sums of the split ones (K >= 128) in another.
+@pytest.mark.parametrize("dims,s", [
+    ((5, 6, 7), (2, 3, 2)), ((130, 129, 9), (3, 4, 5)), ((300, 17, 19), (7, 2, 3)), ((2, 513, 15), (2, 8, 3)),
+    ((9, 8, 7, 6), (2, 3, 2, 3)), ((140, 3, 130, 5), (3, 2, 4, 3)), ((200, 190, 180), (5, 4, 3)), ((40, 600, 61), (8, 8, 7)),
+])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("keep", [0b1111, 0b0110, 0b0001])
+def test_sketch_second_level_groups(dims, s, dtype, keep):
+    """Every unfolding against numpy; entries and operands are small integers over 8, so the products
+    and, up to order, the binary32 sums are exact to 2^-24 per addition: K terms, K 2^-24 of their sum."""
+    rng = np.random.default_rng(sum(dims))
+    d = len(dims)
+    X = rng.integers(-8, 9, dims) / 8.0
+    phis = [rng.integers(-8, 9, (s[k], dims[k])) / 8.0 for k in range(d)]
+    modes = [n for n in range(d) if keep >> n & 1]
+    Ys = rt.rtucker_sketch(_dev(X, dtype), [_dev(p) for p in phis], list(s), modes)
+    for n in range(d):
+        if n not in modes:
+            assert Ys[n] is None
+            continue
+        want, bound = X, np.abs(X)
+        for k in range(d):
+            if k != n:
+                want = np.moveaxis(np.tensordot(phis[k], want, (1, k)), 0, k)
+                bound = np.moveaxis(np.tensordot(np.abs(phis[k]), bound, (1, k)), 0, k)
+        want, bound = (np.moveaxis(v, n, 0).reshape(dims[n], -1) for v in (want, bound))
+        unit = 2.0 ** -53 if dtype == torch.float64 else 2.0 ** -24
+        got = Ys[n].cpu().double().numpy()
+        assert np.all(np.abs(got - want) <= sum(dims) * unit * bound + 1e-300), (n, np.abs(got - want).max())
