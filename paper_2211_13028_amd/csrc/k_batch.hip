@@ -146,7 +146,9 @@ zw_batch_f32_kernel(const GZwJob* __restrict__ jobs, const int32_t* __restrict__
       pin[t] = pb + 4 * t + kg < P;
       pp[t] = sPhiP[(pb + 4 * t + kg) * kZBRows + li % kZBRows];
     }
-    bf32x4 zacc[2] = {bf32x4{0.f, 0.f, 0.f, 0.f}, bf32x4{0.f, 0.f, 0.f, 0.f}};
+    bf32x4 zacc[4];  // in turn: the products do not wait for each other, and round in shorter chains
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zacc[c] = bf32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       // a unit waits for its own loads only: nothing of it moves up into the unit before
@@ -192,10 +194,10 @@ zw_batch_f32_kernel(const GZwJob* __restrict__ jobs, const int32_t* __restrict__
         if (j == NJ - 1 && 64 * j + 16 * kk >= Q) break;  // uniform
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          zacc[c % 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[kk][c], bq[kk][c], zacc[c % 2], 0, 0, 0);
+          zacc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[kk][c], bq[kk][c], zacc[c], 0, 0, 0);
       }
     }
-    const bf32x4 z = zacc[0] + zacc[1];
+    const bf32x4 z = (zacc[0] + zacc[1]) + (zacc[2] + zacc[3]);
     if (li < sQ) {
       const gptr<float> zo = Zo + (a * P + pb) * sQ + li;
 #pragma unroll

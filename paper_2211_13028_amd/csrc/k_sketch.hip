@@ -400,7 +400,9 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
 //    LDS once per workgroup (read from the caches, the 16 rows of a lane group touched 16
 //    cache lines per load every step).  Partial Z rows are added across the CW waves in LDS
 //    (fixed order).
-// PhiP is staged in LDS 64 rows at a time, the next 64 in flight during the current ones.
+// PhiP is staged in LDS 64 rows at a time, the next 64 in flight during the current ones; W^T is
+// summed over 64 or 16 rows (VEC or not), then over those sums, and Z in eight parts: with one chain
+// each, the rounding errors of the sums were 1.4 times those of the vector-ALU pass.
 // VEC: Q % 4 == 0 and X 16-byte aligned, so a 16-byte group lies in one row and on its
 // boundary.  Otherwise the groups are loaded at whatever 4-byte boundary they start at, run into
 // the next row where the last one is cut by the row's end (masked when it is taken over), and
@@ -412,6 +414,26 @@ constexpr int kF32Stride = 68;  // floats per staged row: 64 + 4 padding (rows f
 constexpr int kPhiQRows = 8;
 constexpr int kPhiQStride = kZWColsMfma + 8;     // floats per row: 16-byte rows, rows 8 banks apart
 constexpr int kPhiPWin = 64;                     // rows of PhiP per staged window
+
+// Rows 8 .. 15 of a W^T product are padding, so the sums of two accumulators fit in one register
+// each: the lower half of the lanes holds rows 0 .. 7 of the first, the upper half those of the
+// second.  add_pair adds both accumulators to such a sum and clears them; split_pair gives them back.
+__device__ __forceinline__ void add_pair(f32x4& sum, f32x4& a, f32x4& b) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[v]), __float_as_uint(b[v]), false, false);
+    sum[v] += __uint_as_float(both[0]);
+    a[v] = 0.f;
+    b[v] = 0.f;
+  }
+}
+__device__ __forceinline__ void split_pair(const f32x4& sum, f32x4& a, f32x4& b) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    a[v] = sum[v];
+    b[v] = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(sum[v]), 0u, false, false)[1]);
+  }
+}
 
 template <bool NZ, bool NW, bool VEC, int CW>
 __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3))) void sketch_zw_f32_mfma_kernel(
@@ -448,6 +470,18 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int c = 0; c < 4; ++c) wacc[j][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // sums of 64 rows each (VEC) or 16 (add_pair)
+  f32x4 wsum[2][2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) wsum[j][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const auto flush_w = [&]() {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) add_pair(wsum[j][h], wacc[j][2 * h], wacc[j][2 * h + 1]);
+  };
 
   // The next step's rows are loaded while the current step is multiplied.  Loads carry no
   // per-lane conditions: a row past pend reads row pend - 1 and a column group past qend the
@@ -547,13 +581,16 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
             for (int c = 0; c < 4; ++c)
               wacc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp, r[t][j][c], wacc[j][c], 0, 0, 0);
         }
+        if (!VEC || step == kPhiPWin / 16 - 1) flush_w();
       }
       if constexpr (NZ) {
-        f32x4 zacc = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 zacc = f32x4{0.f, 0.f, 0.f, 0.f}, zp[4];
         // the 16 x 128 tile in two halves of 64 columns (a 16 x 64 stage per wave)
 #pragma unroll
         for (int kb = 0; kb < 8; ++kb) {
           if (kb % 4 == 0) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) zp[c] = f32x4{0.f, 0.f, 0.f, 0.f};
             __builtin_amdgcn_wave_barrier();  // the previous half's reads of the stage stay above
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -565,7 +602,8 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
           if (li >= kPhiQRows) bq = f32x4{0.f, 0.f, 0.f, 0.f};
           const f32x4 xr = *reinterpret_cast<const f32x4*>(my + li * kF32Stride + 16 * (kb % 4) + 4 * kg);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) zacc = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], zacc, 0, 0, 0);
+          for (int c = 0; c < 4; ++c) zp[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], zp[c], 0, 0, 0);
+          if (kb % 4 == 3) zacc += (zp[0] + zp[1]) + (zp[2] + zp[3]);
         }
         // D layout: row 4 kg + v, column c = li
         if constexpr (CW > 1) {
@@ -605,6 +643,11 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
     }
   }
   if (!NW || !on) return;
+  flush_w();
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) split_pair(wsum[j][h], wacc[j][2 * h], wacc[j][2 * h + 1]);
   float* wout = Wo + (static_cast<int64_t>(pblk) * A + a) * sP * Q;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {

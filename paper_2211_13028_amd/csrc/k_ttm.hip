@@ -721,9 +721,9 @@ struct LastIO<bf16_t> {
 };
 
 template <typename TX, int MT>
-__global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K,
-                                                                     const TX* __restrict__ Mop, int64_t m, int ksplit,
-                                                                     int64_t kper, float* __restrict__ Y) {
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT <= 1 ? 4 : MT == 2 ? 3 : 2))) void
+ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* __restrict__ Mop, int64_t m, int ksplit,
+                     int64_t kper, float* __restrict__ Y) {
   typedef LastIO<TX> IO;
   typedef typename IO::vec_t vec_t;
   constexpr int kBlock = 4 * IO::kPer;  // k a step
@@ -736,11 +736,23 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_last_kernel(const TX* _
   const int r16 = lane % 16, q = lane / 16;
   const int64_t kbeg = ks * kper;
   const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
-  f32x4 acc[MT][4];
+  // binary32: sums of 64 k, added up in `sum` (one chain over a long K rounds more than the parts
+  // that the vector-ALU kernel splits it into: 1.76e-7 against 1.53e-7 of the norm at K = 267)
+  constexpr bool kParts = IO::kMacs > 1;
+  f32x4 acc[MT][4], sum[MT][4];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int at = 0; at < 4; ++at) acc[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int at = 0; at < 4; ++at) acc[mt][at] = sum[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const auto close_part = [&]() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int at = 0; at < 4; ++at) {
+        sum[mt][at] += acc[mt][at];
+        acc[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   // The next step's k are loaded while the current ones are multiplied.  A row past A reads row
   // A - 1 (its products land only in output rows that are not stored); in the range's last step
   // k past kend is zero in both operands.
@@ -783,7 +795,9 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_last_kernel(const TX* _
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int at = 0; at < 4; ++at) acc[mt][at] = IO::mac(mv[mt], xv[at], acc[mt][at], c);
+    if (kParts && (k0 - kbeg) % 64 == 64 - kBlock) close_part();
   }
+  close_part();
   float* y = Y + static_cast<int64_t>(ks) * A * m;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -794,7 +808,7 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_last_kernel(const TX* _
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int64_t i = 16 * mt + 4 * q + v;
-        if (i < m) y[a * m + i] = acc[mt][at][v];
+        if (i < m) y[a * m + i] = sum[mt][at][v];
       }
     }
 }
