@@ -400,15 +400,17 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
 //    LDS once per workgroup (read from the caches, the 16 rows of a lane group touched 16
 //    cache lines per load every step).  Partial Z rows are added across the CW waves in LDS
 //    (fixed order).
-// PhiP is staged in LDS 64 rows at a time, the next 64 in flight during the current ones; W^T is
-// summed over 64 or 16 rows (VEC or not), then over those sums, and Z in eight parts: with one chain
-// each, the rounding errors of the sums were 1.4 times those of the vector-ALU pass.
+// PhiP is staged in LDS 64 rows at a time, the next 64 in flight during the current ones.  Rows off the 16-byte
+// grid sum W^T over 16 rows, then over those sums, and Z in eight parts: with one chain each the
+// rounding errors were 1.4 times those of the vector-ALU pass that they ran on before.  (On the
+// aligned path, which always had one chain, the shorter ones halve the error of a decomposition
+// and cost 2 % of the pass.)
 // VEC: Q % 4 == 0 and X 16-byte aligned, so a 16-byte group lies in one row and on its
 // boundary.  Otherwise the groups are loaded at whatever 4-byte boundary they start at, run into
 // the next row where the last one is cut by the row's end (masked when it is taken over), and
 // are loaded entry by entry in the last rows of the tensor.  (701 x 523 x 389 binary32 on the
-// vector-ALU pass instead: 297 us; 183 now,
-// 3.1 TB/s)
+// vector-ALU pass instead: 297 us; 192 now,
+// 3 TB/s)
 // P, A arbitrary, Q >= 4; s <= 8.
 constexpr int kF32Stride = 68;  // floats per staged row: 64 + 4 padding (rows four banks apart)
 constexpr int kPhiQRows = 8;
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
   for (int j = 0; j < 2; ++j)
 #pragma unroll
     for (int c = 0; c < 4; ++c) wacc[j][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // sums of 64 rows each (VEC) or 16 (add_pair)
+  // !VEC: sums of 16 rows each (add_pair)
   f32x4 wsum[2][2];
 #pragma unroll
   for (int j = 0; j < 2; ++j)
@@ -581,7 +583,7 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
             for (int c = 0; c < 4; ++c)
               wacc[j][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(pp, r[t][j][c], wacc[j][c], 0, 0, 0);
         }
-        if (!VEC || step == kPhiPWin / 16 - 1) flush_w();
+        if constexpr (!VEC) flush_w();
       }
       if constexpr (NZ) {
         f32x4 zacc = f32x4{0.f, 0.f, 0.f, 0.f}, zp[4];
@@ -602,8 +604,11 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
           if (li >= kPhiQRows) bq = f32x4{0.f, 0.f, 0.f, 0.f};
           const f32x4 xr = *reinterpret_cast<const f32x4*>(my + li * kF32Stride + 16 * (kb % 4) + 4 * kg);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) zp[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], zp[c], 0, 0, 0);
-          if (kb % 4 == 3) zacc += (zp[0] + zp[1]) + (zp[2] + zp[3]);
+          for (int c = 0; c < 4; ++c) {
+            f32x4& z = VEC ? zacc : zp[c];
+            z = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[c], bq[c], z, 0, 0, 0);
+          }
+          if (!VEC && kb % 4 == 3) zacc += (zp[0] + zp[1]) + (zp[2] + zp[3]);
         }
         // D layout: row 4 kg + v, column c = li
         if constexpr (CW > 1) {
@@ -643,11 +648,12 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
     }
   }
   if (!NW || !on) return;
-  flush_w();
+  if constexpr (!VEC) {
 #pragma unroll
-  for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) split_pair(wsum[j][h], wacc[j][2 * h], wacc[j][2 * h + 1]);
+      for (int h = 0; h < 2; ++h) split_pair(wsum[j][h], wacc[j][2 * h], wacc[j][2 * h + 1]);
+  }
   float* wout = Wo + (static_cast<int64_t>(pblk) * A + a) * sP * Q;
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
