@@ -8,11 +8,10 @@
 //    thread, m split into register tiles, M chunks broadcast from LDS).
 //  * ttm_split:  matrix-core kernel for binary32 X (B >= 64, m <= 64): three
 //    bfloat16 terms a value, X streamed once, M split and staged in LDS.
-//  * ttm_mfma:   matrix-core kernels for bfloat16 X (B % 8 == 0, m <= 64) and for the
-//    small binary32 contractions of one launch.  Each wave owns a 64 x 128
-//    output tile (m padded to a multiple of 16) and streams X rows once; the
-//    prepared M operand is read from L2.  bfloat16 operands are re-packed in
-//    registers so that each lane holds 8 consecutive k of one column.
+//  * ttm_mfma:   matrix-core kernels for bfloat16 X (B >= 64, m <= 64; M staged in LDS, operands
+//    re-packed in registers so that each lane holds 8 consecutive k of one column) and for the
+//    small binary32 contractions of one launch (the prepared M operand is read from L2).
+//  * ttm_mfma_last: the last mode (B == 1), X in rows of K contiguous values.
 #include <algorithm>
 
 #include "kernels.hpp"
