@@ -1445,9 +1445,13 @@ WidePlan wide_plan(int64_t A, int64_t m, int64_t B) {
   p.tiles1 = static_cast<int>(ceil_div(m, kMCTile));
   p.upper = p.tiles1 * (p.tiles1 + 1) / 2;
   const int64_t total = A * B;
-  // at most 1024 working workgroups (one round of four per CU: 199 us at 300 x 80000;
-  // four rounds 196 us, and four times the partials to write and add), at least 64 t each
-  int64_t want = 1024 / p.upper;
+  // At most 4096 working workgroups (four rounds of four per CU, which even out: 10.3 ms at
+  // 1024 x 524288, 11.1 with one round), at least 64 t each.  Where a workgroup of the four rounds
+  // would take less than 1024 t, the partials cost more than that gains, and one round is used
+  // (300 x 80000: 199 us and 6 for the sum; four rounds 196 and about 19).
+  int64_t want = 4096 / p.upper;
+  if (want < 1) want = 1;
+  if (ceil_div(total, want) < 1024) want = 1024 / p.upper;
   if (want < 1) want = 1;
   int64_t chunk = ceil_div(total, want);
   if (chunk < kGWT) chunk = kGWT;
