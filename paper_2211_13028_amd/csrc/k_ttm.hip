@@ -719,8 +719,8 @@ struct LastIO<bf16_t> {
   static constexpr int kMacs = 1;
 };
 
-template <typename TX, int MT>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT <= 1 ? 4 : MT == 2 ? 3 : 2))) void
+template <typename TX, int MT, bool PARTS>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : MT >= 3 ? 2 : PARTS ? 3 : 4))) void
 ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* __restrict__ Mop, int64_t m, int ksplit,
                      int64_t kper, float* __restrict__ Y) {
   typedef LastIO<TX> IO;
@@ -735,26 +735,26 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
   const int r16 = lane % 16, q = lane / 16;
   const int64_t kbeg = ks * kper;
   const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
-  // binary32: sums of 64 k, added up in `sum` (one chain over a long K rounds more than the parts
-  // that the vector-ALU kernel splits it into: 1.76e-7 against 1.53e-7 of the norm at K = 267)
-  constexpr bool kParts = IO::kMacs > 1;
-  f32x4 acc[MT][4], sum[MT][4];
+  // PARTS: sums of 64 k, added up in `sum`
+  f32x4 acc[MT][4], sum[PARTS ? MT : 1][4];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int at = 0; at < 4; ++at) acc[mt][at] = sum[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int at = 0; at < 4; ++at) acc[mt][at] = sum[PARTS ? mt : 0][at] = f32x4{0.f, 0.f, 0.f, 0.f};
   const auto close_part = [&]() {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int at = 0; at < 4; ++at) {
-        sum[mt][at] += acc[mt][at];
+        sum[PARTS ? mt : 0][at] += acc[mt][at];
         acc[mt][at] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
   };
   // The next step's k are loaded while the current ones are multiplied.  A row past A reads row
   // A - 1 (its products land only in output rows that are not stored); in the range's last step
-  // k past kend is zero in both operands.
+  // k past kend is zero in both operands.  EVEN (binary32 on the 16-byte grid): the loads carry no
+  // conditions, k past kend reads the range's last four and is zeroed when it is taken over.
+  constexpr bool EVEN = !PARTS && IO::kMacs > 1;
   const TX* xr[4];
 #pragma unroll
   for (int at = 0; at < 4; ++at) {
@@ -764,7 +764,13 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
   const TX* mr = Mop + r16 * K + IO::kPer * q;
   vec_t nx[4], nw[MT];
   const auto load = [&](int64_t k0) {
-    if (k0 + kBlock <= kend) {
+    if constexpr (EVEN) {
+      const int64_t kc = (k0 + IO::kPer * q < kend) ? k0 : kend - IO::kPer * (q + 1);
+#pragma unroll
+      for (int at = 0; at < 4; ++at) nx[at] = *reinterpret_cast<const vec_t*>(xr[at] + kc);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) nw[mt] = *reinterpret_cast<const vec_t*>(mr + 16 * mt * K + kc);
+    } else if (k0 + kBlock <= kend) {
 #pragma unroll
       for (int at = 0; at < 4; ++at) nx[at] = *reinterpret_cast<const typename IO::load_t*>(xr[at] + k0);
 #pragma unroll
@@ -785,6 +791,13 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
     for (int at = 0; at < 4; ++at) xv[at] = nx[at];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) mv[mt] = nw[mt];
+    if constexpr (EVEN) {
+      const bool kin = k0 + IO::kPer * q < kend;
+#pragma unroll
+      for (int at = 0; at < 4; ++at) xv[at] = kin ? xv[at] : IO::zero();
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) mv[mt] = kin ? mv[mt] : IO::zero();
+    }
     __builtin_amdgcn_sched_barrier(0);
     load(k0 + kBlock);
     __builtin_amdgcn_sched_barrier(0);
@@ -794,9 +807,9 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int at = 0; at < 4; ++at) acc[mt][at] = IO::mac(mv[mt], xv[at], acc[mt][at], c);
-    if (kParts && (k0 - kbeg) % 64 == 64 - kBlock) close_part();
+    if (PARTS && (k0 - kbeg) % 64 == 64 - kBlock) close_part();
   }
-  close_part();
+  if constexpr (PARTS) close_part();
   float* y = Y + static_cast<int64_t>(ks) * A * m;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
@@ -807,7 +820,7 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int64_t i = 16 * mt + 4 * q + v;
-        if (i < m) y[a * m + i] = sum[mt][at][v];
+        if (i < m) y[a * m + i] = (PARTS ? sum[PARTS ? mt : 0][at] : acc[mt][at])[v];
       }
     }
 }
@@ -1174,37 +1187,44 @@ struct LastPlan {
   int ksplit;
   int64_t kper;
 };
-LastPlan last_plan(int64_t A, int64_t K, int64_t m) {
+LastPlan last_plan(rt_dtype xdt, int64_t A, int64_t K, int64_t m) {
   LastPlan p;
   const int64_t units = ceil_div(A, 64);
   int ks = 1;
   while (units * ks < 2048 && K / (ks * 2) >= 64 && ks < 16 && 2 * ks * A * m * 4 <= A * K * 4) ks *= 2;
   p.ksplit = ks;
-  p.kper = ceil_div(ceil_div(K, ks), 32) * 32;
+  const int64_t step = xdt == RT_F32 ? 16 : 32;  // k a step of the kernel: the parts of K are whole steps
+  p.kper = ceil_div(ceil_div(K, ks), step) * step;
   return p;
 }
 }  // namespace
 
 size_t ttm_mfma_last_ws(int64_t A, int64_t K, int64_t m, bool f64_out) {
-  const LastPlan p = last_plan(A, K, m);
+  const LastPlan p = last_plan(RT_F32, A, K, m);  // (the split is the same for both types)
   return (p.ksplit == 1 && !f64_out) ? 0 : align256(static_cast<size_t>(p.ksplit) * A * m * sizeof(float));
 }
 
 hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t K, const void* Mop, int64_t m, float* Y,
                                 void* ws, hipStream_t st, double* Y64, std::vector<SplitSum>* later) {
-  const LastPlan p = last_plan(A, K, m);
+  const LastPlan p = last_plan(xdt, A, K, m);
   float* out = (p.ksplit == 1 && !Y64) ? Y : static_cast<float*>(ws);
   const int64_t units = ceil_div(A, 64) * p.ksplit;
   const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
-#define RT_LAUNCH_LAST(MTV)                                                                                       \
-  do {                                                                                                            \
-    if (xdt == RT_F32)                                                                                            \
-      ttm_mfma_last_kernel<float, MTV><<<grid, kMfmaThreads, 0, st>>>(                                            \
-          static_cast<const float*>(X), A, K, static_cast<const float*>(Mop), m, p.ksplit, p.kper, out);          \
-    else                                                                                                          \
-      ttm_mfma_last_kernel<bf16_t, MTV><<<grid, kMfmaThreads, 0, st>>>(                                           \
-          static_cast<const bf16_t*>(X), A, K, static_cast<const bf16_t*>(Mop), m, p.ksplit, p.kper, out);        \
+  // Rows off the 16-byte grid are summed in parts of 64 k: one chain over a long K rounds more than the
+  // parts that the vector-ALU kernel they ran on before splits it into (1.76e-7 against 1.53e-7 of the
+  // norm at K = 267; 1.42e-7 in parts).  On the grid, one chain with loads that carry no conditions is
+  // faster for up to two row tiles (112 x 768 x 784 with m = 24: 81 us, 91 in parts), the parts for more
+  // (400 x 500 x 600 with m = 44: 214 us, 225 in one chain; 256 x 256 x 1024 with m = 64: 123 and 128).
+  const bool parts = xdt == RT_F32 && (MT >= 3 || K % 4 != 0 || reinterpret_cast<uintptr_t>(X) % 16 != 0);
+#define RT_LAST(TXV, MTV, PV)                                                                                     \
+  ttm_mfma_last_kernel<TXV, MTV, PV><<<grid, kMfmaThreads, 0, st>>>(                                              \
+      static_cast<const TXV*>(X), A, K, static_cast<const TXV*>(Mop), m, p.ksplit, p.kper, out)
+#define RT_LAUNCH_LAST(MTV)                      \
+  do {                                           \
+    if (xdt != RT_F32) RT_LAST(bf16_t, MTV, false); \
+    else if (parts) RT_LAST(float, MTV, true);   \
+    else RT_LAST(float, (MTV < 3 ? MTV : 2), false); \
   } while (0)
   switch (MT) {
     case 1: RT_LAUNCH_LAST(1); break;
@@ -1213,6 +1233,7 @@ hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t 
     default: RT_LAUNCH_LAST(4); break;
   }
 #undef RT_LAUNCH_LAST
+#undef RT_LAST
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || (p.ksplit == 1 && !Y64)) return e;
   const int64_t n = A * m;
