@@ -35,7 +35,7 @@ struct Ctx {
   size_t cap;
   hipStream_t st;
   hipError_t err = hipSuccess;
-  size_t peak = 0;
+  size_t peak = 0;  // most of the workspace in use at any point: what the plan needs
   std::vector<PrepTask> pending;  // operand roundings not yet launched (one batched launch)
   // phase timing (rtucker_decompose_phases): an event at each phase boundary
   std::vector<hipEvent_t>* marks = nullptr;
@@ -60,7 +60,14 @@ struct Ctx {
     if (bytes == 0) return nullptr;
     const size_t o = align256(off);
     off = o + align256(bytes);
+    if (off > peak) peak = off;
     return dry ? nullptr : base + o;
+  }
+  // Gives back what was taken since `mark` (a value of off): later launches of the plan, which
+  // follow on the same stream, write over it.  Nothing taken since may be read after this.
+  void rewind(size_t mark) {
+    flush();
+    off = mark;
   }
   void chk(hipError_t e) {
     if (err == hipSuccess && e != hipSuccess) err = e;
@@ -126,9 +133,9 @@ Ten ten_of(const rt_tensor* X) {
 }
 
 int check_ws(const Ctx& c, void* ws, size_t ws_bytes) {
-  if (c.off == 0) return RT_OK;
+  if (c.peak == 0) return RT_OK;
   if (!ws || (reinterpret_cast<uintptr_t>(ws) & 255u) != 0) return RT_EWORKSPACE;
-  if (ws_bytes < c.off) return RT_EWORKSPACE;
+  if (ws_bytes < c.peak) return RT_EWORKSPACE;
   return RT_OK;
 }
 
@@ -150,9 +157,11 @@ Ten ttm(Ctx& c, const Ten& T, int k, const void* M, int64_t m, void* dst = nullp
   const int64_t A = T.before(k), K = T.dims[k], B = T.after(k);
   void* y = dst ? dst : c.take(static_cast<size_t>(A) * m * B * dtype_size(out.dt));
   out.p = y;
+  const size_t kept = c.off;
   void* w = c.take(ttm_generic_ws(T.dt, A, K, B, m));
   c.flush();
   if (!c.dry) c.chk(launch_ttm_generic(T.p, T.dt, A, K, B, M, m, y, w, c.st, mtrans));
+  c.rewind(kept);  // the parts of a split contraction are summed
   return out;
 }
 
@@ -297,7 +306,7 @@ void sketch_impl(Ctx& c, const Ten& X, const double* const* phi, const int64_t* 
       o.dims[k] = m;
       o.dt = RT_F32;
       o.p = c.take(static_cast<size_t>(Ab) * m * Bb * sizeof(float));
-      void* w = c.take(last ? ttm_mfma_last_ws(Ab, K, m) : ttm_mfma_ws(RT_F32, Ab, K, Bb, m));
+      void* w = c.take(last ? ttm_mfma_last_ws(Ab, K, m) : ttm_mfma_ws(RT_F32, Ab, K, Bb, m, /*grouped=*/true));
       node[key] = o;
       if (last) {
         last_keys.push_back(key);
@@ -385,21 +394,23 @@ Ten core_impl(Ctx& c, const Ten& X, const double* const* U, const int64_t* l, ui
     // a contraction over the last mode (B = 1) runs on the matrix-core kernel for contiguous rows
     st.last = !st.mfma && st.B == 1 && ttm_mfma_last_ok(cur_dt, st.A, st.K, st.m);
     st.wide = last && f64_out && st.last && !dst;
-    st.y = (last && dst) ? dst
-                         : c.take(static_cast<size_t>(st.A) * st.m * st.B * (st.wide ? sizeof(double) : dtype_size(ct)));
-    if (st.mfma) {
-      st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m));
-      st.w = c.take(ttm_mfma_ws(cur_dt, st.A, st.K, st.B, st.m));
-    } else if (st.last) {
-      st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m));
-      st.w = c.take(ttm_mfma_last_ws(st.A, st.K, st.m, st.wide));
-    } else {
-      st.op = prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt == RT_F64 ? RT_F64 : cur_dt, ct);
-      st.w = c.take(ttm_generic_ws(cur_dt, st.A, st.K, st.B, st.m));
-    }
+    st.op = st.mfma || st.last
+                ? prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m))
+                : prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt == RT_F64 ? RT_F64 : cur_dt, ct);
     steps.push_back(st);
     dims[k] = st.m;
     cur_dt = ct;
+  }
+  // the parts of a split contraction are summed before the next one starts, whose result goes over them
+  for (size_t idx = 0; idx < steps.size(); ++idx) {
+    Step& st = steps[idx];
+    const size_t out = static_cast<size_t>(st.A) * st.m * st.B * (st.wide ? sizeof(double) : dtype_size(ctype(st.in_dt)));
+    st.y = (idx + 1 == steps.size() && dst) ? dst : c.take(out);
+    const size_t kept = c.off;
+    st.w = c.take(st.mfma   ? ttm_mfma_ws(st.in_dt, st.A, st.K, st.B, st.m)
+                  : st.last ? ttm_mfma_last_ws(st.A, st.K, st.m, st.wide)
+                            : ttm_generic_ws(st.in_dt, st.A, st.K, st.B, st.m));
+    c.rewind(kept);
   }
   c.flush();
   Ten cur = X;
@@ -742,6 +753,10 @@ int plan_decompose(Ctx& c, const rt_tensor* X, const rt_tensor* Xs, const int32_
   std::vector<double*> Uhat(d);
   for (int n = 0; n < d; ++n) Uhat[n] = static_cast<double*>(c.take(static_cast<size_t>(I[n]) * cdim[n] * sizeof(double)));
   Ten cur = ten_of(X);
+  // A sketch and its QR leave nothing but U_hat: the core takes their workspace over.  (The two
+  // side by side need up to 2.2 times as much, and rtucker_decompose_noalloc has a fixed size:
+  // 400 x 500 x 450 binary32, ranks 16: 77 MiB, now 22.)
+  const size_t kept = c.off;
   if (algo == RT_RHKRON_NOREUSE) {
     // App. A: every mode's sketch with its own factors, each from one read of X (the
     // first level of a one-mode dimension tree), then one QR launch for all modes and the
@@ -762,6 +777,7 @@ int plan_decompose(Ctx& c, const rt_tensor* X, const rt_tensor* Xs, const int32_
     void* w = c.take(qr_ws(jobs.data(), d));
     c.mark(kPhaseQR);
     if (!c.dry) c.chk(launch_qr(jobs.data(), d, ctype(cur.dt), w, c.st));
+    c.rewind(kept);
     c.mark(kPhaseCore);
     cur = core_impl(c, cur, Uhat.data(), cdim.data(), (1u << d) - 1u, nullptr, /*f64_out=*/true);
   } else if (algo == RT_RHKRON) {
@@ -774,6 +790,7 @@ int plan_decompose(Ctx& c, const rt_tensor* X, const rt_tensor* Xs, const int32_
     void* w = c.take(qr_ws(jobs.data(), d));
     c.mark(kPhaseQR);
     if (!c.dry) c.chk(launch_qr(jobs.data(), d, ctype(Tsk.dt), w, c.st));
+    c.rewind(kept);
     c.mark(kPhaseCore);
     cur = core_impl(c, cur, Uhat.data(), cdim.data(), (1u << d) - 1u, nullptr, /*f64_out=*/true);
   } else {
@@ -783,12 +800,14 @@ int plan_decompose(Ctx& c, const rt_tensor* X, const rt_tensor* Xs, const int32_
       if (phi)
         for (int k = 0; k < d; ++k) phij[k] = (k == j) ? nullptr : phi[j * d + k];
       std::vector<SketchOut> outs;
+      const size_t cores = c.off;  // U_hat and the cores of the steps so far
       c.mark(kPhaseSketch);
       sketch_impl(c, cur, phij.data(), sj.data(), 1u << j, outs);
       QRJob job{outs[j].Y.p, outs[j].A, outs[j].m, outs[j].B, Uhat[j], nullptr};
       void* w = c.take(qr_ws(&job, 1));
       c.mark(kPhaseQR);
       if (!c.dry) c.chk(launch_qr(&job, 1, ctype(cur.dt), w, c.st));
+      c.rewind(cores);
       c.mark(kPhaseCore);
       cur = core_impl(c, cur, Uhat.data(), cdim.data(), 1u << j, nullptr, /*f64_out=*/j == d - 1);
     }
@@ -877,6 +896,7 @@ int plan_sthosvd(Ctx& c, const rt_tensor* X, const int32_t* r, double* G, double
   int status = RT_OK;
   for (int j = 0; j < d; ++j) {
     const int64_t n = cur.dims[j], A = cur.before(j), B = cur.after(j), rj = r[j];
+    const size_t kept = c.off;  // the tensors of the steps so far
     double* M = static_cast<double*>(c.take(static_cast<size_t>(n) * n * sizeof(double)));
     void* mcws = c.take(cur.dt == RT_F64 ? mode_contract_ws(RT_F64, A, n, n, B) : gram_wide_ws(A, n, B));
     c.flush();
@@ -893,6 +913,7 @@ int plan_sthosvd(Ctx& c, const rt_tensor* X, const int32_t* r, double* G, double
       const int sst = subspace_top(c, M, n, rj, V, iters);
       if (sst == RT_ENOTCONVERGED) status = sst;
     }
+    c.rewind(kept);  // the Gram matrix and the eigensolver's buffers are done with
     std::vector<const double*> Us(d, nullptr);
     std::vector<int64_t> l(d, 0);
     Us[j] = V;
@@ -982,7 +1003,9 @@ int plan_multi_ttm(Ctx& c, const rt_tensor* X, const void* const* A, const int64
       out.dims[k] = m[k];
       out.dt = RT_F32;
       out.p = dst ? dst : c.take(static_cast<size_t>(Ab) * m[k] * Bb * es);
+      const size_t kept = c.off;
       void* w = c.take(last ? ttm_mfma_last_ws(Ab, K, m[k]) : ttm_mfma_ws(RT_F32, Ab, K, Bb, m[k]));
+      c.rewind(kept);  // the parts of a split contraction are summed before the next one starts
       if (!c.dry) {
         float* y = static_cast<float*>(const_cast<void*>(out.p));
         c.chk(launch_pack_f32(static_cast<const float*>(M), m[k], K, trans != 0, mp, op, c.st));
@@ -1445,7 +1468,7 @@ int query(F&& plan, size_t* bytes) {
   Ctx dry{true, false, nullptr, 0, 0, nullptr};
   const int st = plan(dry);
   if (st) return st;
-  *bytes = dry.off ? align256(dry.off) : 0;
+  *bytes = align256(dry.peak);
   return RT_OK;
 }
 

@@ -133,7 +133,8 @@ __global__ __launch_bounds__(kWave) void ttm_generic_group_kernel(GenJobTable ta
 // Split sums of several jobs in one launch: job q covers the flat indices [off_q, off_q + n_q).
 template <typename T>
 struct SumJob {
-  const T* part;
+  const T* first;
+  const T* rest;
   T* Y;
   int64_t n, off;
   int ksplit;
@@ -152,8 +153,8 @@ __global__ __launch_bounds__(256) void sum_splits_grouped_kernel(SumJobTable<T> 
       if (g >= tab.j[t].off) q = t;
     const SumJob<T>& J = tab.j[q];
     const int64_t i = g - J.off;
-    T acc = J.part[i];
-    for (int k = 1; k < J.ksplit; ++k) acc += J.part[k * J.n + i];
+    T acc = J.first[i];
+    for (int k = 1; k < J.ksplit; ++k) acc += J.rest[(k - 1) * J.n + i];
     J.Y[i] = acc;
   }
 }
@@ -163,8 +164,8 @@ hipError_t split_sums(const std::vector<SplitSum>& sums, hipStream_t st) {
     SumJobTable<T> tab{};
     int64_t total = 0;
     for (size_t i = i0; i < sums.size() && tab.count < kMaxF32Group; ++i) {
-      tab.j[tab.count++] = SumJob<T>{static_cast<const T*>(sums[i].part), static_cast<T*>(sums[i].Y), sums[i].n, total,
-                                     sums[i].ksplit};
+      tab.j[tab.count++] = SumJob<T>{static_cast<const T*>(sums[i].first), static_cast<const T*>(sums[i].rest),
+                                     static_cast<T*>(sums[i].Y), sums[i].n, total, sums[i].ksplit};
       total += sums[i].n;
     }
     const unsigned g = static_cast<unsigned>(ceil_div(total, 256) > 8192 ? 8192 : ceil_div(total, 256));
@@ -239,7 +240,8 @@ hipError_t generic_group(const GenericContraction* c, int count, std::vector<Spl
     J.gx = ceil_div(J.A * J.B, kWave);
     J.gy = ceil_div(J.m, kGenGroupRows);
     blocks += J.gx * J.gy * ks;
-    if (ks > 1) sums.push_back(SplitSum{c[i].ws, c[i].Y, J.A * J.m * J.B, ks});
+    const int64_t n = J.A * J.m * J.B;
+    if (ks > 1) sums.push_back(SplitSum{c[i].ws, static_cast<const T*>(c[i].ws) + n, c[i].Y, n, ks});
   }
   ttm_generic_group_kernel<T><<<static_cast<unsigned>(blocks), kWave, 0, st>>>(tab);
   return hipGetLastError();
@@ -302,6 +304,12 @@ typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));  // at 
 constexpr int kMfmaThreads = 256;  // 4 waves, one 128-column unit each
 constexpr int kUnitCols = 128;
 
+// Where part ks of a contraction of n results goes: the first one into the result itself, the others
+// behind one another (so a contraction in two parts needs the space of one).
+__device__ __forceinline__ float* part_of(float* Y, float* rest, int64_t ks, int64_t n) {
+  return ks == 0 ? Y : rest + (ks - 1) * n;
+}
+
 // Work unit = (a, 128-column chunk, k-split part).  Y (or a split-K partial) is
 // written for rows i < m only.
 // One work unit (a wave) of the binary32 contraction; unit < A * chunks * ksplit.
@@ -309,7 +317,7 @@ constexpr int kUnitCols = 128;
 template <int MT, bool VM>
 __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_t A, int64_t K, int64_t B,
                                              const float* __restrict__ Mop, int64_t m, int64_t chunks, int ksplit,
-                                             int64_t kper, float* __restrict__ Y, int64_t unit) {
+                                             int64_t kper, float* __restrict__ Y, float* __restrict__ rest, int64_t unit) {
   const int lane = threadIdx.x % kWave;
   const int ks = static_cast<int>(unit % ksplit);
   const int64_t ac = unit / ksplit;
@@ -408,7 +416,7 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
           if (kb < kend) block(kb, Pc);
         },
         sets);
-  float* ya = Y + (static_cast<int64_t>(ks) * A + a) * m * B;
+  float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
@@ -477,7 +485,7 @@ __device__ __forceinline__ void split3(float x0, float x1, uint32_t& h, uint32_t
 template <int MT, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ttm_split_f32_kernel(
     const float* __restrict__ X, int64_t A, int64_t K, int64_t B, const float* __restrict__ Mop, int64_t m,
-    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y) {
+    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y, float* __restrict__ rest) {
   __shared__ __align__(16) uint16_t sM[2][3][16 * MT * kSplitStride];
   __shared__ int odd;  // M has entries that its terms cannot hold
   const int tid = threadIdx.x, lane = tid % kWave;
@@ -636,7 +644,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     }
   }
   if (col_raw >= B) return;
-  float* ya = Y + (ks * A + a) * m * B + col;
+  float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B + col;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -651,7 +659,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
 struct F32Job {
   const float* X;
   const float* Mop;
-  float* out;
+  float* Y;
+  float* rest;
   int64_t A, K, B, m, chunks, kper, unit0;
   int ksplit;
 };
@@ -668,7 +677,7 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_grouped_kernel(F32J
   const F32Job& J = tab.j[q];
   const int64_t local = unit - J.unit0;
   if (local >= J.A * J.chunks * J.ksplit) return;
-  ttm_f32_unit<MT, VM>(J.X, J.A, J.K, J.B, J.Mop, J.m, J.chunks, J.ksplit, J.kper, J.out, local);
+  ttm_f32_unit<MT, VM>(J.X, J.A, J.K, J.B, J.Mop, J.m, J.chunks, J.ksplit, J.kper, J.Y, J.rest, local);
 }
 
 // Last-mode contraction (B == 1): Y[a, i] = sum_k X[a, k] M[i, k], a GEMM with
@@ -838,7 +847,7 @@ __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a 
 template <int MT, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_bf16_kernel(
     const bf16_t* __restrict__ X, int64_t A, int64_t K, int64_t B, const bf16_t* __restrict__ Mop, int64_t m,
-    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y) {
+    int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y, float* __restrict__ rest) {
   __shared__ __align__(16) uint16_t sM[2][16 * MT * kSplitStride];
   const int tid = threadIdx.x, lane = tid % kWave;
   const int j = lane % 16, q = lane / 16;
@@ -949,7 +958,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     }
   }
   if (!active || col_raw >= B) return;
-  float* ya = Y + (ks * A + a) * m * B + col;
+  float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B + col;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -964,12 +973,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
 
 // Y = sum of the split parts in part order (binary32), stored as TO
 template <typename TO>
-__global__ __launch_bounds__(256) void sum_splits_kernel(const float* __restrict__ part, int ksplit, int64_t n,
-                                                         TO* __restrict__ Y) {
+__global__ __launch_bounds__(256) void sum_splits_kernel(const float* first, const float* __restrict__ rest, int ksplit,
+                                                         int64_t n, TO* Y) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < n; i += stride) {
-    float s = part[i];
-    for (int k = 1; k < ksplit; ++k) s += part[k * n + i];
+    float s = first[i];
+    for (int k = 1; k < ksplit; ++k) s += rest[(k - 1) * n + i];
     Y[i] = static_cast<TO>(s);
   }
 }
@@ -1067,18 +1076,19 @@ bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
   return false;
 }
 
-size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m) {
-  // (a binary32 contraction may run alone or in a group, whose plans differ)
-  int ks = mfma_plan(xdt, A, K, B, m, kUnitCols).ksplit;
-  if (xdt == RT_F32) ks = std::max(ks, mfma_plan(xdt, A, K, B, m, kSplitCols).ksplit);
+size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m, bool grouped) {
+  // (a binary32 contraction that leaves a group and runs alone has as many units or more, and so
+  // as many parts or fewer)
+  const int64_t unit_cols = (xdt == RT_F32 && !grouped) ? kSplitCols : kUnitCols;
+  const int ks = mfma_plan(xdt, A, K, B, m, unit_cols).ksplit;
   if (ks == 1) return 0;
-  return align256(static_cast<size_t>(ks) * A * m * B * sizeof(float));
+  return align256(static_cast<size_t>(ks - 1) * A * m * B * sizeof(float));
 }
 
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop,
                               int64_t m, float* Y, void* ws, hipStream_t st, std::vector<SplitSum>* later) {
   const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
-  float* out = (p.ksplit == 1) ? Y : static_cast<float*>(ws);
+  float* rest = static_cast<float*>(ws);
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
   // The waves of a workgroup share the k range.  Binary32: eight waves a workgroup when each has a
   // long range of k: they read 2 KB of a row together
@@ -1092,7 +1102,7 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
   const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
 #define RT_TTM(KERNEL, TX, MTV, NTV)                                                                      \
   KERNEL<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const TX*>(X), A, K, B, static_cast<const TX*>(Mop), \
-                                         m, p.chunks, groups, p.kper, out)
+                                         m, p.chunks, groups, p.kper, Y, rest)
 #define RT_TTM_ANY(MTV)                                          \
   do {                                                           \
     if (xdt == RT_BF16 && wide) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 512); \
@@ -1112,11 +1122,11 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
   if (e != hipSuccess || p.ksplit == 1) return e;
   const int64_t n = A * m * B;
   if (later) {
-    later->push_back(SplitSum{out, Y, n, p.ksplit});
+    later->push_back(SplitSum{Y, rest, Y, n, p.ksplit});
     return hipSuccess;
   }
   const unsigned g2 = static_cast<unsigned>(ceil_div(n, 256) > 8192 ? 8192 : ceil_div(n, 256));
-  sum_splits_kernel<float><<<g2, 256, 0, st>>>(out, p.ksplit, n, Y);
+  sum_splits_kernel<float><<<g2, 256, 0, st>>>(Y, rest, p.ksplit, n, Y);
   return hipGetLastError();
 }
 
@@ -1153,14 +1163,15 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, std::ve
     F32Job& J = tab.j[i];
     J.X = c[i].X;
     J.Mop = c[i].Mop;
-    J.out = (p.ksplit == 1) ? c[i].Y : static_cast<float*>(c[i].ws);
+    J.Y = c[i].Y;
+    J.rest = static_cast<float*>(c[i].ws);
     J.A = c[i].A; J.K = c[i].K; J.B = c[i].B; J.m = c[i].m;
     J.chunks = p.chunks;
     J.kper = p.kper;
     J.ksplit = p.ksplit;
     J.unit0 = units;
     units += c[i].A * p.chunks * p.ksplit;
-    if (p.ksplit > 1) sums.push_back(SplitSum{J.out, c[i].Y, c[i].A * c[i].m * c[i].B, p.ksplit});
+    if (p.ksplit > 1) sums.push_back(SplitSum{J.Y, J.rest, J.Y, c[i].A * c[i].m * c[i].B, p.ksplit});
   }
   const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
 #define RT_LAUNCH_GROUP(MTV)                                                                     \
@@ -1238,14 +1249,14 @@ hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t 
   if (e != hipSuccess || (p.ksplit == 1 && !Y64)) return e;
   const int64_t n = A * m;
   if (later && !Y64) {
-    later->push_back(SplitSum{out, Y, n, p.ksplit});
+    later->push_back(SplitSum{out, out + n, Y, n, p.ksplit});
     return hipSuccess;
   }
   const unsigned g2 = static_cast<unsigned>(ceil_div(n, 256) > 8192 ? 8192 : ceil_div(n, 256));
   if (Y64)
-    sum_splits_kernel<double><<<g2, 256, 0, st>>>(out, p.ksplit, n, Y64);
+    sum_splits_kernel<double><<<g2, 256, 0, st>>>(out, out + n, p.ksplit, n, Y64);
   else
-    sum_splits_kernel<float><<<g2, 256, 0, st>>>(out, p.ksplit, n, Y);
+    sum_splits_kernel<float><<<g2, 256, 0, st>>>(out, out + n, p.ksplit, n, Y);
   return hipGetLastError();
 }
 

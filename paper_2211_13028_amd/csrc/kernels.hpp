@@ -83,10 +83,12 @@ hipError_t launch_ttm_generic(const void* X, rt_dtype xdt, int64_t A, int64_t K,
                               const void* M, int64_t m, void* Y, void* ws, hipStream_t st,
                               bool mtrans = false);
 
-// Sum of the split parts of a contraction, Y[i] = sum_k part[k n + i] in order of k, that a launch
-// below leaves to launch_split_sums: one launch for those of several contractions.
+// Sum of the split parts of a contraction, Y[i] = first[i] + sum_k rest[k n + i] in order of k, that a
+// launch below leaves to launch_split_sums: one launch for those of several contractions.  (first
+// may be Y.)
 struct SplitSum {
-  const void* part;
+  const void* first;
+  const void* rest;
   void* Y;
   int64_t n;
   int ksplit;
@@ -114,7 +116,8 @@ hipError_t launch_ttm_generic_group(const GenericContraction* c, int count, rt_d
 //  Split-K partial sums use `ws` (ttm_mfma_ws bytes) when the output is too small to fill the chip.
 bool ttm_mfma_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m);
 int64_t ttm_mfma_mpad(int64_t m);
-size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m);
+// (grouped: for launch_ttm_mfma_f32_group, whose units are wider and take more parts of K)
+size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m, bool grouped = false);
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B,
                               const void* Mop, int64_t m, float* Y, void* ws, hipStream_t st,
                               std::vector<SplitSum>* later = nullptr);
@@ -128,7 +131,7 @@ struct F32Contraction {
   const float* Mop;
   int64_t m;
   float* Y;
-  void* ws;  // ttm_mfma_ws(RT_F32, A, K, B, m) bytes
+  void* ws;  // ttm_mfma_ws(RT_F32, A, K, B, m, true) bytes
 };
 hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, std::vector<SplitSum>& sums, hipStream_t st);
 
