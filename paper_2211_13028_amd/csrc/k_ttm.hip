@@ -496,7 +496,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
   const int64_t unit = active ? unit_raw : 0;
   const int64_t a = unit / chunks;
   const int64_t col_raw = (unit - a * chunks) * kSplitCols + 4 * j;
-  // a lane whose columns run past B takes the last four: its results repeat its neighbour's
+  // A lane whose columns run past B takes the last four.  It stores only those from col_raw on:
+  // the others are its neighbour's, in another wave where a chunk begins, and a wave that takes its
+  // columns once more (see the end) rounds them differently.
   const int64_t col = col_raw + 4 <= B ? col_raw : B - 4;
   const int64_t kbeg = ks * kper;
   const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
@@ -645,12 +647,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
   }
   if (col_raw >= B) return;
   float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B + col;
+  const int skip = static_cast<int>(col_raw - col);  // columns that the lane before stores
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int64_t i = 16 * mt + 4 * q + v;
-      if (i < m) *reinterpret_cast<f32x4u*>(ya + i * B) = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
+      if (i >= m) continue;
+      float* y = ya + i * B;
+      if (skip == 0) {
+        *reinterpret_cast<f32x4u*>(y) = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
+      } else {
+#pragma unroll
+        for (int c = 1; c < 4; ++c)
+          if (c >= skip) y[c] = acc[mt][c][v];
+      }
     }
 }
 
