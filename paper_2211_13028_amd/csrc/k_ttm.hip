@@ -297,6 +297,7 @@ __global__ __launch_bounds__(kWave) void ttm_grouped_kernel(const GTtmJob* __res
 
 // ------------------------------------------------------------------ MFMA
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));  // at any bfloat16 boundary
@@ -428,7 +429,7 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
         const int64_t c = b0 + 64 * g + 4 * j;
         if (c < B) {
           f32x4 o = f32x4{acc[mt][g][0][v], acc[mt][g][1][v], acc[mt][g][2][v], acc[mt][g][3][v]};
-          *reinterpret_cast<f32x4*>(ya + i * B + c) = o;
+          *reinterpret_cast<f32x4u*>(ya + i * B + c) = o;
         }
       }
     }
@@ -452,20 +453,19 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 // range; M is split while it is staged in LDS, 64 k at a time, double-buffered.
 //
 // Bound: HBM (1024 x 1024 x 512 with m = 49: 0.165 ms of matrix-core time at peak against 0.36 ms
-// of reading at 6.3 TB/s); the binary32 products before were bound by the matrix cores.
-// First contraction of the 1024 x 1024 x 512 decomposition: 518 -> 430 us (5.2 TB/s); of 512 x 768
-// x 640 with m = 36: 340 -> 222; of 128^4 with m = 27: 271 -> 245.
+// of reading at 6.3 TB/s); the binary32 products before were bound by the matrix cores.  One after
+// the other, 1024 x 1024 x 512 with m = 49: 540 -> 480 us; 512 x 768 x 640 with m = 36 340 -> 212;
+// 128^4 with m = 27 280 -> 257.
 //
-// X is scaled by 2^32 before it is split, so that all terms of the smallest subnormal are normal
-// bfloat16 values, and the results are scaled back.  What the terms cannot hold goes to binary32
-// products, per wave and after the loop: results that are not finite (an infinity splits into
-// NaN; so does what overflows in the scaling or the sums), and an M with nonzero entries outside
-// [2^-100, 2^20].
-constexpr float kSplitUp = 0x1p32f, kSplitDown = 0x1p-32f;
+// X and M are scaled by 2^24 before they are split, so that all terms of the smallest subnormal are
+// normal bfloat16 values, and the results are scaled back.  What that cannot hold (an infinity, which
+// splits into NaN; values above 2^104, results above 2^80) gives a result that is not finite, and the
+// wave then takes its columns once more, with binary32 products: one infinity in X of 1024 x 1024 x
+// 512 costs 35 us, one in every 195 rows of it, in every wave, 540.
+constexpr float kSplitUp = 0x1p24f, kSplitDown = 0x1p-48f;
 constexpr int kSplitCols = 64;
 constexpr int kSplitWin = 64;                // k of M per staged window
 constexpr int kSplitStride = kSplitWin + 8;  // bfloat16 per staged row: 16-byte groups, rows 36 banks apart
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -487,9 +487,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     const float* __restrict__ X, int64_t A, int64_t K, int64_t B, const float* __restrict__ Mop, int64_t m,
     int64_t chunks, int64_t groups, int64_t kper, float* __restrict__ Y, float* __restrict__ rest) {
   __shared__ __align__(16) uint16_t sM[2][3][16 * MT * kSplitStride];
-  __shared__ int odd;  // M has entries that its terms cannot hold
   const int tid = threadIdx.x, lane = tid % kWave;
   const int j = lane % 16, q = lane / 16;
+  int je = j, qe = q;
   const int64_t ks = blockIdx.x / groups;
   const int64_t unit_raw = (blockIdx.x - ks * groups) * (NT / kWave) + tid / kWave;
   const bool active = unit_raw < A * chunks;
@@ -531,9 +531,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
   // staging: group g = NT i + tid of a window is row g / 16, k = kw + 4 (g % 16) ..
   constexpr int kGroups = 16 * MT * (kSplitWin / 4), kPer = (kGroups + NT - 1) / NT;
   f32x4 sv[kPer];
-  const auto group_of = [&](int g, int64_t kw) {
-    const int64_t k = kw + 4 * (g % 16);
-    const float* src = Mop + static_cast<int64_t>(g / 16) * K + k;
+  const auto group_at = [&](int row, int64_t k) {  // zero past the range
+    const float* src = Mop + static_cast<int64_t>(row) * K + k;
     f32x4 v;
     if (k + 4 <= kend) {
       v = *reinterpret_cast<const f32x4u*>(src);
@@ -547,30 +546,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int g = i * NT + tid;
-      if (g < kGroups) sv[i] = group_of(g, kw);
+      if (g < kGroups) sv[i] = group_at(g / 16, kw + 4 * (g % 16));
     }
   };
-  bool outside = false;
   const auto stage_store = [&](int b) {
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
       const int g = i * NT + tid;
       if (g >= kGroups) break;
       uint32_t t[3][2];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const uint32_t u = __float_as_uint(sv[i][c]) & 0x7fffffffu;
-        outside = outside || (u != 0 && (u < 0x0d800000u || u > 0x49800000u));
-      }
-      split3(sv[i][0], sv[i][1], t[0][0], t[1][0], t[2][0]);
-      split3(sv[i][2], sv[i][3], t[0][1], t[1][1], t[2][1]);
+      split3(sv[i][0] * kSplitUp, sv[i][1] * kSplitUp, t[0][0], t[1][0], t[2][0]);
+      split3(sv[i][2] * kSplitUp, sv[i][3] * kSplitUp, t[0][1], t[1][1], t[2][1]);
 #pragma unroll
       for (int p = 0; p < 3; ++p)
         *reinterpret_cast<uint2*>(&sM[b][p][(g / 16) * kSplitStride + 4 * (g % 16)]) = make_uint2(t[p][0], t[p][1]);
     }
   };
   load(kbeg);
-  if (tid == 0) odd = 0;
   stage_load(kbeg);
   stage_store(0);
   __syncthreads();
@@ -611,14 +603,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     half ^= 1;
     if (half == 0 || k0 + 32 >= kend) {
       if (more) stage_store(buf ^ 1);
-      if (outside) odd = 1;
       lds_barrier();  // the window is read by every wave and the next one staged; loads of X stay in flight
       buf ^= 1;
     }
   }
   if (!active) return;
+  // (nothing of what follows is formed before the loop, whose registers it would take)
+  asm volatile("" : "+v"(je), "+v"(qe));
   // results outside the range of the terms (see above): once more with binary32 products
-  bool again = odd != 0;
+  bool again = false;
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
 #pragma unroll
@@ -630,39 +623,60 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
       }
   }
   if (__any(again)) {
+    // the rows of X as above, the next block in flight; product t of a block sums over the k of
+    // the four lane groups, k0 + 8 q + t, so a lane's share of M is eight consecutive k
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int64_t k0 = kbeg; k0 < kend; k0 += 4) {
-      const int64_t k = k0 + q;
-      const f32x4 xv = k < kend ? static_cast<f32x4>(*reinterpret_cast<const f32x4u*>(xa + k * B)) : f32x4{0.f, 0.f, 0.f, 0.f};
+    xp = xa + (kbeg + 8 * qe) * B;
+    load(kbeg);
+    for (int64_t k0 = kbeg; k0 < kend; k0 += 32) {
+      const int64_t kl = k0 + 8 * qe;
+      f32x4 x[8];
+      f32x4 w[MT][2];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const float w = k < kend ? Mop[(16 * mt + j) * K + k] : 0.f;
+      for (int t = 0; t < 8; ++t) x[t] = (kl + t < kend) ? rn[t] : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, xv[c], acc[mt][c], 0, 0, 0);
-      }
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[mt][h] = group_at(16 * mt + je, kl + 4 * h);
+      __builtin_amdgcn_sched_barrier(0);
+      load(k0 + 32);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[mt][t / 4][t % 4], x[t][c], acc[mt][c], 0, 0, 0);
     }
   }
   if (col_raw >= B) return;
   float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B + col;
-  const int skip = static_cast<int>(col_raw - col);  // columns that the lane before stores
+  if (col == col_raw) {
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t i = 16 * mt + 4 * q + v;
-      if (i >= m) continue;
-      float* y = ya + i * B;
-      if (skip == 0) {
-        *reinterpret_cast<f32x4u*>(y) = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
-      } else {
-#pragma unroll
-        for (int c = 1; c < 4; ++c)
-          if (c >= skip) y[c] = acc[mt][c][v];
+      for (int v = 0; v < 4; ++v) {
+        const int64_t i = 16 * mt + 4 * qe + v;
+        if (i < m) *reinterpret_cast<f32x4u*>(ya + i * B) = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
       }
+  } else {
+    const int skip = static_cast<int>(col_raw - col);  // columns that the lane before stores
+#pragma unroll
+    for (int c = 1; c < 4; ++c) {
+      if (c < skip) continue;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int64_t i = 16 * mt + 4 * qe + v;
+          if (i < m) ya[i * B + c] = acc[mt][c][v];
+        }
     }
+  }
 }
 
 // Independent binary32 contractions of one shape class in one launch: job q owns the

@@ -50,3 +50,31 @@ def test_every_column_has_one_owner(tail, where):
     got = _contract(X, U)
     alone = _contract(X[:, :, :B - tail], U)
     assert np.array_equal(got[:, :, :B - tail], alone, equal_nan=True)
+
+
+# Both operands are scaled by powers of two before they are split, and no size of M's entries short of
+# binary32's limits changes the way a contraction is computed: a factor of 2^30 on M is a factor of
+# 2^30 on every result, bit for bit.
+@pytest.mark.parametrize("K,m", [(40, 20), (130, 49)])
+@pytest.mark.parametrize("power", [-90, -30, 30])
+def test_power_of_two_in_the_operand(K, m, power):
+    rng = np.random.default_rng(K)
+    X, U = _float32(rng, 2, K, 192), _float32(rng, K, m)
+    assert np.array_equal(_contract(X, U * 2.0 ** power), _contract(X, U) * 2.0 ** power)
+
+
+# results past 2^80 and entries past 2^104 are taken again with binary32 products, in blocks of 32 k
+# with a remainder: entries one wave at a time, every row tile of M
+@pytest.mark.parametrize("shape,m", [((1, 33, 128), 17), ((2, 70, 68), 33), ((1, 1, 16389), 5), ((130, 95, 131), 64)])
+def test_results_outside_the_terms(shape, m):
+    rng = np.random.default_rng(sum(shape))
+    X, U = _float32(rng, *shape), _float32(rng, shape[1], m)
+    X[0, :, 3] *= 2.0 ** 110
+    X[-1, :, -1] *= 2.0 ** 90
+    X[-1, shape[1] - 1, shape[2] // 2] = np.inf
+    got = _contract(X, U)
+    assert np.array_equal(got[-1, :, shape[2] // 2], np.sign(U[-1]) * np.inf)
+    ref, mag = _reference(np.where(np.isfinite(X), X, 0.0), U)
+    off = ~np.isfinite(X).all(axis=1)
+    err = np.abs(np.moveaxis(got - ref, 1, 2))[~off]
+    assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[~off])
