@@ -439,12 +439,20 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 // ------------------------------------------------------------------ binary32 as three bfloat16 terms
 // The binary32 contraction on the bfloat16 matrix cores, at binary32 accuracy.  Every value is
 // the exact sum of three bfloat16 terms, x = h + m + l (each the rounding to nearest of what is
-// left, 8 bits at a time), and of the nine products of x and M the six of relative size 2^-16 or
-// more are kept (hh, hm, mh, mm, hl, lh, smallest first); the dropped ones are below 2^-24 of
-// |x M|, half a unit in the last place of binary32, with random signs.  A 16x16x32 bfloat16
-// product takes a quarter of the time a k of 16x16x4 binary32 ones do, so six of them take
-// 0.375 of it, and the sum of 32 k is rounded six times instead of eight (normal X of 1024 k: error
-// 1.23e-7 of the result's norm against 1.63e-7; over K = 100 .. 4096 between 0.5 and 0.97 of it).
+// left, 8 bits at a time: the splitting of Henry, Tang and Heinecke, ARITH 2019), and of the nine
+// products of x and M the six of relative size 2^-16 or more are kept (hh, hm, mh, mm, hl, lh); the
+// dropped ones are below 2^-24 of |x M|, half a unit in the last place of binary32, with random
+// signs.  A 16x16x32 bfloat16 product takes a quarter of the time a k of 16x16x4 binary32 ones do, so
+// six of them take 0.375 of it.
+//
+// Per block of 32 k the five small products are summed by themselves, smallest first, and that sum is
+// added on the vector ALU: the matrix cores cut an addend to the accumulator off where the vector ALU
+// rounds, and every product that they add to the whole sum costs it one more rounding.  Error of
+// the result's norm against 64 bits, over that of binary32 products on the matrix cores: normal data
+// 0.38 (K = 64), 0.45 (100), 0.59 (267), 0.58 (1024), 0.44 (4096); values exp(5 N), whose sums are mostly
+// one product, 0.99 .. 1.13 (with all six products added to the accumulator 1.13 .. 1.6, and normal
+// data 0.65 .. 0.85); a single product (K = 1) 1.02.  Cost: 1393 -> 1409 us for the 1024 x 1024 x 512
+// decomposition, nothing measurable for three row tiles of M or fewer.
 //
 // A wave owns 64 columns of one slab (lane j: four consecutive columns, at any 4-byte
 // boundary) and takes k in blocks of 32: lane group q loads the rows k0 + 8 q .. + 7, converts
@@ -592,13 +600,27 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
 #pragma unroll
       for (int p = 0; p < 3; ++p)
         mv[p] = *reinterpret_cast<const bf16x8*>(mw + (p * 16 * MT + 16 * mt) * kSplitStride);
-      constexpr int kTm[6] = {2, 0, 1, 1, 0, 0}, kTx[6] = {0, 2, 1, 0, 1, 0};
+      constexpr int kTm[5] = {2, 0, 1, 1, 0}, kTx[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-      for (int e = 0; e < 6; ++e)
+      for (int c0 = 0; c0 < 4; c0 += 2) {
+        f32x4 low[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              mv[kTm[e]], __builtin_bit_cast(bf16x8, xt[kTx[e]][c]), acc[mt][c], 0, 0, 0);
+        for (int e = 0; e < 5; ++e)
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            low[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[kTm[e]], __builtin_bit_cast(bf16x8, xt[kTx[e]][c0 + c]),
+                                                             low[c], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          acc[mt][c0 + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[0], __builtin_bit_cast(bf16x8, xt[0][c0 + c]),
+                                                                    acc[mt][c0 + c], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          acc[mt][c0 + c] += low[c];
+          // formed here: moved past the branches below, it would keep every `low` in registers
+          asm volatile("" : "+v"(acc[mt][c0 + c]));
+        }
+      }
     }
     half ^= 1;
     if (half == 0 || k0 + 32 >= kend) {

@@ -78,3 +78,33 @@ def test_results_outside_the_terms(shape, m):
     off = ~np.isfinite(X).all(axis=1)
     err = np.abs(np.moveaxis(got - ref, 1, 2))[~off]
     assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[~off])
+
+
+# A sum that one product makes up is that product rounded once: the error's mean square against 64
+# bits is that of the binary32 product, but for the dropped partial products.  (Each is the product of
+# a second and a third term, at most 2^-8 and 2^-17 of x: two of them add less than a tenth.)
+@pytest.mark.parametrize("shape", [(256, 1, 65), (1, 96, 16384)])
+def test_one_product_is_rounded_once(shape):
+    rng = np.random.default_rng(5)
+    A, K, B = shape
+    X = np.zeros(shape)
+    X[:, K // 2] = _float32(rng, A, B)
+    U = _float32(rng, K, 33)
+    got = _contract(X, U)
+    x, u = X[:, K // 2, None, :], U[K // 2][None, :, None]
+    once = (x.astype(np.float32) * u.astype(np.float32)).astype(np.float64)
+    rms = lambda y: float(np.sqrt(np.mean(((y - x * u) / (np.abs(x * u) + 1e-300)) ** 2)))  # noqa: E731
+    assert rms(got) <= 1.1 * rms(once)
+
+
+# the sums over k are no further from 64 bits than binary32 products summed four by four are
+@pytest.mark.parametrize("K,spread", [(64, 0.0), (300, 0.0), (1024, 2.0)])
+def test_error_of_the_sums(K, spread):
+    rng = np.random.default_rng(K)
+    X, U = _float32(rng, 2, K, 1024), _float32(rng, K, 33)
+    X = (X * np.exp(spread * rng.standard_normal(X.shape))).astype(np.float32).astype(np.float64)
+    ref, _ = _reference(X, U)
+    acc = np.zeros((2, 33, 1024), dtype=np.float32)
+    for k in range(0, K, 4):
+        acc += np.matmul(U[k:k + 4].T, X[:, k:k + 4]).astype(np.float32)
+    assert np.linalg.norm(_contract(X, U) - ref) <= np.linalg.norm(acc - ref)
