@@ -314,8 +314,9 @@ __device__ __forceinline__ float* part_of(float* Y, float* rest, int64_t ks, int
 // Work unit = (a, 128-column chunk, k-split part).  Y (or a split-K partial) is
 // written for rows i < m only.
 // One work unit (a wave) of the binary32 contraction; unit < A * chunks * ksplit.
-// (binary32 products: the small grouped contractions of the sketch's dimension tree)
-template <int MT, bool VM>
+// (binary32 products: the small grouped contractions of the sketch's dimension tree, and short K or
+// few rows of M)
+template <int MT, bool VM, int DEPTH, bool SUMS>
 __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_t A, int64_t K, int64_t B,
                                              const float* __restrict__ Mop, int64_t m, int64_t chunks, int ksplit,
                                              int64_t kper, float* __restrict__ Y, float* __restrict__ rest, int64_t unit) {
@@ -349,7 +350,6 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
   const int64_t c0off = colok0 ? b0 + 4 * j : b0, c1off = colok1 ? b0 + 64 + 4 * j : b0;
   const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
   // DEPTH blocks in flight: set P holds the block DEPTH steps ahead of the one multiplied
-  constexpr int DEPTH = 3;  // (four measured slower: registers)
   f32x4 n0[DEPTH][4], n1[DEPTH][4];
   float nw[DEPTH][MT][4];
   const auto load_block = [&](int64_t k0, auto Pc) {
@@ -396,6 +396,29 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
     __builtin_amdgcn_sched_barrier(0);
     load_block(k0 + 16 * DEPTH, Pc);  // past kend: rows kend - 1 again, never used
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SUMS) {
+      // sums of eight k each, added on the vector ALU: one chain over a long K rounds more (K = 80, normal
+      // data: 1.6e-7 of the result's norm, 7.5e-8 in these sums)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          f32x4 part[2][4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+              part[s % 2][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][mt], (g == 0 ? y0 : y1)[s][t],
+                                                                    s < 2 ? zero4 : part[s % 2][t], 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            acc[mt][g][t] += part[0][t] + part[1][t];
+            // formed here: moved past the loop's branches, it would keep the parts in registers
+            asm volatile("" : "+v"(acc[mt][g][t]));
+          }
+        }
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
 #pragma unroll
@@ -701,6 +724,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
   }
 }
 
+// Binary32 products, one block of 16 k in flight (see launch_ttm_mfma_ws for the sizes that take them).
+template <int MT, bool VM>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT == 4 ? 1 : 2))) void ttm_mfma_f32_kernel(
+    const float* __restrict__ X, int64_t A, int64_t K, int64_t B, const float* __restrict__ Mop, int64_t m,
+    int64_t chunks, float* __restrict__ Y) {
+  const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
+  if (unit < A * chunks) ttm_f32_unit<MT, VM, 1, MT == 1>(X, A, K, B, Mop, m, chunks, 1, (K + 3) / 4 * 4, Y, nullptr, unit);
+}
+
 // Independent binary32 contractions of one shape class in one launch: job q owns the
 // units [unit0_q, unit0_q + A_q chunks_q ksplit_q).
 struct F32Job {
@@ -724,7 +756,7 @@ __global__ __launch_bounds__(kMfmaThreads) void ttm_mfma_f32_grouped_kernel(F32J
   const F32Job& J = tab.j[q];
   const int64_t local = unit - J.unit0;
   if (local >= J.A * J.chunks * J.ksplit) return;
-  ttm_f32_unit<MT, VM>(J.X, J.A, J.K, J.B, J.Mop, J.m, J.chunks, J.ksplit, J.kper, J.Y, J.rest, local);
+  ttm_f32_unit<MT, VM, 3, false>(J.X, J.A, J.K, J.B, J.Mop, J.m, J.chunks, J.ksplit, J.kper, J.Y, J.rest, local);
 }
 
 // Last-mode contraction (B == 1): Y[a, i] = sum_k X[a, k] M[i, k], a GEMM with
@@ -1132,8 +1164,46 @@ size_t ttm_mfma_ws(rt_dtype xdt, int64_t A, int64_t K, int64_t B, int64_t m, boo
   return align256(static_cast<size_t>(ks - 1) * A * m * B * sizeof(float));
 }
 
+namespace {
+// Where binary32 products take less time than the three-term ones, which convert every value of X
+// and multiply a block of 32 k whatever part of it exists:
+//  * up to 16 k (64 x 4 x 4096 with m = 8: 8 us against 12; 16 x 262144, m = 36: 17 and 21);
+//  * one 16-row tile of M, whose products are few: 400 x 262144 with m = 8 77 us against 84, 48 x 262144 15
+//    and 19, 200 x 400 x 640 34 and 42.  Below 512 units of 128 columns they are alike or the
+//    split over k of the other gains more (400 x 4096: 23 against 10), and from 4096 units on
+//    HBM bounds both, but for short K (64 x 1048576: 75 and 65; 20 x 1048576: 33 and 39).
+bool f32_products_ok(int64_t A, int64_t K, int64_t B, int64_t m) {
+  if (B % 4 != 0) return false;
+  const int64_t units = A * ceil_div(B, kUnitCols);
+  return K <= 16 || (m <= 16 && units >= 512 && (units < 4096 || K <= 24));
+}
+
+hipError_t launch_f32_products(const float* X, int64_t A, int64_t K, int64_t B, const float* Mop, int64_t m, float* Y,
+                               hipStream_t st) {
+  const int64_t chunks = ceil_div(B, kUnitCols);
+  const unsigned grid = static_cast<unsigned>(ceil_div(A * chunks, kMfmaThreads / kWave));
+#define RT_F32(MTV, VMV) ttm_mfma_f32_kernel<MTV, VMV><<<grid, kMfmaThreads, 0, st>>>(X, A, K, B, Mop, m, chunks, Y)
+#define RT_F32_VM(MTV)                \
+  do {                                \
+    if (K % 4 == 0) RT_F32(MTV, true); \
+    else RT_F32(MTV, false);          \
+  } while (0)
+  switch (ttm_mfma_mpad(m) / 16) {
+    case 1: RT_F32_VM(1); break;
+    case 2: RT_F32_VM(2); break;
+    case 3: RT_F32_VM(3); break;
+    default: RT_F32_VM(4); break;
+  }
+#undef RT_F32_VM
+#undef RT_F32
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop,
                               int64_t m, float* Y, void* ws, hipStream_t st, std::vector<SplitSum>* later) {
+  if (xdt == RT_F32 && f32_products_ok(A, K, B, m) && reinterpret_cast<uintptr_t>(X) % 16 == 0)
+    return launch_f32_products(static_cast<const float*>(X), A, K, B, static_cast<const float*>(Mop), m, Y, st);
   const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
   float* rest = static_cast<float*>(ws);
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);

@@ -108,3 +108,26 @@ def test_error_of_the_sums(K, spread):
     for k in range(0, K, 4):
         acc += np.matmul(U[k:k + 4].T, X[:, k:k + 4]).astype(np.float32)
     assert np.linalg.norm(_contract(X, U) - ref) <= np.linalg.norm(acc - ref)
+
+
+# Binary32 products: up to 16 k (every count of row tiles of M, K on and off its 16-byte grid), and one
+# row tile where there are at least 512 units of 128 columns.
+@pytest.mark.parametrize("shape,m", [
+    ((1, 1, 64), 1), ((2, 3, 68), 16), ((3, 4, 132), 17), ((1, 7, 256), 33), ((2, 13, 124), 48), ((5, 16, 128), 64),
+    ((1, 15, 260), 49), ((512, 17, 64), 16), ((130, 50, 516), 9), ((600, 33, 68), 1), ((1, 130, 65536), 13),
+    ((4096, 24, 64), 7), ((4096, 25, 64), 7), ((511, 40, 128), 11),
+])
+@pytest.mark.parametrize("bad", [False, True])
+def test_binary32_products(shape, m, bad):
+    rng = np.random.default_rng(sum(shape) + m)
+    X, U = _float32(rng, *shape), _float32(rng, shape[1], m)
+    fin = np.ones((shape[0], shape[2]), dtype=bool)
+    if bad:
+        X[-1, shape[1] - 1, shape[2] - 2] = -np.inf
+        fin[-1, shape[2] - 2] = False
+    got = _contract(X, U)
+    ref, mag = _reference(np.where(np.isfinite(X), X, 0.0), U)
+    err = np.abs(np.moveaxis(got - ref, 1, 2))[fin]
+    assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[fin])
+    if bad:
+        assert np.array_equal(got[-1, :, shape[2] - 2], -np.sign(U[-1]) * np.inf)
