@@ -131,3 +131,38 @@ def test_binary32_products(shape, m, bad):
     assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[fin])
     if bad:
         assert np.array_equal(got[-1, :, shape[2] - 2], -np.sign(U[-1]) * np.inf)
+
+
+# rows that start at any 4-byte boundary run on this kernel from 256 units on
+@pytest.mark.parametrize("shape,m", [((256, 5, 65), 16), ((130, 31, 67), 17), ((128, 513, 70), 18), ((90, 65, 191), 49),
+                                     ((2, 100, 16001), 64), ((1, 130, 16387), 33), ((64, 96, 194), 50)])
+@pytest.mark.parametrize("skew", [0, 1, 3])
+@pytest.mark.parametrize("bad", [False, True])
+def test_ragged_rows(shape, m, skew, bad):
+    assert _units(shape) >= 256 and shape[2] % 4 != 0  # the rule that takes these sizes to the kernel
+    rng = np.random.default_rng(sum(shape) + m)
+    X, U = _float32(rng, *shape), _float32(rng, shape[1], m)
+    fin = np.ones((shape[0], shape[2]), dtype=bool)
+    if bad:
+        for a, b, v in ((0, 0, np.inf), (-1, shape[2] - 1, -np.inf), (shape[0] // 2, shape[2] - 3, np.nan)):
+            X[a, shape[1] // 2, b] = v
+            fin[a, b] = False
+    got = _contract(X, U, skew)
+    ref, mag = _reference(np.where(np.isfinite(X), X, 0.0), U)
+    err = np.abs(np.moveaxis(got - ref, 1, 2))[fin]
+    assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[fin])
+    if bad:
+        assert not np.isfinite(np.moveaxis(got, 1, 2)[~fin]).any()
+
+
+# eight waves a workgroup: an unsplit k range past 768 (2049 units of 64 columns), every entry checked
+def test_eight_waves_a_workgroup():
+    K, B, m = 800, 131072 + 64, 49
+    print("core", K, B, m, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn(1, K, B, generator=g, device="cuda")
+    U = torch.randn(K, m, generator=g, device="cuda").double()
+    got = rt.rtucker_core(X, [None, U, None], modes=[1])[0].double()
+    Ut, Xd = U.t().contiguous(), X[0].double()
+    bound = 2 * (K + 8) * 2.0 ** -24 * (Ut.abs() @ Xd.abs())
+    assert bool(((got - Ut @ Xd).abs() <= bound).all())
