@@ -1050,6 +1050,83 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     }
 }
 
+// The same with the lane's share of M (eight k of a row) read from the caches beside its rows of X,
+// for rows on the 16-byte grid (B and K multiples of eight): without the LDS windows a wave starts its
+// products as soon as its own loads are there.  Bound: latency, for the small contractions that run
+// here (see bf16_direct_ok).
+template <int MT>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_bf16_direct_kernel(
+    const bf16_t* __restrict__ X, int64_t A, int64_t K, int64_t B, const bf16_t* __restrict__ Mop, int64_t m,
+    int64_t chunks, int ksplit, int64_t kper, float* __restrict__ Y, float* __restrict__ rest) {
+  const int lane = threadIdx.x % kWave;
+  const int64_t unit = static_cast<int64_t>(blockIdx.x) * (kMfmaThreads / kWave) + threadIdx.x / kWave;
+  if (unit >= A * chunks * ksplit) return;
+  const int ks = static_cast<int>(unit % ksplit);
+  const int64_t ac = unit / ksplit;
+  const int64_t a = ac / chunks;
+  const int j = lane % 16, q = lane / 16;
+  const int64_t col = (ac - a * chunks) * kUnitCols + 8 * j;
+  const int64_t kbeg = ks * kper;
+  const int64_t kend = (kbeg + kper < K) ? kbeg + kper : K;
+  f32x4 acc[MT][8];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[mt][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // The next 32 k are loaded while the current ones are multiplied.  Loads carry no conditions: a
+  // block past kend reads the last 8 k of the range (zeroed before use; kbeg and kend are
+  // multiples of 8), and columns past B are the last 8 (their products are not stored).
+  const bf16_t* xa = X + a * K * B + (col < B ? col : B - 8);
+  const bf16_t* ma = Mop + j * K;
+  u32x4 rn[8], nw[MT];
+  const auto load = [&](int64_t k0) {
+    const int64_t k = k0 + 8 * q;
+    const int64_t kc = (k < kend) ? k : kend - 8;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) nw[mt] = *reinterpret_cast<const u32x4*>(ma + 16 * mt * K + kc);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) rn[t] = *reinterpret_cast<const u32x4*>(xa + (kc + t) * B);
+  };
+  if (kbeg < kend) load(kbeg);
+  const u32x4 zero4 = u32x4{0u, 0u, 0u, 0u};
+  for (int64_t k0 = kbeg; k0 < kend; k0 += 32) {
+    const bool kin = k0 + 8 * q < kend;
+    u32x4 r[8], mv[MT];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) r[t] = kin ? rn[t] : zero4;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) mv[mt] = kin ? nw[mt] : zero4;
+    __builtin_amdgcn_sched_barrier(0);
+    load(k0 + 32);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      u32x4 op;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const uint32_t lo = r[2 * w][c / 2], hi = r[2 * w + 1][c / 2];
+        op[w] = (c % 2 == 0) ? pack_lo(lo, hi) : pack_hi(lo, hi);
+      }
+      const bf16x8 bv = __builtin_bit_cast(bf16x8, op);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+        acc[mt][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, mv[mt]), bv, acc[mt][c], 0, 0, 0);
+    }
+  }
+  if (col >= B) return;
+  float* ya = part_of(Y, rest, ks, A * m * B) + a * m * B + col;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t i = 16 * mt + 4 * q + v;
+      if (i >= m) continue;
+      f32x4u* dst = reinterpret_cast<f32x4u*>(ya + i * B);
+      dst[0] = f32x4{acc[mt][0][v], acc[mt][1][v], acc[mt][2][v], acc[mt][3][v]};
+      dst[1] = f32x4{acc[mt][4][v], acc[mt][5][v], acc[mt][6][v], acc[mt][7][v]};
+    }
+}
+
 // Y = sum of the split parts in part order (binary32), stored as TO
 template <typename TO>
 __global__ __launch_bounds__(256) void sum_splits_kernel(const float* first, const float* __restrict__ rest, int ksplit,
@@ -1178,6 +1255,13 @@ bool f32_products_ok(int64_t A, int64_t K, int64_t B, int64_t m) {
   return K <= 16 || (m <= 16 && units >= 512 && (units < 4096 || K <= 24));
 }
 
+// Where the bfloat16 contraction reads M from the caches: rows on the 16-byte grid, and too few units
+// or too short a K to gain from sharing M (208 x 80 x 112 with m = 60: 11 us, 18 with M in LDS; 480 x 65536:
+// 20 and 30; 208 x 512 x 512, m = 60: 32 and 35; 480 x 262144, m = 60: 70 and 61; 208 x 1048576: 170 and 167).
+bool bf16_direct_ok(int64_t units, int64_t K, int64_t B) {
+  return B % 8 == 0 && K % 8 == 0 && (units < 2048 || (units < 8192 && K <= 256));
+}
+
 hipError_t launch_f32_products(const float* X, int64_t A, int64_t K, int64_t B, const float* Mop, int64_t m, float* Y,
                                hipStream_t st) {
   const int64_t chunks = ceil_div(B, kUnitCols);
@@ -1198,6 +1282,62 @@ hipError_t launch_f32_products(const float* X, int64_t A, int64_t K, int64_t B, 
 #undef RT_F32
   return hipGetLastError();
 }
+hipError_t launch_bf16_direct(const bf16_t* X, int64_t A, int64_t K, int64_t B, const bf16_t* Mop, int64_t m,
+                              const MfmaPlan& p, float* Y, float* rest, hipStream_t st) {
+  const unsigned grid = static_cast<unsigned>(ceil_div(A * p.chunks * p.ksplit, kMfmaThreads / kWave));
+#define RT_DIRECT(MTV)                                                                                          \
+  ttm_mfma_bf16_direct_kernel<MTV><<<grid, kMfmaThreads, 0, st>>>(X, A, K, B, Mop, m, p.chunks, p.ksplit, p.kper, \
+                                                                  Y, rest)
+  switch (ttm_mfma_mpad(m) / 16) {
+    case 1: RT_DIRECT(1); break;
+    case 2: RT_DIRECT(2); break;
+    case 3: RT_DIRECT(3); break;
+    default: RT_DIRECT(4); break;
+  }
+#undef RT_DIRECT
+  return hipGetLastError();
+}
+
+// The kernels that stage M in LDS; the waves of a workgroup share the k range.
+hipError_t launch_staged(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop, int64_t m,
+                         const MfmaPlan& p, float* Y, float* rest, hipStream_t st) {
+  const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
+  const int64_t units = A * p.chunks;
+  // Binary32: eight waves a workgroup when each has a long range of k: they read 2 KB of a row together
+  // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
+  // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
+  // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
+  // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
+  // 49) was no faster here, unlike with binary32 products.
+  // bfloat16: eight for four row tiles of M, which with four waves do not fit the registers (1024 x
+  // 262144 with m = 60: 140 us with four, 119 with eight), except in the small contractions, where
+  // the second workgroup of a CU is worth more (24576 columns, K = 208: 17.4 and 18.6; 98304: 23.0 and 22.4).
+  const bool wide = xdt == RT_F32 ? p.kper > 768 : MT == 4 && units * K >= 150000;
+  const int64_t groups = ceil_div(units, wide ? 8 : 4);
+  const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
+#define RT_TTM(KERNEL, TX, MTV, NTV)                                                                      \
+  KERNEL<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const TX*>(X), A, K, B, static_cast<const TX*>(Mop), \
+                                         m, p.chunks, groups, p.kper, Y, rest)
+#define RT_TTM_ANY(MTV)                                                    \
+  do {                                                                     \
+    if (xdt == RT_BF16) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 256);    \
+    else if (wide) RT_TTM(ttm_split_f32_kernel, float, MTV, 512);          \
+    else RT_TTM(ttm_split_f32_kernel, float, MTV, 256);                    \
+  } while (0)
+  if (xdt == RT_BF16 && wide) {
+    RT_TTM(ttm_mfma_bf16_kernel, bf16_t, 4, 512);
+  } else {
+    switch (MT) {
+      case 1: RT_TTM_ANY(1); break;
+      case 2: RT_TTM_ANY(2); break;
+      case 3: RT_TTM_ANY(3); break;
+      default: RT_TTM_ANY(4); break;
+    }
+  }
+#undef RT_TTM_ANY
+#undef RT_TTM
+  return hipGetLastError();
+}
 }  // namespace
 
 hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K, int64_t B, const void* Mop,
@@ -1206,36 +1346,11 @@ hipError_t launch_ttm_mfma_ws(const void* X, rt_dtype xdt, int64_t A, int64_t K,
     return launch_f32_products(static_cast<const float*>(X), A, K, B, static_cast<const float*>(Mop), m, Y, st);
   const MfmaPlan p = mfma_plan(xdt, A, K, B, m, xdt == RT_F32 ? kSplitCols : kUnitCols);
   float* rest = static_cast<float*>(ws);
-  const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
-  // The waves of a workgroup share the k range.  Binary32: eight waves a workgroup when each has a
-  // long range of k: they read 2 KB of a row together
-  // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
-  // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
-  // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
-  // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
-  // 49) was no faster here, unlike with binary32 products.
-  const bool wide = xdt == RT_F32 ? p.kper > 768 : MT == 4;
-  const int64_t groups = ceil_div(A * p.chunks, wide ? 8 : 4);
-  const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
-#define RT_TTM(KERNEL, TX, MTV, NTV)                                                                      \
-  KERNEL<MTV, NTV><<<grid, NTV, 0, st>>>(static_cast<const TX*>(X), A, K, B, static_cast<const TX*>(Mop), \
-                                         m, p.chunks, groups, p.kper, Y, rest)
-#define RT_TTM_ANY(MTV)                                          \
-  do {                                                           \
-    if (xdt == RT_BF16 && wide) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 512); \
-    else if (xdt == RT_BF16) RT_TTM(ttm_mfma_bf16_kernel, bf16_t, MTV, 256); \
-    else if (wide) RT_TTM(ttm_split_f32_kernel, float, MTV, 512);  \
-    else RT_TTM(ttm_split_f32_kernel, float, MTV, 256);          \
-  } while (0)
-  switch (MT) {
-    case 1: RT_TTM_ANY(1); break;
-    case 2: RT_TTM_ANY(2); break;
-    case 3: RT_TTM_ANY(3); break;
-    default: RT_TTM_ANY(4); break;
-  }
-#undef RT_TTM_ANY
-#undef RT_TTM
-  hipError_t e = hipGetLastError();
+  hipError_t e;
+  if (xdt == RT_BF16 && bf16_direct_ok(A * p.chunks, K, B) && reinterpret_cast<uintptr_t>(X) % 16 == 0)
+    e = launch_bf16_direct(static_cast<const bf16_t*>(X), A, K, B, static_cast<const bf16_t*>(Mop), m, p, Y, rest, st);
+  else
+    e = launch_staged(X, xdt, A, K, B, Mop, m, p, Y, rest, st);
   if (e != hipSuccess || p.ksplit == 1) return e;
   const int64_t n = A * m * B;
   if (later) {

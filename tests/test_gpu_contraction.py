@@ -166,3 +166,28 @@ def test_eight_waves_a_workgroup():
     Ut, Xd = U.t().contiguous(), X[0].double()
     bound = 2 * (K + 8) * 2.0 ** -24 * (Ut.abs() @ Xd.abs())
     assert bool(((got - Ut @ Xd).abs() <= bound).all())
+
+
+# ------------------------------------------------------------------ bfloat16, M read from the caches
+# rows on the 16-byte grid and fewer than 2048 units of 128 columns (or 8192 with at most 256 k): 32-k blocks
+# cut at multiples of eight, every count of row tiles, splits of k; one element off the grid the same
+# contraction runs with M in LDS.  Products are exact; binary32 sums as above.
+@pytest.mark.parametrize("shape,m", [((1, 8, 64), 1), ((3, 16, 72), 17), ((2, 40, 136), 33), ((5, 72, 640), 64),
+                                     ((1, 1000, 128), 50), ((2, 2048, 64), 30), ((2100, 8, 64), 16), ((700, 264, 384), 7)])
+@pytest.mark.parametrize("skew", [0, 1])
+@pytest.mark.parametrize("bad", [False, True])
+def test_bfloat16_small(shape, m, skew, bad):
+    rng = np.random.default_rng(sum(shape) + m)
+    X = torch.from_numpy(rng.standard_normal(shape)).to(torch.bfloat16).double().numpy()
+    U = torch.from_numpy(rng.standard_normal((shape[1], m))).to(torch.bfloat16).double().numpy()
+    fin = np.ones((shape[0], shape[2]), dtype=bool)
+    if bad:
+        X[-1, shape[1] - 1, shape[2] - 1] = np.inf
+        fin[-1, shape[2] - 1] = False
+    print("core bf16", shape, m, skew, flush=True)
+    got = rt.rtucker_core(_dev(X, torch.bfloat16, skew), [None, _dev(U), None], modes=[1]).double().cpu().numpy()
+    ref, mag = _reference(np.where(np.isfinite(X), X, 0.0), U)
+    err = np.abs(np.moveaxis(got - ref, 1, 2))[fin]
+    assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[fin])
+    if bad:
+        assert np.array_equal(got[-1, :, -1][U[-1] != 0], (np.sign(U[-1]) * np.inf)[U[-1] != 0])
