@@ -616,35 +616,55 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void tt
     __builtin_amdgcn_sched_barrier(0);
     load(k0 + 32);
     __builtin_amdgcn_sched_barrier(0);
+    // The columns in pairs: the small products of a pair, then the large ones of the next pair, then
+    // the pair's addition, whose operands the matrix cores have finished by then; the terms of the
+    // next row tile are read during the second pair's products.
     const uint16_t* mw = &sM[buf][0][j * kSplitStride + 32 * half + 8 * q];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      bf16x8 mv[3];
+    const auto read_m = [&](bf16x8 (&mv)[3], int mt) {
 #pragma unroll
       for (int p = 0; p < 3; ++p)
         mv[p] = *reinterpret_cast<const bf16x8*>(mw + (p * 16 * MT + 16 * mt) * kSplitStride);
+    };
+    const auto large = [&](int mt, int c0, bf16x8 mv) {
+#pragma unroll
+      for (int c = c0; c < c0 + 2; ++c)
+        acc[mt][c] =
+            __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv, __builtin_bit_cast(bf16x8, xt[0][c]), acc[mt][c], 0, 0, 0);
+    };
+    bf16x8 mv[3], nx[3];
+    read_m(mv, 0);
+    large(0, 0, mv[0]);
+#pragma unroll
+    for (int pair = 0; pair < 2 * MT; ++pair) {
       constexpr int kTm[5] = {2, 0, 1, 1, 0}, kTx[5] = {0, 2, 1, 0, 1};
+      const int mt = pair / 2, c0 = 2 * (pair % 2);
+      if (c0 == 2 && mt + 1 < MT) {
+        read_m(nx, mt + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      f32x4 low[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-      for (int c0 = 0; c0 < 4; c0 += 2) {
-        f32x4 low[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-        for (int e = 0; e < 5; ++e)
-#pragma unroll
-          for (int c = 0; c < 2; ++c)
-            low[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[kTm[e]], __builtin_bit_cast(bf16x8, xt[kTx[e]][c0 + c]),
-                                                             low[c], 0, 0, 0);
+      for (int e = 0; e < 5; ++e)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
-          acc[mt][c0 + c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[0], __builtin_bit_cast(bf16x8, xt[0][c0 + c]),
-                                                                    acc[mt][c0 + c], 0, 0, 0);
+          low[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(mv[kTm[e]], __builtin_bit_cast(bf16x8, xt[kTx[e]][c0 + c]),
+                                                           low[c], 0, 0, 0);
+      if (c0 == 0) {
+        large(mt, 2, mv[0]);
+      } else if (mt + 1 < MT) {
+        large(mt + 1, 0, nx[0]);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          acc[mt][c0 + c] += low[c];
-          // formed here: moved past the branches below, it would keep every `low` in registers
-          asm volatile("" : "+v"(acc[mt][c0 + c]));
-        }
+        for (int p = 0; p < 3; ++p) mv[p] = nx[p];
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[mt][c0 + c] += low[c];
     }
+    // the sums are formed here: moved past the branches below, they would keep every `low` in registers
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(acc[mt][c]));
     half ^= 1;
     if (half == 0 || k0 + 32 >= kend) {
       if (more) stage_store(buf ^ 1);
@@ -1303,16 +1323,19 @@ hipError_t launch_staged(const void* X, rt_dtype xdt, int64_t A, int64_t K, int6
                          const MfmaPlan& p, float* Y, float* rest, hipStream_t st) {
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
   const int64_t units = A * p.chunks;
-  // Binary32: eight waves a workgroup when each has a long range of k: they read 2 KB of a row together
-  // and split M once for all (first contraction of the 1024 x 1024 x 512 decomposition: 444 us
-  // with four, 419 with eight).  With a shorter range the prologue of the one such workgroup that
-  // a CU holds is exposed (K = 128, m = 27: 281 us with eight, 256 with four; K = 768, m = 36: 226
-  // and 214).  A row past the last whole tile on the vector ALU instead of a padded tile (m =
-  // 49) was no faster here, unlike with binary32 products.
+  // Binary32: eight waves a workgroup read 2 KB of a row together and split M once for all, but the
+  // prologue of the one such workgroup that a CU holds is exposed.  Rows of 131072 columns on gain from
+  // 256 k on (2 x 512 x 131072, m = 36: 119 us with four, 112 with eight; 2 x 1024 x 131072, m = 49: 247 and
+  // 232; K = 128, m = 27: 256 and 281).  Shorter ones lose, the more the shorter (16 x 512 x 16384, m = 36:
+  // 108 and 124; 40 x 1024 x 2048, m = 49: 103 and 117), but for four row tiles and a long K, where four
+  // waves wait for M (32 x 1024 x 8192: 241 and 230, 64 x 1024 x 4096: 238 and 233; 512 x 1024 x 640: 299 and 325).
+  // A row past the last whole tile on the vector ALU instead of a padded tile (m = 49) was no faster here,
+  // unlike with binary32 products.
   // bfloat16: eight for four row tiles of M, which with four waves do not fit the registers (1024 x
   // 262144 with m = 60: 140 us with four, 119 with eight), except in the small contractions, where
   // the second workgroup of a CU is worth more (24576 columns, K = 208: 17.4 and 18.6; 98304: 23.0 and 22.4).
-  const bool wide = xdt == RT_F32 ? p.kper > 768 : MT == 4 && units * K >= 150000;
+  const bool wide = xdt == RT_BF16 ? MT == 4 && units * K >= 150000
+                                   : (B >= 131072 ? p.kper >= 256 : MT == 4 && B >= 4096 && p.kper > 768);
   const int64_t groups = ceil_div(units, wide ? 8 : 4);
   const unsigned grid = static_cast<unsigned>(groups * p.ksplit);
 #define RT_TTM(KERNEL, TX, MTV, NTV)                                                                      \

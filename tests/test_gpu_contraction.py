@@ -191,3 +191,20 @@ def test_bfloat16_small(shape, m, skew, bad):
     assert np.all(err <= 2 * (shape[1] + 8) * 2.0 ** -24 * np.moveaxis(mag, 1, 2)[fin])
     if bad:
         assert np.array_equal(got[-1, :, -1][U[-1] != 0], (np.sign(U[-1]) * np.inf)[U[-1] != 0])
+
+
+# The two rules that give eight waves to a workgroup: rows of 131072 columns from 256 k on (every count of row
+# tiles, a remainder of the 32-k block, rows off the 16-byte grid), and four row tiles with more than 768 k.
+@pytest.mark.parametrize("shape,m", [((1, 256, 131072), 16), ((1, 263, 131072), 32), ((1, 270, 131077), 36), ((1, 289, 131072), 64),
+                                     ((33, 777, 4100), 50), ((1, 255, 131072), 36)])
+def test_eight_waves_by_row_length(shape, m):
+    A, K, B = shape
+    print("core", shape, m, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(K)
+    X = torch.randn(shape, generator=g, device="cuda")
+    U = torch.randn(K, m, generator=g, device="cuda").double()
+    got = rt.rtucker_core(X, [None, U, None], modes=[1])
+    Ut = U.t().contiguous()
+    for a in range(A):
+        Xd = X[a].double()
+        assert bool(((got[a].double() - Ut @ Xd).abs() <= 2 * (K + 8) * 2.0 ** -24 * (Ut.abs() @ Xd.abs())).all())
