@@ -391,9 +391,12 @@ Ten core_impl(Ctx& c, const Ten& X, const double* const* U, const int64_t* l, ui
     st.in_dt = cur_dt;
     const rt_dtype ct = ctype(cur_dt);
     st.mfma = (cur_dt == RT_F32 || cur_dt == RT_BF16) && ttm_mfma_ok(cur_dt, st.A, st.K, st.B, st.m);
-    // a contraction over the last mode (B = 1) runs on the matrix-core kernel for contiguous rows
-    st.last = !st.mfma && st.B == 1 && ttm_mfma_last_ok(cur_dt, st.A, st.K, st.m);
-    st.wide = last && f64_out && st.last && !dst;
+    // a contraction over the last mode (B = 1) runs on the matrix-core kernel for contiguous rows where
+    // that is faster, or saves the launch that widens the core
+    const bool widen = last && f64_out && !dst;
+    st.last = !st.mfma && st.B == 1 &&
+              (widen ? ttm_mfma_last_ok(cur_dt, st.A, st.K, st.m) : ttm_mfma_last_pays(cur_dt, st.A, st.K, st.m));
+    st.wide = widen && st.last;
     st.op = st.mfma || st.last
                 ? prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt, cur_dt, ttm_mfma_mpad(st.m))
                 : prep(c, U ? U[k] : nullptr, st.m, st.K, true, cur_dt == RT_F64 ? RT_F64 : cur_dt, ct);
@@ -993,7 +996,7 @@ int plan_multi_ttm(Ctx& c, const rt_tensor* X, const void* const* A, const int64
     void* dst = (i + 1 == order.size()) ? Y : nullptr;
     const int64_t Ab = cur.before(k), K = cur.dims[k], Bb = cur.after(k);
     const bool mf = X->dtype == RT_F32 && ttm_mfma_ok(RT_F32, Ab, K, Bb, m[k]);
-    const bool last = X->dtype == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_ok(RT_F32, Ab, K, m[k]);
+    const bool last = X->dtype == RT_F32 && !mf && Bb == 1 && ttm_mfma_last_pays(RT_F32, Ab, K, m[k]);
     if (mf || last) {
       // matrix cores: operand packed to a multiple of 16 rows, binary32 accumulation
       const int64_t mp = ttm_mfma_mpad(m[k]);

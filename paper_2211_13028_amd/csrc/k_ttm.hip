@@ -13,6 +13,7 @@
 //    small binary32 contractions of one launch (the prepared M operand is read from L2).
 //  * ttm_mfma_last: the last mode (B == 1), X in rows of K contiguous values.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -37,6 +38,11 @@ __device__ __forceinline__ void generic_accumulate(const TX* __restrict__ xp, in
   constexpr int kPer = MT * kGenKC / kWave;  // M elements per thread at the smallest block (one wave)
   const int nth = static_cast<int>(blockDim.x);
   for (int64_t k0 = kb; k0 < ke; k0 += kGenKC) {
+    // binary32: the sums of 64 k are added up (one chain over a long K rounds more)
+    constexpr bool kSums = std::is_same<TC, float>::value;
+    TC part[MT];
+#pragma unroll
+    for (int ii = 0; ii < MT; ++ii) part[ii] = kSums ? TC(0) : acc[ii];
     TC mv[kPer];
 #pragma unroll
     for (int rep = 0; rep < kPer; ++rep) {
@@ -63,9 +69,11 @@ __device__ __forceinline__ void generic_accumulate(const TX* __restrict__ xp, in
 #pragma unroll
         for (int u = 0; u < kXB; ++u)
 #pragma unroll
-          for (int ii = 0; ii < MT; ++ii) acc[ii] = fma(sM[ii][kk0 + u], xv[u], acc[ii]);
+          for (int ii = 0; ii < MT; ++ii) part[ii] = fma(sM[ii][kk0 + u], xv[u], part[ii]);
       }
     }
+#pragma unroll
+    for (int ii = 0; ii < MT; ++ii) acc[ii] = kSums ? acc[ii] + part[ii] : part[ii];
   }
 }
 
@@ -827,8 +835,8 @@ struct LastIO<bf16_t> {
   static constexpr int kMacs = 1;
 };
 
-template <typename TX, int MT, bool PARTS>
-__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : MT >= 3 ? 2 : PARTS ? 3 : 4))) void
+template <typename TX, int MT, bool PARTS, bool EVEN>
+__global__ __launch_bounds__(kMfmaThreads) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : MT >= 3 ? 2 : EVEN ? 4 : 3))) void
 ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* __restrict__ Mop, int64_t m, int ksplit,
                      int64_t kper, float* __restrict__ Y) {
   typedef LastIO<TX> IO;
@@ -862,7 +870,6 @@ ttm_mfma_last_kernel(const TX* __restrict__ X, int64_t A, int64_t K, const TX* _
   // A - 1 (its products land only in output rows that are not stored); in the range's last step
   // k past kend is zero in both operands.  EVEN (binary32 on the 16-byte grid): the loads carry no
   // conditions, k past kend reads the range's last four and is zeroed when it is taken over.
-  constexpr bool EVEN = !PARTS && IO::kMacs > 1;
   const TX* xr[4];
 #pragma unroll
   for (int at = 0; at < 4; ++at) {
@@ -1448,6 +1455,12 @@ bool ttm_mfma_last_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t m) {
   return (xdt == RT_F32 || xdt == RT_BF16) && A >= 1 && m >= 1 && m <= 64 && K >= 4;
 }
 
+bool ttm_mfma_last_pays(rt_dtype xdt, int64_t A, int64_t K, int64_t m) {
+  if (!ttm_mfma_last_ok(xdt, A, K, m)) return false;
+  if (xdt == RT_F32) return K % 4 == 0 || A * K > 400000 || (m <= 16 && K >= 64);
+  return A * K > 200000 || (K >= 32 && (K >= 64 || K % 8 == 0 || m <= 32));
+}
+
 namespace {
 struct LastPlan {
   int ksplit;
@@ -1478,19 +1491,21 @@ hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t 
   const unsigned grid = static_cast<unsigned>(ceil_div(units, kMfmaThreads / kWave));
   const int MT = static_cast<int>(ttm_mfma_mpad(m) / 16);
   // Rows off the 16-byte grid are summed in parts of 64 k: one chain over a long K rounds more than the
-  // parts that the vector-ALU kernel they ran on before splits it into (1.76e-7 against 1.53e-7 of the
+  // parts that the vector-ALU kernel splits it into (1.76e-7 against 1.53e-7 of the
   // norm at K = 267; 1.42e-7 in parts).  On the grid, one chain with loads that carry no conditions is
-  // faster for up to two row tiles (112 x 768 x 784 with m = 24: 81 us, 91 in parts), the parts for more
-  // (400 x 500 x 600 with m = 44: 214 us, 225 in one chain; 256 x 256 x 1024 with m = 64: 123 and 128).
-  const bool parts = xdt == RT_F32 && (MT >= 3 || K % 4 != 0 || reinterpret_cast<uintptr_t>(X) % 16 != 0);
-#define RT_LAST(TXV, MTV, PV)                                                                                     \
-  ttm_mfma_last_kernel<TXV, MTV, PV><<<grid, kMfmaThreads, 0, st>>>(                                              \
+  // faster for up to two row tiles (112 x 768 x 784 with m = 24: 81 us, 91 in parts).  For more, the
+  // parts, with such loads where X stays in the caches (1521 x 384 with m = 55: 17.9 us, 19.5 with
+  // conditions; 5332 x 784, m = 39: 21.0 and 22.5; 20000 x 384, m = 55: 45.0 and 41.7; 100000 x 784: 207 and 174).
+  const bool grid16 = xdt == RT_F32 && K % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const bool even = grid16 && (MT < 3 || A * K <= (int64_t(1) << 22));
+#define RT_LAST(TXV, MTV, PV, EV)                                                                                 \
+  ttm_mfma_last_kernel<TXV, MTV, PV, EV><<<grid, kMfmaThreads, 0, st>>>(                                          \
       static_cast<const TXV*>(X), A, K, static_cast<const TXV*>(Mop), m, p.ksplit, p.kper, out)
-#define RT_LAUNCH_LAST(MTV)                      \
-  do {                                           \
-    if (xdt != RT_F32) RT_LAST(bf16_t, MTV, false); \
-    else if (parts) RT_LAST(float, MTV, true);   \
-    else RT_LAST(float, (MTV < 3 ? MTV : 2), false); \
+#define RT_LAUNCH_LAST(MTV)                                \
+  do {                                                     \
+    if (xdt != RT_F32) RT_LAST(bf16_t, MTV, false, false); \
+    else if (even) RT_LAST(float, MTV, (MTV >= 3), true);  \
+    else RT_LAST(float, MTV, true, false);                 \
   } while (0)
   switch (MT) {
     case 1: RT_LAUNCH_LAST(1); break;

@@ -142,6 +142,10 @@ hipError_t launch_ttm_mfma_f32_group(const F32Contraction* c, int count, std::ve
 // the split parts, widened exactly), and Y is not used; the workspace query then needs
 // f64_out set.  With `later` given, the sum of split parts into Y is left there.
 bool ttm_mfma_last_ok(rt_dtype xdt, int64_t A, int64_t K, int64_t m);
+// Where it is also faster than the vector ALU, whose waves share the rows of M in a small contraction:
+// binary32 rows off the 16-byte grid, 625 x 127 with m = 39: 11 us against 17, 1521 x 201, m = 55: 15 and 21,
+// 3034 x 201, m = 25: 14.3 and 13.8; bfloat16 1521 x 20, m = 25: 7 and 9, 1521 x 53, m = 55: 10 and 13.
+bool ttm_mfma_last_pays(rt_dtype xdt, int64_t A, int64_t K, int64_t m);
 size_t ttm_mfma_last_ws(int64_t A, int64_t K, int64_t m, bool f64_out = false);
 hipError_t launch_ttm_mfma_last(const void* X, rt_dtype xdt, int64_t A, int64_t K, const void* Mop, int64_t m, float* Y,
                                 void* ws, hipStream_t st, double* Y64 = nullptr, std::vector<SplitSum>* later = nullptr);

@@ -208,3 +208,42 @@ def test_eight_waves_by_row_length(shape, m):
     for a in range(A):
         Xd = X[a].double()
         assert bool(((got[a].double() - Ut @ Xd).abs() <= 2 * (K + 8) * 2.0 ** -24 * (Ut.abs() @ Xd.abs())).all())
+
+
+# ------------------------------------------------------------------ last mode and vector ALU
+# Three and four row tiles on the 16-byte grid, in parts of 64 k: with loads that carry no conditions up to
+# 2^22 entries, with conditions past them; k ranges cut anywhere, splits of k.
+@pytest.mark.parametrize("shape,m", [((1, 1, 4), 33), ((9, 7, 20), 48), ((65, 1, 64), 64), ((7, 1, 132), 49), ((200, 1, 520), 50),
+                                     ((3, 50, 1000), 40), ((4, 1100, 960), 35)])
+@pytest.mark.parametrize("bad", [False, True])
+def test_last_mode_three_and_four_tiles(shape, m, bad):
+    rng = np.random.default_rng(sum(shape) + m)
+    K = shape[2]
+    X, U = _float32(rng, *shape), _float32(rng, K, m)
+    fin = np.ones(shape[:2], dtype=bool)
+    if bad:
+        X[-1, -1, K - 1] = np.inf
+        fin[-1, -1] = False
+    print("core last", shape, m, flush=True)
+    got = rt.rtucker_core(_dev(X, torch.float32), [None, None, _dev(U)], modes=[2]).double().cpu().numpy()
+    Xf = np.where(np.isfinite(X), X, 0.0)
+    assert np.all(np.abs(got - Xf @ U)[fin] <= (2 * (K + 8) * 2.0 ** -24 * (np.abs(Xf) @ np.abs(U)))[fin])
+    if bad:
+        assert np.array_equal(got[-1, -1], np.sign(U[-1]) * np.inf)
+
+
+# Small contractions on the vector ALU (rows shorter than 64, last modes off the 16-byte grid): sums of 64 k,
+# remainders, splits of k.
+@pytest.mark.parametrize("dims,mode,m", [((5, 1, 3), 1, 4), ((5, 63, 3), 1, 5), ((2, 64, 33), 1, 20), ((7, 65, 5), 1, 64),
+                                         ((1, 130, 63), 1, 17), ((2, 1001, 3), 1, 9), ((9, 7, 53), 2, 40), ((3, 4, 129), 2, 20)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_vector_alu_sums(dims, mode, m, dtype):
+    rng = np.random.default_rng(sum(dims) + m)
+    X = torch.from_numpy(rng.standard_normal(dims)).to(dtype).double().numpy()
+    U = torch.from_numpy(rng.standard_normal((dims[mode], m))).to(dtype).double().numpy()
+    Us = [None] * 3
+    Us[mode] = _dev(U)
+    print("core", dims, mode, m, dtype, flush=True)
+    got = rt.rtucker_core(_dev(X, dtype), Us, modes=[mode]).double().cpu().numpy()
+    f = lambda x, u: np.moveaxis(np.tensordot(x, u, axes=([mode], [0])), -1, mode)  # noqa: E731
+    assert np.all(np.abs(got - f(X, U)) <= 2 * (dims[mode] + 8) * 2.0 ** -24 * f(np.abs(X), np.abs(U)))
