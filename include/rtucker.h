@@ -351,9 +351,9 @@ int rtucker_scaled_diff(const rt_tensor* A, const void* B, const double* g, doub
  * rtucker_decompose_batched_launch: only enqueues the kernels, reading the
  *  tables left in ws by an upload with the same arguments.  It copies nothing
  *  from the host and allocates nothing, so it can be captured in a graph.
- * rtucker_decompose_batched_autotune: times the whole batch for each pair of a
- *  row tile of the vector-ALU core contractions (8, 16, 32 rows) and a number of
- *  slabs that a wave of the sketch pass takes in turn (at most 1, 2 or 4), keeps
+ * rtucker_decompose_batched_autotune: times the whole batch for each row tile of
+ *  the vector-ALU core contractions (8, 16, 32 rows), with one slab at a time for
+ *  a wave of the sketch pass and, if a first mode has 256, with two there; keeps
  *  the fastest for this batch signature (sizes, ranks, subranks, p, dtype) for the
  *  rest of the process, writes chosen[0] = row tile and chosen[1] = slabs
  *  (chosen: nullable, 2 int32), and leaves the matching tables in ws.  It
@@ -361,8 +361,9 @@ int rtucker_scaled_diff(const rt_tensor* A, const void* B, const double* g, doub
  *  a file, the choice is also appended to it ("<signature key, 16 hex digits>
  *  <row tile> <slabs>" per line), and every batched call of a process that has the
  *  variable set reads the file once per path before it looks a signature up, so a
- *  later process starts tuned; lines that do not parse are skipped.  The slabs
- *  setting does not change any result; the row tile changes the summation order
+ *  later process starts tuned; lines that do not parse are skipped.  Slabs may be
+ *  1, 2 or 4 there: two are taken in first modes of 256 unless it is 1, and one in
+ *  all others.  The slabs setting does not change any result; the row tile changes the summation order
  *  of the vector-ALU contractions only.
  * rtucker_decompose_batched_tuning: host only; the setting the batched calls would
  *  use now for this signature (the cache, else the defaults 16 and 4): tuning[0] =

@@ -1052,7 +1052,7 @@ int plan_mode_contract(Ctx& c, const rt_tensor* P, const rt_tensor* Q, int32_t n
 // copies and can be captured in a graph.
 struct BatchTune {
   int core_mt = 16;  // row tile of the vector-ALU core contractions (8, 16 or 32)
-  int spb_cap = 4;   // most slabs a wave of the sketch pass takes in turn (1, 2 or 4)
+  int spb_cap = 4;   // most slabs a wave of the sketch pass takes in turn: 1, or two in first modes of 256 (2 and 4)
 };
 
 enum class BatchMode { kFull, kUploadOnly, kLaunchOnly };
@@ -1154,10 +1154,12 @@ int plan_batched_impl(Ctx& c, int32_t count, const rt_batch_item* items, int32_t
     // first sketch level: Z = X x_3 Phi_3, W = X x_2 Phi_2 (one pass over X)
     float* Z = static_cast<float*>(c.take(static_cast<size_t>(I0) * I1 * t.s[2] * 4));
     float* W = static_cast<float*>(c.take(static_cast<size_t>(I0) * t.s[1] * I2 * 4));
-    // a workgroup takes 4 spb slabs (spb per wave); more than one only in long tensors: 512 tensors
-    // of 32 .. 192 a mode take 820 us (binary32) and 568 us (bfloat16) with one slab a wave, 960 and
-    // 672 with up to four, whose last workgroups run alone
-    const int64_t spb = std::max<int64_t>(1, std::min<int64_t>(tune.spb_cap, I0 / 128));
+    // a workgroup takes 4 spb slabs, spb per wave.  One in short first modes: 512 tensors of 32 .. 192 a
+    // mode take 820 us (binary32) and 568 us (bfloat16), 960 and 672 with up to four, whose last
+    // workgroups run alone.  Two in the longest, which are of 256: whole batches of 1000 x (256 x 32 x 32) take
+    // 1473 and 1285 us, 1552 and 1339 with one; 512 x (256 x 48 x 96) 1652 and 1303, 1704 and 1337;
+    // 64 x 256^3 2127 and 1628, 2103 and 1661.
+    const int64_t spb = I0 >= 256 && tune.spb_cap > 1 ? 2 : 1;
     const int zc = zw_batch_class(I2) / 4 - 1;
     zw[zc].push_back(GZwJob{b.X, op[1], op[2], Z, W, I0, I1, I2, zw_blocks[zc], static_cast<int32_t>(t.s[1]),
                             static_cast<int32_t>(t.s[2]), static_cast<int32_t>(spb), 0});
@@ -1738,7 +1740,8 @@ int rtucker_decompose_batched_tuning(int32_t count, const rt_batch_item* items, 
 int rtucker_decompose_batched_autotune(int32_t count, const rt_batch_item* items, int32_t p, rt_dtype dtype,
                                        void* ws, size_t ws_bytes, void* stream, int32_t* chosen) {
   const int mts[3] = {8, 16, 32};
-  const int spbs[3] = {1, 2, 4};
+  bool two_slabs = false;  // two slabs a wave are another plan only where a first mode is long enough for them
+  for (int32_t i = 0; items && i < count; ++i) two_slabs = two_slabs || items[i].dims[0] >= 256;
   float best_ms = -1.0f;
   BatchTune best;
   hipEvent_t e0, e1;
@@ -1748,10 +1751,10 @@ int rtucker_decompose_batched_autotune(int32_t count, const rt_batch_item* items
     return RT_EHIP;
   }
   int status = RT_OK;
-  for (int ci = 0; ci < 9 && status == RT_OK; ++ci) {
+  for (int ci = 0; ci < (two_slabs ? 6 : 3) && status == RT_OK; ++ci) {
     BatchTune tune;
     tune.core_mt = mts[ci % 3];
-    tune.spb_cap = spbs[ci / 3];
+    tune.spb_cap = 1 + ci / 3;
     auto plan = [&](Ctx& c, BatchMode m) { return plan_batched_impl(c, count, items, p, dtype, tune, m); };
     status = run([&](Ctx& c) { return plan(c, BatchMode::kUploadOnly); }, ws, ws_bytes, stream);
     if (status) break;

@@ -182,3 +182,26 @@ def test_batched_validation():
     phis = [[dev(np.ones((9, 20))), dev(np.ones((2, 30))), dev(np.ones((2, 20)))]]
     with pytest.raises(rt.RtuckerError):
         rt.Batch([X], [(2, 2, 2)], 1, phis, s=[(9, 2, 2)]).run()  # subrank above 8
+
+
+# slabs a wave: the autotuner times the settings that are different plans (two only where a first mode is 256
+# long) and the outputs do not depend on the setting
+@pytest.mark.parametrize("first", [255, 256])
+def test_slabs_a_wave(first, tmp_path, monkeypatch):
+    rng = np.random.default_rng(first)
+    dims = [(first, 33, 40), (96, 48, 37), (first, 40, 17)]
+    ranks = [(5, 4, 4)] * 3
+    s = [rt.rtucker_sketch_sizes(d, r, P_OVER, "rhkron") for d, r in zip(dims, ranks)]
+    Xd = [dev(rng.standard_normal(d), torch.float32) for d in dims]
+    B = rt.Batch(Xd, ranks, P_OVER, _device_phis(synth.batch_phis(dims, s)), s)
+    key, outs = B.tuning()[2], []
+    for slabs in (1, 2, 4):
+        path = tmp_path / f"{slabs}.txt"
+        path.write_text(f"{key:016x} 16 {slabs}\n")
+        monkeypatch.setenv("RTUCKER_TUNE_CACHE", str(path))
+        assert B.tuning()[:2] == (16, slabs)
+        Gs, Us = B.run()
+        outs.append([host(t).copy() for t in Gs] + [host(u).copy() for us in Us for u in us])
+    for o in outs[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(outs[0], o))
+    assert B.autotune()[1] in ((1, 2) if first == 256 else (1,))
