@@ -277,7 +277,7 @@ hipError_t launch_ttm_grouped(const GTtmJob* jobs, const int32_t* blkjob, int co
                               rt_dtype xdt, int mt, hipStream_t st);
 
 // First sketch level (Z = X x_3 PhiQ: A x P x sQ, W = X x_2 PhiP: A x sP x Q) of one 3-way
-// tensor (A, P, Q) of a batch; Q <= 256, s <= 16, operands binary32; Z or W may be null.
+// tensor (A, P, Q) of a batch; P and Q <= 256, s <= 8, operands binary32; Z and W are both written.
 // Workgroups blk0 .. of the job each take a run of 4 spb slabs.
 struct GZwJob {
   const void* X;
