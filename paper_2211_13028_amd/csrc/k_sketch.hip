@@ -323,7 +323,9 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
             zacc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xr),
                                                                 __builtin_bit_cast(bf16x8, bq[ks]), zacc[mt], 0, 0, 0);
           }
-        // D layout: row 16 mt + 4 kg + v, column c = li
+        // D layout: row 16 mt + 4 kg + v, column c = li (addressed from the wave's own row, with one
+        // offset a lane: eight of them, kept through the loop, spilled registers)
+        const int left = pend - pb < 32 ? static_cast<int>(pend - pb) : 32, zoff = 4 * kg * sQ + li;
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -331,8 +333,8 @@ __global__ __launch_bounds__(kZWThreads) __attribute__((amdgpu_waves_per_eu(3)))
             const int row = 16 * mt + 4 * kg + v;
             if constexpr (CW > 1)
               zpart[buf][wave][row * 16 + li] = zacc[mt][v];
-            else if (li < sQ && pb + row < pend)
-              zout[(pb + row) * sQ + li] = zacc[mt][v];
+            else if (li < sQ && row < left)
+              (zout + (pb + 16 * mt + v) * sQ)[zoff] = zacc[mt][v];
           }
       }
       if (needW) {

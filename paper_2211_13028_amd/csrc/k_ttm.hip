@@ -950,6 +950,8 @@ __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a 
 // of a workgroup share the k range, and M is staged in LDS 64 k at a time, double-buffered, zero
 // past the range.  Bound: HBM.  Rows off the 16-byte grid ran on the vector ALU before, at a
 // twentieth of the rate: the core step of 293 x 544 x 387 took 456 us, now 67.
+// With four row tiles the registers do not suffice: with 512 threads five are put aside around the
+// loop, with 256 also a part of the next window of M, once in 64 k.
 template <int MT, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void ttm_mfma_bf16_kernel(
     const bf16_t* __restrict__ X, int64_t A, int64_t K, int64_t B, const bf16_t* __restrict__ Mop, int64_t m,
