@@ -13,6 +13,8 @@
 // is wave-uniform (scalar loads).  Row ranges or column ranges split over
 // several workgroups produce partial sums that a second kernel adds in a fixed
 // order.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace rt {
@@ -719,6 +721,16 @@ hipError_t zw_dispatch(const TX* X, int64_t A, int64_t P, int64_t Q, const TC* p
 
 bool sketch_zw_ok(rt_dtype, int64_t sP, int64_t sQ) { return sP >= 1 && sQ >= 1 && sP <= 8 && sQ <= 8; }
 
+// Where binary32 rows off the 16-byte grid are faster on the vector ALU, given the row ranges of all
+// slabs.  A matrix-core step of 16 rows takes a wave about 2 us however small the grid is; the vector ALU
+// splits the rows among up to 2048 workgroups but reduces every row of Z across a wave.  200 rows of 90
+// columns with s = 5: 15 us against 36 for 24 slabs, 36 and 36 for 192, 53 and 37 for 384; s = 3: 13 and 36,
+// 23 and 36, 35 and 36.  Past 256 columns a lane of the vector ALU has eight of them (300 x 510, s = 5:
+// 25 and 34 for 24 slabs, 49 and 37 for 96).
+static bool zw_few_slabs(int64_t ranges, int64_t Q, int64_t s) {
+  return Q % 4 != 0 && ranges < (s <= 4 ? (Q <= 256 ? 400 : 200) : (Q <= 256 ? 200 : 64));
+}
+
 ZWPlan sketch_zw_plan(rt_dtype xdt, int64_t A, int64_t P, int64_t Q, int64_t sP, int64_t sQ, bool needZ,
                       bool needW) {
   ZWPlan p;
@@ -766,11 +778,21 @@ ZWPlan sketch_zw_plan(rt_dtype xdt, int64_t A, int64_t P, int64_t Q, int64_t sP,
       }
     }
     p.rows_per_block = best_rows ? best_rows : ceil_div(P, step) * step;
-  } else {
+    if (mf32 && zw_few_slabs(A * ceil_div(P, p.rows_per_block), Q, std::max(sP, sQ))) {
+      p.mfma = false;
+      p.qblocks = ceil_div(Q, 64 * nq);
+      p.qcols = 64 * nq;
+      p.waves_per_slab = kZWWaves;
+    }
+  }
+  if (!p.mfma) {
     int64_t pb = 1;
     const int64_t target = 2048;
     if (A * p.qblocks < target) pb = ceil_div(target, A * p.qblocks);
-    const int64_t maxpb = ceil_div(P, 16);  // keep at least 16 rows per block
+    int64_t maxpb = ceil_div(P, 16);  // keep at least 16 rows per block
+    // (and, where a matrix-core pass would sum W in a few parts, no longer chain of parts: 33 of them, P = 520,
+    // had 1.2 times its error)
+    if (mf32 && P >= 16 && Q >= 16) maxpb = std::min<int64_t>(maxpb, 16);
     if (pb > maxpb) pb = maxpb;
     if (pb < 1) pb = 1;
     p.rows_per_block = ceil_div(P, pb);

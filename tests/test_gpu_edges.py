@@ -385,3 +385,24 @@ def test_sketch_second_level_groups(dims, s, dtype, keep):
         unit = 2.0 ** -53 if dtype == torch.float64 else 2.0 ** -24
         got = Ys[n].cpu().double().numpy()
         assert np.all(np.abs(got - want) <= sum(dims) * unit * bound + 1e-300), (n, np.abs(got - want).max())
+
+
+# binary32 rows off the 16-byte grid, on both sides of the rule that sends small grids to the vector ALU: 400 row
+# ranges up to 256 columns (200 past s = 4), 200 (64) beyond; up to 16 row ranges a slab, one of them cut
+@pytest.mark.parametrize("dims,s", [((1, 16, 17), 3), ((399, 17, 18), 4), ((400, 17, 18), 4), ((199, 130, 45), 5), ((200, 130, 45), 5),
+                                    ((199, 21, 257), 4), ((200, 21, 257), 4), ((63, 33, 258), 8), ((64, 33, 258), 8),
+                                    ((2, 1031, 91), 8), ((12, 520, 513), 3)])
+@pytest.mark.parametrize("want", [(True, True), (True, False), (False, True)])
+def test_f32_sketch_of_few_slabs(dims, s, want):
+    A, P, Q = dims
+    rng = np.random.default_rng(A + P + Q + s)
+    f32 = lambda *n: rng.standard_normal(n).astype(np.float32).astype(np.float64)  # noqa: E731
+    X, fP, fQ = f32(A, P, Q), f32(s, P), f32(s, Q)
+    print("sketch pass", dims, s, want, flush=True)
+    Z, W = rt.rtucker_sketch_pass(_dev(X, torch.float32), _dev(fP), _dev(fQ), want=want)
+    if want[0]:
+        bound = 2 * (Q + 8) * 2.0 ** -24 * (np.abs(X) @ np.abs(fQ).T)
+        assert np.all(np.abs(Z.double().cpu().numpy() - X @ fQ.T) <= bound)
+    if want[1]:
+        bound = 2 * (P + 8) * 2.0 ** -24 * np.matmul(np.abs(fP), np.abs(X))
+        assert np.all(np.abs(W.double().cpu().numpy() - np.matmul(fP, X)) <= bound)
