@@ -38,8 +38,10 @@ __device__ __forceinline__ void generic_accumulate(const TX* __restrict__ xp, in
   constexpr int kPer = MT * kGenKC / kWave;  // M elements per thread at the smallest block (one wave)
   const int nth = static_cast<int>(blockDim.x);
   for (int64_t k0 = kb; k0 < ke; k0 += kGenKC) {
-    // binary32: the sums of 64 k are added up (one chain over a long K rounds more)
-    constexpr bool kSums = std::is_same<TC, float>::value;
+    // binary32, four rows of M: the sums of 64 k are added up (one chain over a long K rounds more).
+    // Not with more rows, which hold the registers of waves in flight (a 256^3 projection step, whose
+    // expansions have K = 24 and m = 256: 586 us with such sums, 531 without).
+    constexpr bool kSums = std::is_same<TC, float>::value && MT == 4;
     TC part[MT];
 #pragma unroll
     for (int ii = 0; ii < MT; ++ii) part[ii] = kSums ? TC(0) : acc[ii];
