@@ -6,11 +6,13 @@
 //
 //  * ttm_generic: VALU kernel for every dtype and shape (one output column per
 //    thread, m split into register tiles, M chunks broadcast from LDS).
-//  * ttm_split:  matrix-core kernel for binary32 X (B >= 64, m <= 64): three
+//  * ttm_split_f32: matrix-core kernel for binary32 X (B >= 64, m <= 64): three
 //    bfloat16 terms a value, X streamed once, M split and staged in LDS.
-//  * ttm_mfma:   matrix-core kernels for bfloat16 X (B >= 64, m <= 64; M staged in LDS, operands
-//    re-packed in registers so that each lane holds 8 consecutive k of one column) and for the
-//    small binary32 contractions of one launch (the prepared M operand is read from L2).
+//  * ttm_mfma_f32, ttm_mfma_f32_grouped: binary32 products, M read from L2, for a short K or few rows
+//    of M on the 16-byte grid, and for the small contractions of one launch.
+//  * ttm_mfma_bf16: bfloat16 X (B >= 64, m <= 64), M staged in LDS, operands re-packed in registers so
+//    that each lane holds 8 consecutive k of one column; ttm_mfma_bf16_direct: the same with
+//    M read from the caches, for small tensors on the 16-byte grid.
 //  * ttm_mfma_last: the last mode (B == 1), X in rows of K contiguous values.
 #include <algorithm>
 #include <type_traits>
@@ -484,8 +486,8 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 // the result's norm against 64 bits, over that of binary32 products on the matrix cores: normal data
 // 0.38 (K = 64), 0.45 (100), 0.59 (267), 0.58 (1024), 0.44 (4096); values exp(5 N), whose sums are mostly
 // one product, 0.99 .. 1.13 (with all six products added to the accumulator 1.13 .. 1.6, and normal
-// data 0.65 .. 0.85); a single product (K = 1) 1.02.  Cost: 1393 -> 1409 us for the 1024 x 1024 x 512
-// decomposition, nothing measurable for three row tiles of M or fewer.
+// data 0.65 .. 0.85); a single product (K = 1) 1.02.  Cost: 460 -> 478 us for 1024 x 524288
+// with m = 49, nothing measurable for three row tiles of M or fewer.
 //
 // A wave owns 64 columns of one slab (lane j: four consecutive columns, at any 4-byte
 // boundary) and takes k in blocks of 32: lane group q loads the rows k0 + 8 q .. + 7, converts
@@ -495,14 +497,14 @@ __device__ __forceinline__ void ttm_f32_unit(const float* __restrict__ X, int64_
 //
 // Bound: HBM (1024 x 1024 x 512 with m = 49: 0.165 ms of matrix-core time at peak against 0.36 ms
 // of reading at 6.3 TB/s); the binary32 products before were bound by the matrix cores.  One after
-// the other, 1024 x 1024 x 512 with m = 49: 540 -> 480 us; 512 x 768 x 640 with m = 36 340 -> 212;
-// 128^4 with m = 27 280 -> 257.
+// the other, 1024 x 524288 with m = 49: 544 -> 478 us; 512 x 768 x 640 with m = 36 338 -> 213;
+// 128^4 with m = 27 285 -> 255 (first mode), 273 -> 232 (second).
 //
 // X and M are scaled by 2^24 before they are split, so that all terms of the smallest subnormal are
 // normal bfloat16 values, and the results are scaled back.  What that cannot hold (an infinity, which
 // splits into NaN; values above 2^104, results above 2^80) gives a result that is not finite, and the
-// wave then takes its columns once more, with binary32 products: one infinity in X of 1024 x 1024 x
-// 512 costs 35 us, one in every 195 rows of it, in every wave, 540.
+// wave then takes its columns once more, with binary32 products: one infinity in X of 1024 x
+// 524288 costs 46 us, one in every 195 rows of every column 840.
 constexpr float kSplitUp = 0x1p24f, kSplitDown = 0x1p-48f;
 constexpr int kSplitCols = 64;
 constexpr int kSplitWin = 64;                // k of M per staged window
