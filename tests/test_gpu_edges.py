@@ -128,7 +128,7 @@ def test_sketch_pass_f32_nonfinite_stays_in_its_row_and_column():
 
 
 # ------------------------------------------------------------------ binary32 contraction in three bfloat16 terms
-# 64-column waves of four or eight a workgroup (eight from k ranges past 512), 16-row tiles of M with
+# 64-column waves, four a workgroup (eight on much longer rows or k ranges), 16-row tiles of M with
 # one row more, 32-k blocks, 64-k windows, splits of k, rows at any 4-byte boundary.  A binary32
 # sum of K products is within (K + 8) 2^-24 of the sum of their magnitudes in any order; the
 # matrix cores may truncate where an addition rounds, hence twice that.

@@ -226,6 +226,8 @@ def test_core_single_modes():
         assert_entrywise(G, want, bound, 2e-5, f"core mode {k}")
 
 
+# (binary32 in three bfloat16 terms pads every width to whole tiles; the widths were chosen for a
+# kernel with a vector-ALU tail)
 @pytest.mark.parametrize("m", [17, 18, 33, 34, 49, 50, 48, 19])
 @pytest.mark.parametrize("K", [1024, 92, 90])
 def test_core_first_contraction_tail_rows(m, K):
@@ -243,6 +245,7 @@ def test_core_first_contraction_tail_rows(m, K):
     assert_entrywise(G, want, bound, 2e-5, f"core m={m} K={K}")
 
 
+# (64-column units in three bfloat16 terms: 4098 of them, the last one of 60 columns, M in windows of 64 k)
 @pytest.mark.parametrize("m", [17, 49, 50])
 @pytest.mark.parametrize("K", [92, 212])
 def test_core_first_contraction_unsplit(m, K):
